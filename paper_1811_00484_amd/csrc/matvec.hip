@@ -30,6 +30,7 @@
 // dense is stored).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <type_traits>
@@ -60,14 +61,14 @@ __device__ __forceinline__ void load_tw(c2<T>* dst, const c2<T>* src, int L, int
 }
 
 // ------------------------------- pass X+ --------------------------------
-template <typename TV, typename T, int W, int MAXE, int LC = 0>
+template <typename TV, typename T, int W, int MAXE>
 __device__ __forceinline__ void xfwd_body(const c2<TV>* __restrict__ x, const c2<TV>* __restrict__ eps,
                                              c2<T>* __restrict__ S1, FftPlan pl, const c2<T>* __restrict__ tw,
                                              int n1, int n2, int n3, int mode, const int* __restrict__ rhs_map, int bx, int by, int bz)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     c2<T>* buf = reinterpret_cast<c2<T>*>(smem_raw);
-    const int L1 = LC ? LC : pl.L;
+    const int L1 = pl.L;
     c2<T>* tws = buf + (size_t)L1 * (W + 1);
     const int tid = threadIdx.x;
     const int j0 = bx * W, k = by;
@@ -99,7 +100,7 @@ __device__ __forceinline__ void xfwd_body(const c2<TV>* __restrict__ x, const c2
         buf[i * (W + 1) + w] = mk<T>(0, 0);
     }
     __syncthreads();
-    fft_lds_len<-1, true, MAXE, LC>(buf, W, 1, W + 1, pl, tws, tid, NT);
+    fft_lds<-1, true, MAXE>(buf, W, 1, W + 1, pl, tws, tid, NT);
     for (int e = tid; e < W * L1; e += NT) {
         int w = e % W, i = e / W;
         int j = j0 + w;
@@ -108,13 +109,13 @@ __device__ __forceinline__ void xfwd_body(const c2<TV>* __restrict__ x, const c2
 }
 
 // ------------------------------- pass Y+ --------------------------------
-template <typename T, int W, int MAXE, int LC = 0>
+template <typename T, int W, int MAXE>
 __device__ __forceinline__ void yfwd_body(const c2<T>* __restrict__ S1, c2<T>* __restrict__ S2, FftPlan pl,
                                              const c2<T>* __restrict__ tw, int L1, int n2, int n3, int bx, int by, int bz)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     c2<T>* buf = reinterpret_cast<c2<T>*>(smem_raw);
-    const int L2 = LC ? LC : pl.L;
+    const int L2 = pl.L;
     c2<T>* tws = buf + (size_t)L2 * (W + 1);
     const int tid = threadIdx.x;
     const int k0 = bx * W, i = by;
@@ -132,7 +133,7 @@ __device__ __forceinline__ void yfwd_body(const c2<T>* __restrict__ S1, c2<T>* _
         buf[j * (W + 1) + w] = mk<T>(0, 0);
     }
     __syncthreads();
-    fft_lds_len<-1, true, MAXE, LC>(buf, W, 1, W + 1, pl, tws, tid, NT);
+    fft_lds<-1, true, MAXE>(buf, W, 1, W + 1, pl, tws, tid, NT);
     for (int e = tid; e < W * L2; e += NT) {
         int w = e % W, j = e / W;
         int k = k0 + w;
@@ -141,13 +142,13 @@ __device__ __forceinline__ void yfwd_body(const c2<T>* __restrict__ S1, c2<T>* _
 }
 
 // ------------------------------- pass Y- --------------------------------
-template <typename T, int W, int MAXE, int LC = 0>
+template <typename T, int W, int MAXE>
 __device__ __forceinline__ void yinv_body(const c2<T>* __restrict__ S2, c2<T>* __restrict__ S3, FftPlan pl,
                                              const c2<T>* __restrict__ tw, int L1, int n2, int n3, int bx, int by, int bz)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     c2<T>* buf = reinterpret_cast<c2<T>*>(smem_raw);
-    const int L2 = LC ? LC : pl.L;
+    const int L2 = pl.L;
     c2<T>* tws = buf + (size_t)L2 * (W + 1);
     const int tid = threadIdx.x;
     const int k0 = bx * W, i = by;
@@ -161,7 +162,7 @@ __device__ __forceinline__ void yinv_body(const c2<T>* __restrict__ S2, c2<T>* _
         buf[j * (W + 1) + w] = v;
     }
     __syncthreads();
-    fft_lds_len<1, true, MAXE, LC>(buf, W, 1, W + 1, pl, tws, tid, NT);
+    fft_lds<1, true, MAXE>(buf, W, 1, W + 1, pl, tws, tid, NT);
     for (int e = tid; e < W * n2; e += NT) {
         int w = e / n2, j = e - w * n2;
         int k = k0 + w;
@@ -170,7 +171,7 @@ __device__ __forceinline__ void yinv_body(const c2<T>* __restrict__ S2, c2<T>* _
 }
 
 // ------------------------------- pass X- --------------------------------
-template <typename TV, typename T, int W, int MAXE, int LC = 0>
+template <typename TV, typename T, int W, int MAXE>
 __device__ __forceinline__ void xinv_body(const c2<T>* __restrict__ S3, const c2<TV>* __restrict__ x,
                                              const c2<TV>* __restrict__ eps, c2<TV>* __restrict__ y, FftPlan pl,
                                              const c2<T>* __restrict__ tw, int n1, int n2, int n3, int mode,
@@ -178,7 +179,7 @@ __device__ __forceinline__ void xinv_body(const c2<T>* __restrict__ S3, const c2
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     c2<T>* buf = reinterpret_cast<c2<T>*>(smem_raw);
-    const int L1 = LC ? LC : pl.L;
+    const int L1 = pl.L;
     c2<T>* tws = buf + (size_t)L1 * (W + 1);
     const int tid = threadIdx.x;
     const int j0 = bx * W, k = by;
@@ -196,7 +197,7 @@ __device__ __forceinline__ void xinv_body(const c2<T>* __restrict__ S3, const c2
         buf[i * (W + 1) + w] = v;
     }
     __syncthreads();
-    fft_lds_len<1, true, MAXE, LC>(buf, W, 1, W + 1, pl, tws, tid, NT);
+    fft_lds<1, true, MAXE>(buf, W, 1, W + 1, pl, tws, tid, NT);
     for (int e = tid; e < W * n1; e += NT) {
         int w = e / n1, i = e - w * n1;
         int j = j0 + w;
@@ -376,38 +377,7 @@ __device__ __forceinline__ void zmid_body(c2<T>* __restrict__ S2, FftPlan pl, co
     }
 }
 
-// ----------------------- single-instance kernels --------------------------
-template <typename TV, typename T, int W, int MAXE, int LC = 0>
-__global__ void __launch_bounds__(NT) k_xfwd(const c2<TV>* __restrict__ x, const c2<TV>* __restrict__ eps,
-                                             c2<T>* __restrict__ S1, FftPlan pl, const c2<T>* __restrict__ tw,
-                                             int n1, int n2, int n3, int mode, const int* __restrict__ rhs_map)
-{
-    xfwd_body<TV, T, W, MAXE, LC>(x, eps, S1, pl, tw, n1, n2, n3, mode, rhs_map, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
-template <typename T, int W, int MAXE, int LC = 0>
-__global__ void __launch_bounds__(NT) k_yfwd(const c2<T>* __restrict__ S1, c2<T>* __restrict__ S2, FftPlan pl,
-                                             const c2<T>* __restrict__ tw, int L1, int n2, int n3)
-{
-    yfwd_body<T, W, MAXE, LC>(S1, S2, pl, tw, L1, n2, n3, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
-template <typename T, int W, int MAXE, int LC = 0>
-__global__ void __launch_bounds__(NT) k_yinv(const c2<T>* __restrict__ S2, c2<T>* __restrict__ S3, FftPlan pl,
-                                             const c2<T>* __restrict__ tw, int L1, int n2, int n3)
-{
-    yinv_body<T, W, MAXE, LC>(S2, S3, pl, tw, L1, n2, n3, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
-template <typename TV, typename T, int W, int MAXE, int LC = 0>
-__global__ void __launch_bounds__(NT) k_xinv(const c2<T>* __restrict__ S3, const c2<TV>* __restrict__ x,
-                                             const c2<TV>* __restrict__ eps, c2<TV>* __restrict__ y, FftPlan pl,
-                                             const c2<T>* __restrict__ tw, int n1, int n2, int n3, int mode,
-                                             const int* __restrict__ rhs_map)
-{
-    xinv_body<TV, T, W, MAXE, LC>(S3, x, eps, y, pl, tw, n1, n2, n3, mode, rhs_map, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-
+// ----------------------- single-instance z kernel --------------------------
 template <typename T, int MAXE>
 __global__ void __launch_bounds__(NT) k_zmid(c2<T>* __restrict__ S2, FftPlan pl, const c2<T>* __restrict__ tw,
                                              ZArgs a, const c2<T>* __restrict__ core,
@@ -577,7 +547,9 @@ size_t matvec_ws_elems(const DeviceOp& op, int nrhs)
     const OpView& v = op.view;
     size_t s2 = (size_t)3 * v.L[1] * v.L[0] * v.n[2];
     size_t s1 = (size_t)3 * v.n[2] * v.L[0] * v.n[1];
-    return (s2 + s1) * (size_t)nrhs;
+    // S1 also holds the z pass's V tables (larger than S1 only on grids whose
+    // z rank reaches n3)
+    return s2 * (size_t)nrhs + std::max(s1 * (size_t)nrhs, zv_elems(v));
 }
 
 template <typename T>
@@ -597,35 +569,19 @@ static size_t z_lds_bytes(const OpView& v, int G)
     default: { constexpr int Wc = 1; __VA_ARGS__; } break;               \
     }
 
-// Default tile width of the mixed-radix X/Y kernels, and the lengths whose
-// radix sequence those kernels take at compile time (the sphere series'
-// 2n = 60 ... 300; the register-FFT lengths have kernels of their own)
-template <typename T>
-constexpr int kWDefault = sizeof(T) == 4 ? 16 : 8;
-
-template <class F>
-static void with_lc(int L, F&& f)
-{
-    switch (L) {
-    case 60: f(std::integral_constant<int, 60>{}); break;
-    case 120: f(std::integral_constant<int, 120>{}); break;
-    case 180: f(std::integral_constant<int, 180>{}); break;
-    case 240: f(std::integral_constant<int, 240>{}); break;
-    case 300: f(std::integral_constant<int, 300>{}); break;
-    default: f(std::integral_constant<int, 0>{}); break;
-    }
-}
-
 // One pass of the matvec on explicit buffers (see launch_matvec for the
 // layouts): pass 0 reads x and writes S1 (out), 1 reads S1 (in) and writes
 // S2 (out), 2 transforms S2 in place (out), 3 reads S2 (in) and writes S3
 // (out), 4 reads S3 (in) and writes y (out).  ident (passes 0 and 4 only):
 // the transform is replaced by the identity, so only the pass's index maps
 // (padding, transposes, cropping; pass 4 with the bare epilogue) remain.
+// zv: scratch of zv_elems() for pass 2's V tables; without it (a caller that
+// has none, vie_debug_pass under stream capture) the z pass of the lengths
+// without a register-FFT kernel contracts the cores in every workgroup.
 template <typename TV, typename T>
 hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<TV>* eps, const c2<TV>* x,
                     const void* in, void* out, int nrhs, hipStream_t s, const int* rhs_map, std::string& err,
-                    bool ident)
+                    bool ident, c2<T>* zv)
 {
     const OpView& v = op.view;
     const int n1 = v.n[0], n2 = v.n[1], n3 = v.n[2];
@@ -645,59 +601,27 @@ hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<
         fac = op.d32.fac;
         dense = op.dense32;
     }
-    constexpr int MAXE_XY = 32;   // W * L <= MAXE * NT for W*L <= 8192
     constexpr int MAXE_Z = 24;    // 3 * G * L3 <= 6144
     const bool allow_fast = g_kernel_path == 0;
-    // the identity "transform": a plan without stages leaves the LDS tile as loaded
-    FftPlan id0 = op.plan[0];
-    id0.nst = 0;
-    const FftPlan& px = ident ? id0 : op.plan[0];
     PassTimer timer(pass, s);
-    if (pass == 0) {
-        c2<T>* S1 = reinterpret_cast<c2<T>*>(out);
+    if (pass != 2) {
+        const int kind = pass < 2 ? pass : pass - 1;   // X+, Y+, Y-, X-
+        const int L = (kind == 0 || kind == 3) ? L1 : L2, axis = (kind == 0 || kind == 3) ? 0 : 1;
         if (ident) {
             if constexpr (std::is_same<TV, T>::value) {
-                if (allow_fast && xy_ident_fast<T>(0, L1, nullptr, S1, x, tw[0], n1, n2, n3, L1, L2, nrhs, s))
+                const c2<T>* xi = kind == 0 ? x : nullptr;
+                if (allow_fast && xy_ident_fast<T>(kind, L, in, out, xi, tw[axis], n1, n2, n3, L1, L2, nrhs, s))
                     return hipGetLastError();
             }
-        } else if (allow_fast && xy_pass_fast<TV, T>(0, L1, nullptr, S1, x, eps, tw[0], n1, n2, n3, L1, L2, mode,
+        } else if (allow_fast && xy_pass_fast<TV, T>(kind, L, in, out, x, eps, tw[axis], n1, n2, n3, L1, L2, mode,
                                                      nrhs, rhs_map, s)) {
             return hipGetLastError();
         }
-        int W = tile_width<T>(op.max_lds, L1);
-        if ((size_t)W * L1 > (size_t)MAXE_XY * NT) { err = "x length too large"; return hipErrorInvalidValue; }
-        size_t lds = (size_t)(W + 1) * L1 * sizeof(c2<T>) + (size_t)L1 * sizeof(c2<T>);
-        dim3 grid((n2 + W - 1) / W, n3, nrhs * 3);
-        VIE_W_DISPATCH(W, {
-            auto launch = [&](auto lc) {
-                auto kern = k_xfwd<TV, T, Wc, MAXE_XY, decltype(lc)::value>;
-                (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, x, eps, S1, px, tw[0], n1, n2, n3,
-                                   ident ? (int)MODE_N : mode, rhs_map);
-            };
-            if constexpr (Wc == kWDefault<T>) with_lc(ident ? 0 : L1, launch);
-            else launch(std::integral_constant<int, 0>{});
-        });
-    } else if (pass == 1) {
-        const c2<T>* S1 = reinterpret_cast<const c2<T>*>(in);
-        c2<T>* S2 = reinterpret_cast<c2<T>*>(out);
-        if (allow_fast && xy_pass_fast<TV, T>(1, L2, S1, S2, x, eps, tw[1], n1, n2, n3, L1, L2, mode, nrhs,
-                                              rhs_map, s))
-            return hipGetLastError();
-        int W = tile_width<T>(op.max_lds, L2);
-        if ((size_t)W * L2 > (size_t)MAXE_XY * NT) { err = "y length too large"; return hipErrorInvalidValue; }
-        size_t lds = (size_t)(W + 1) * L2 * sizeof(c2<T>) + (size_t)L2 * sizeof(c2<T>);
-        dim3 grid((n3 + W - 1) / W, L1, nrhs * 3);
-        VIE_W_DISPATCH(W, {
-            auto launch = [&](auto lc) {
-                auto kern = k_yfwd<T, Wc, MAXE_XY, decltype(lc)::value>;
-                (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, S1, S2, op.plan[1], tw[1], L1, n2, n3);
-            };
-            if constexpr (Wc == kWDefault<T>) with_lc(L2, launch);
-            else launch(std::integral_constant<int, 0>{});
-        });
-    } else if (pass == 2) {
+        if (!xy_pass_mix<TV, T>(op, kind, in, out, x, eps, mode, nrhs, rhs_map, ident, s)) {
+            err = axis == 0 ? "x length too large" : "y length too large";
+            return hipErrorInvalidValue;
+        }
+    } else {
         c2<T>* S2 = reinterpret_cast<c2<T>*>(out);
         if (op.nhat_source == 1 && dense == nullptr) {
             err = "dense spectrum not materialised";
@@ -709,6 +633,7 @@ hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<
             err = "BF16 z pass could not be launched";
             return hipErrorInvalidValue;
         }
+        if (zv && z_pass_mix<T>(op, mode, nrhs, S2, zv, s)) return hipGetLastError();
         int G = 4;
         while (G > 1 && z_lds_bytes<T>(v, G) > op.max_lds) G /= 2;
         size_t lds = z_lds_bytes<T>(v, G);
@@ -724,49 +649,6 @@ hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<
         auto kern = k_zmid<T, MAXE_Z>;
         (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, S2, op.plan[2], tw[2], za, core, fac, dense);
-    } else if (pass == 3) {
-        const c2<T>* S2 = reinterpret_cast<const c2<T>*>(in);
-        c2<T>* S3 = reinterpret_cast<c2<T>*>(out);
-        if (allow_fast && xy_pass_fast<TV, T>(2, L2, S2, S3, x, eps, tw[1], n1, n2, n3, L1, L2, mode, nrhs,
-                                              rhs_map, s))
-            return hipGetLastError();
-        int W = tile_width<T>(op.max_lds, L2);
-        size_t lds = (size_t)(W + 1) * L2 * sizeof(c2<T>) + (size_t)L2 * sizeof(c2<T>);
-        dim3 grid((n3 + W - 1) / W, L1, nrhs * 3);
-        VIE_W_DISPATCH(W, {
-            auto launch = [&](auto lc) {
-                auto kern = k_yinv<T, Wc, MAXE_XY, decltype(lc)::value>;
-                (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, S2, S3, op.plan[1], tw[1], L1, n2, n3);
-            };
-            if constexpr (Wc == kWDefault<T>) with_lc(L2, launch);
-            else launch(std::integral_constant<int, 0>{});
-        });
-    } else {
-        const c2<T>* S3 = reinterpret_cast<const c2<T>*>(in);
-        c2<TV>* y = reinterpret_cast<c2<TV>*>(out);
-        if (ident) {
-            if constexpr (std::is_same<TV, T>::value) {
-                if (allow_fast && xy_ident_fast<T>(3, L1, S3, y, nullptr, tw[0], n1, n2, n3, L1, L2, nrhs, s))
-                    return hipGetLastError();
-            }
-        } else if (allow_fast && xy_pass_fast<TV, T>(3, L1, S3, y, x, eps, tw[0], n1, n2, n3, L1, L2, mode, nrhs,
-                                                     rhs_map, s)) {
-            return hipGetLastError();
-        }
-        int W = tile_width<T>(op.max_lds, L1);
-        size_t lds = (size_t)(W + 1) * L1 * sizeof(c2<T>) + (size_t)L1 * sizeof(c2<T>);
-        dim3 grid((n2 + W - 1) / W, n3, nrhs * 3);
-        VIE_W_DISPATCH(W, {
-            auto launch = [&](auto lc) {
-                auto kern = k_xinv<TV, T, Wc, MAXE_XY, decltype(lc)::value>;
-                (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, S3, x, eps, y, px, tw[0], n1, n2, n3,
-                                   ident ? (int)MODE_N : mode, rhs_map);
-            };
-            if constexpr (Wc == kWDefault<T>) with_lc(ident ? 0 : L1, launch);
-            else launch(std::integral_constant<int, 0>{});
-        });
     }
     return hipGetLastError();
 }
@@ -788,18 +670,22 @@ hipError_t launch_matvec(const DeviceOp& op, int mode, int recon, const c2<TV>* 
     void* const ins[5] = {nullptr, S1, S2, S2, S1};
     void* const outs[5] = {S1, S2, S2, S1, y};
     for (int p = 0; p < 5; ++p) {
-        hipError_t e = run_pass<TV, T>(op, p, mode, recon, eps, x, ins[p], outs[p], nrhs, s, rhs_map, err, false);
+        // S1 is dead between Y+ and Y-: the z pass's V tables take its place
+        hipError_t e = run_pass<TV, T>(op, p, mode, recon, eps, x, ins[p], outs[p], nrhs, s, rhs_map, err, false, S1);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 template hipError_t run_pass<float, float>(const DeviceOp&, int, int, int, const c2<float>*, const c2<float>*,
-                                           const void*, void*, int, hipStream_t, const int*, std::string&, bool);
+                                           const void*, void*, int, hipStream_t, const int*, std::string&, bool,
+                                           c2<float>*);
 template hipError_t run_pass<double, double>(const DeviceOp&, int, int, int, const c2<double>*, const c2<double>*,
-                                             const void*, void*, int, hipStream_t, const int*, std::string&, bool);
+                                             const void*, void*, int, hipStream_t, const int*, std::string&, bool,
+                                             c2<double>*);
 template hipError_t run_pass<double, float>(const DeviceOp&, int, int, int, const c2<double>*, const c2<double>*,
-                                            const void*, void*, int, hipStream_t, const int*, std::string&, bool);
+                                            const void*, void*, int, hipStream_t, const int*, std::string&, bool,
+                                            c2<float>*);
 
 template hipError_t launch_matvec<float, float>(const DeviceOp&, int, int, const c2<float>*, const c2<float>*,
                                                 c2<float>*, int, c2<float>*, hipStream_t, const int*,

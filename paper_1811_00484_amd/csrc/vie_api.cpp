@@ -958,12 +958,26 @@ static vie_status debug_pass_common(const char* who, const vie_op* op, int pass,
     if (pass == 2 && in != out) e = hipMemcpyAsync(out, in, nin, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return hip_fail(e, w.c_str());
     std::string err;
+    // pass 2 outside a matvec has no S1 to hold the V tables: take scratch for
+    // the call (not under stream capture, where nothing can be allocated)
+    void* zv = nullptr;
+    if (pass == 2) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        e = hipStreamIsCapturing(s, &cap);
+        if (e == hipSuccess && cap == hipStreamCaptureStatusNone) e = hipMalloc(&zv, zv_elems(v) * el);
+        if (e != hipSuccess) return hip_fail(e, w.c_str());
+    }
     if (dtype == VIE_C128)
         e = run_pass<double, double>(op->d, pass, mode, 0, (const c2<double>*)eps_c, (const c2<double>*)x, in, out,
-                                     nrhs, s, nullptr, err, ident);
+                                     nrhs, s, nullptr, err, ident, (c2<double>*)zv);
     else
         e = run_pass<float, float>(op->d, pass, mode, recon == VIE_RECON_BF16 ? 1 : 0, (const c2<float>*)eps_c,
-                                   (const c2<float>*)x, in, out, nrhs, s, nullptr, err, ident);
+                                   (const c2<float>*)x, in, out, nrhs, s, nullptr, err, ident, (c2<float>*)zv);
+    if (zv) {
+        const hipError_t es = hipStreamSynchronize(s);
+        (void)hipFree(zv);
+        if (e == hipSuccess) e = es;
+    }
     if (e != hipSuccess) {
         if (!err.empty()) return fail(VIE_E_UNSUPPORTED, w + ": " + err);
         return hip_fail(e, w.c_str());

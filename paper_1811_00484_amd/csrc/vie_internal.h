@@ -179,7 +179,7 @@ hipError_t launch_matvec(const DeviceOp& op, int mode, int recon, const c2<TV>* 
 template <typename TV, typename T>
 hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<TV>* eps, const c2<TV>* x,
                     const void* in, void* out, int nrhs, hipStream_t s, const int* rhs_map, std::string& err,
-                    bool ident);
+                    bool ident, c2<T>* zv);
 
 // Multi-instance matvec: one launch per pass over all instances (mixed-radix
 // LDS kernels).  tab_dev: device scratch for the instance table.
@@ -217,6 +217,13 @@ bool xy_pass_fast(int kind, int L, const void* in, void* out, const c2<TV>* x, c
 template <typename T>
 bool xy_ident_fast(int kind, int L, const void* in, void* out, const c2<T>* x, const c2<T>* tw, int n1, int n2,
                    int n3, int L1, int L2, int nrhs, hipStream_t s);
+// mixed-radix passes of any length (matvec_mix.hip); false = does not fit
+template <typename TV, typename T>
+bool xy_pass_mix(const DeviceOp& op, int kind, const void* in, void* out, const c2<TV>* x, const c2<TV>* eps,
+                 int mode, int nrhs, const int* rhs_map, bool ident, hipStream_t s);
+size_t zv_elems(const OpView& v);   // complex elements of the z pass's V tables
+template <typename T>
+bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hipStream_t s);
 // recon 1: N^ tables from the BF16 z factors on MFMA (T = float only)
 template <typename T>
 bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, const c2<T>* tw, const c2<T>* core,
