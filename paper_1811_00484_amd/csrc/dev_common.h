@@ -59,6 +59,17 @@ __device__ __forceinline__ c2<T> mul_i(c2<T> a)
     return DIR > 0 ? mk<T>(-a.y, a.x) : mk<T>(a.y, -a.x);
 }
 
+// Read through a pointer that the kernel found in memory (a descriptor, not an
+// argument) and that points to global memory: a plain read would be a flat
+// one, which waits for the LDS and the scalar loads too.
+template <typename T>
+__device__ __forceinline__ c2<T> ldg(const c2<T>* p)
+{
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    const v2 v = *(const __attribute__((address_space(1))) v2*)p;
+    return mk<T>(v.x, v.y);
+}
+
 template <typename TO, typename TI>
 __device__ __forceinline__ c2<TO> cvt(c2<TI> a)
 {

@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include "mix_fft.h"
+#include "v_rows.h"
 #include "vie_internal.h"
 
 namespace vie {
@@ -386,70 +387,25 @@ bool xy_pass_mix(const DeviceOp& op, int kind, const void* in, void* out, const 
 }
 
 // ---------------------------------------------------------------------------
-// V tables: V[((k2 (n1 + 1) + k1) nc + c) rs + g], c the stored components
-// (six, or K's three), rs the largest z rank.  One workgroup per (k2, c).
+// V tables: V[((k2 nc + c) (n1 + 1) + k1) rs + g], c the stored components (six,
+// or K's three), zero for g beyond the component's z rank (rs: the largest one
+// in whole batches of eight, so that the z pass reads and sums without a
+// branch).  One workgroup per (k2, c).
 template <typename T>
-__global__ void __launch_bounds__(256) k_zv(OpView v, const c2<T>* __restrict__ core, const c2<T>* __restrict__ fac,
-                                            int rs, c2<T>* __restrict__ V)
+__global__ void __launch_bounds__(kVNT) k_zv(OpView v, const c2<T>* __restrict__ core, const c2<T>* __restrict__ fac,
+                                             int lanes, int rs, c2<T>* __restrict__ V)
 {
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    c2<T>* Wc = reinterpret_cast<c2<T>*>(smem_raw);   // [r1][r3], or [R] for a superdiagonal core
     const int k2 = blockIdx.x, nc = gridDim.y, ci = blockIdx.y, c = 6 - nc + ci;
-    const int r1 = v.r[c][0], r2 = v.r[c][1], r3 = v.r[c][2];
-    const c2<T>* G = core + v.core_off[c];
-    const c2<T>* U1 = fac + v.fac_off[c][0];
-    const c2<T>* U2 = fac + v.fac_off[c][1] + (long)k2 * r2;
-    c2<T>* out = V + ((long)k2 * (v.n[0] + 1) * nc + ci) * rs;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int total = (v.n[0] + 1) * r3;
-    if (v.cp) {
-        for (int l = tid; l < r3; l += nt) Wc[l] = G[(long)l * (r3 * r3 + r3 + 1)] * U2[l];
-        __syncthreads();
-        for (int e = tid; e < total; e += nt) {
-            const int k1 = e / r3, l = e - k1 * r3;
-            out[(long)k1 * nc * rs + l] = U1[e] * Wc[l];
-        }
-        return;
-    }
-    for (int e = tid; e < r1 * r3; e += nt) {
-        const int al = e / r3, ga = e - al * r3;
-        const c2<T>* g = G + (long)al * r2 * r3 + ga;
-        c2<T> acc = mk<T>(0, 0);
-        for (int b0 = 0; b0 < r2; b0 += 8) {
-            c2<T> gv[8], uv[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const bool ok = b0 + q < r2;
-                gv[q] = ok ? g[(long)(b0 + q) * r3] : mk<T>(0, 0);
-                uv[q] = ok ? U2[b0 + q] : mk<T>(0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) fma_c(acc, gv[q], uv[q]);
-        }
-        Wc[e] = acc;
-    }
-    __syncthreads();
-    for (int e = tid; e < total; e += nt) {
-        const int k1 = e / r3, ga = e - k1 * r3;
-        const c2<T>* u = U1 + (long)k1 * r1;
-        c2<T> acc = mk<T>(0, 0);
-        for (int a0 = 0; a0 < r1; a0 += 8) {
-            c2<T> uv[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) uv[q] = a0 + q < r1 ? u[a0 + q] : mk<T>(0, 0);
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (a0 + q < r1) fma_c(acc, uv[q], Wc[(a0 + q) * r3 + ga]);
-        }
-        out[(long)k1 * nc * rs + ga] = acc;
-    }
+    const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
+    v_rows<T>(core + v.core_off[c], fac + v.fac_off[c][0], fac + v.fac_off[c][1] + (long)k2 * r2, v.r[c][0], r2,
+              v.r[c][2], n1p1, lanes, v.rmax, rs, v.cp, V + ((long)k2 * nc + ci) * n1p1 * rs);
 }
 
 static int zv_stride(const OpView& v)
 {
     int rs = 1;
     for (int c = v.fam ? 3 : 0; c < 6; ++c) rs = rs > v.r[c][2] ? rs : v.r[c][2];
-    return rs;
+    return (rs + 7) & ~7;
 }
 
 size_t zv_elems(const OpView& v)
@@ -461,9 +417,11 @@ template <typename T>
 static void launch_zv(const DeviceOp& op, const c2<T>* core, const c2<T>* fac, c2<T>* V, hipStream_t s)
 {
     const OpView& v = op.view;
-    const size_t lds = sizeof(c2<T>) * (v.cp ? (size_t)v.rmax : (size_t)v.rmax * v.rmax);
+    const int rs = zv_stride(v), lanes = v_rows_lanes<T>(v.n[0] + 1, v.rmax, rs);
+    const size_t lds = v_rows_lds<T>(lanes, v.rmax, rs);
     (void)hipFuncSetAttribute((const void*)k_zv<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_zv<T>, dim3(v.n[1] + 1, v.fam ? 3 : 6), dim3(256), lds, s, v, core, fac, zv_stride(v), V);
+    hipLaunchKernelGGL(k_zv<T>, dim3(v.n[1] + 1, v.fam ? 3 : 6), dim3(kVNT), lds, s, v, core, fac, lanes,
+                       rs, V);
 }
 
 // ---------------------------------------------------------------------------
@@ -646,19 +604,27 @@ __global__ void __launch_bounds__(512) k_mix_z(c2<T>* __restrict__ S2, const c2<
             continue;
         }
         const c2<T>* U3 = fac + a.fac3t_off[cc] + k3;
-        const c2<T>* va = V + (((long)k2 * (n1 + 1) + kA) * NC + c) * a.rs;
-        const c2<T>* vb = nq > 1 ? va + NC * a.rs : va;
-        c2<T> s0 = mk<T>(0, 0), s1 = mk<T>(0, 0);
-        for (int g0 = 0; g0 < r3; g0 += 8) {
-            c2<T> u[8];
+        const c2<T>* va = V + (((long)k2 * NC + c) * (n1 + 1) + kA) * a.rs;
+        const c2<T>* vb = nq > 1 ? va + a.rs : va;
+        c2<T> s0 = mk<T>(0, 0), s1 = mk<T>(0, 0), u[8], w[8];
+        // sixteen z factors in flight; rows beyond the rank meet zeros of V
+        auto factors = [&](c2<T>(&d)[8], int g0) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) u[q] = g0 + q < r3 ? U3[(long)(g0 + q) * n3p1] : mk<T>(0, 0);
+            for (int q = 0; q < 8; ++q) d[q] = U3[(long)min(g0 + q, r3 - 1) * n3p1];
+        };
+        auto sum = [&](const c2<T>(&d)[8], int g0) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (g0 + q < r3) {
-                    fma_c(s0, va[g0 + q], u[q]);
-                    fma_c(s1, vb[g0 + q], u[q]);
-                }
+            for (int q = 0; q < 8; ++q) {
+                fma_c(s0, va[g0 + q], d[q]);
+                fma_c(s1, vb[g0 + q], d[q]);
+            }
+        };
+        factors(u, 0);
+        for (int g0 = 0; g0 < r3; g0 += 16) {
+            if (g0 + 8 < r3) factors(w, g0 + 8);
+            sum(u, g0);
+            if (g0 + 16 < r3) factors(u, g0 + 16);
+            if (g0 + 8 < r3) sum(w, g0 + 8);
         }
         tab[c * n3p1 + k3] = mk<T>(s0.x, cs * s0.y);
         if (nq > 1) tab[(NC + c) * n3p1 + k3] = mk<T>(s1.x, cs * s1.y);

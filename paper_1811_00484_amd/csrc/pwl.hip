@@ -34,23 +34,40 @@
 // The coupled JM operator of eq. 4 takes [J; M] as two right-hand sides of
 // the N and of the K product and combines them per voxel.
 //
-// Kernel layout: one 512-thread workgroup per mirror group of pencils (as
-// the generic z pass), the twelve pencils of each in LDS; every thread owns
-// up to EPT Fourier-domain positions and keeps their twelve output
-// components in registers while the ten pairs go by, in batches whose
-// tables fit the LDS together, each table rebuilt from the Tucker form:
-// W_c(k2) = G_c x2 U2_c(k2, :) comes from a small kernel that runs first
-// (once per canonical k2, not per pencil group), V_c = U1_c(k1, :) W_c(k2),
-// then the z factor per k3.
+// Kernel layout: the V rows of every stored tensor, V_c(k1, k2, :) =
+// U1_c(k1, :) (G_c x2 U2_c(k2, :)), come from a kernel that runs first.  A
+// workgroup of the z pass takes one mirror group of pencils (four; two or one
+// where they do not fit), builds the group's N^ tables from V and the z
+// factors and keeps all ten pairs' (or as many as the LDS holds) while the
+// right-hand sides go by.  The twelve pencils of each of the group's (k1, k2)
+// are transformed in place in LDS (mix_fft.h) and every thread then owns one
+// Fourier position: twelve values in, the sixteen blocks accumulated in
+// registers, twelve values out.
+//
+// Signs: N^_(l,p),(l',q) at a mirrored position is the octant's value times
+// d_(l,p) d_(l',q), d_(l,p) = (-1)^(f_p + f_(l-1)) with f_a = 1 on a mirrored
+// axis (K: times (-1)^(f1 + f2 + f3) too), so twelve values change sign on
+// the way in and on the way out instead of sixty table entries.
+//
+// What bounds it: at 120^3 complex64 a group issues about 38 k cycles of vector
+// instructions per SIMD set (0.9 ms in all) in phases that alternate with LDS
+// traffic behind barriers, one 960-thread workgroup per CU; leaving phases out
+// of a copy, the tables take 0.5 ms, the product 0.3, the transforms and the
+// rest 0.6.  The previous kernel (V contracted in every group, a table entry
+// read per sign, stages through two barriers) took 3.6 ms for the pass, 1.45
+// now; whole products, MI355X: 120^3 4.63 -> 2.14 ms, 36 x 45 x 50 complex128
+// adjoint 0.90 -> 0.28 ms, the coupled product at 60^3 1.95 -> 0.86 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdlib>
+#include <iterator>
 #include <string>
 #include <utility>
 
-#include "fft_device.h"
 #include "krylov.h"
+#include "mix_fft.h"
+#include "v_rows.h"
 
 #include "vie.h"
 #include "vie_internal.h"
@@ -64,27 +81,7 @@ namespace {
 
 using namespace vie;
 
-constexpr int kNT = 256;    // threads of the W kernel
 size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
-constexpr int kNTZ = 512;   // threads of the z kernel
-
-template <typename T>
-__device__ __forceinline__ void sym3(const c2<T> (&N)[6], const c2<T> (&x)[3], c2<T> (&y)[3])
-{
-    y[0] = N[0] * x[0] + N[3] * x[1] + N[4] * x[2];
-    y[1] = N[3] * x[0] + N[1] * x[1] + N[5] * x[2];
-    y[2] = N[4] * x[0] + N[5] * x[1] + N[2] * x[2];
-}
-
-// the antisymmetric 3 x 3 product of K (eq. 5: Kt_pq = eps_psq F_s) from its
-// xy, xz, yz entries
-template <typename T>
-__device__ __forceinline__ void asym3(const c2<T> (&K)[3], const c2<T> (&x)[3], c2<T> (&y)[3])
-{
-    y[0] = K[0] * x[1] + K[1] * x[2];
-    y[1] = K[2] * x[2] - K[0] * x[0];
-    y[2] = (T)-1 * (K[1] * x[0] + K[2] * x[1]);
-}
 
 // components per stored pair and the first slot of the block views: N keeps
 // all six, K the three off-diagonal ones (slots 3..5)
@@ -94,368 +91,483 @@ constexpr int pwl_nc()
     return FAM ? 3 : 6;
 }
 
+// ---------------------------------------------------------------------------
+// V[((k2 10 nc + nc b + c) (n1 + 1) + k1) rs + g] for every stored tensor, zero
+// for g beyond its z rank (rs: the largest one, rounded up to whole batches of
+// sixteen, so that the z pass reads and sums without a branch): one workgroup
+// per (k2, tensor).
+template <typename T, int FAM>
+__global__ void __launch_bounds__(kVNT) k_pwl_v(const PwlBlock<T>* __restrict__ blk, int lanes, int rmax,
+                                                int rs, c2<T>* __restrict__ V)
+{
+    constexpr int NC = pwl_nc<FAM>();
+    const int k2 = blockIdx.x, bc = blockIdx.y;
+    const int b = bc / NC, c = 6 - NC + bc % NC;
+    const OpView& v = blk[b].v;
+    const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
+    v_rows<T>(blk[b].core + v.core_off[c], blk[b].fac + v.fac_off[c][0], blk[b].fac + v.fac_off[c][1] + (long)k2 * r2,
+              v.r[c][0], r2, v.r[c][2], n1p1, lanes, rmax, rs, false, V + ((long)k2 * 10 * NC + bc) * n1p1 * rs);
+}
+
+// ---------------------------------------------------------------------------
+// table tasks (64 k3 of one tensor) a wavefront can hold for a second group
+constexpr int kPwlHold = 8;
+
 struct PwlZArgs {
     int n[3];
-    int L[3];
-    int G;       // pencils per workgroup (mirror group size: 1, 2 or 4)
-    int conj;    // adjoint
-    int rmax;    // largest Tucker rank over the ten blocks
-    int pb;      // pairs whose tables are built and applied together (1..10)
-    // for each mirror-flag combination f = f1 | f2 << 1 | f3 << 2, the tables
-    // that change sign there: bit b * nc + c of neg[f] is set when component c
-    // of pair b is odd along an odd number of the flagged axes
-    unsigned long long neg[8];
+    int nq;      // neighbouring groups (k1, k1 + 1) per workgroup, 1 or 2
+    int L1, L2;
+    int nrhs;    // right-hand sides, walked from blockIdx.y in steps of gridDim.y
+    int rs;      // V stride per tensor
 };
 
-// the sign bit of table t under the flags' mask nm
-__device__ __forceinline__ bool pwl_neg(unsigned long long nm, int t)
+// threads per workgroup at most: one Fourier position each
+template <typename T>
+constexpr int pwl_max_nt()
 {
-    return (nm >> t) & 1ull;
+    return sizeof(T) == 4 ? 1024 : 512;
 }
 
-// the (a, b) and (b, a) blocks of stored pair B on one Fourier position,
-// pair indices known at compile time (no runtime selection of registers).
-// N (FAM 0): K^_ab = sigma T, K^_ba = T (the sum runs over m' - m);
-// K (FAM 1): K^_ab = T, K^_ba = sigma T (the sum runs over m - m'); no adjoint
-template <int B, int FAM, typename T>
-__device__ __forceinline__ void pwl_pair(c2<T> (&acc)[12], const c2<T> (&x)[12], const c2<T>* NTT, int n3p1, int kk,
-                                         unsigned long long nm, bool conj)
+// acc += a b, acc -= a b
+template <bool NEG, typename T>
+__device__ __forceinline__ void cmac(c2<T>& acc, c2<T> a, c2<T> b)
 {
-    constexpr int la = kPwlPairs[B][0], lb = kPwlPairs[B][1];
+    fma_c(acc, NEG ? mk<T>(-a.x, -a.y) : a, b);
+}
+
+// The N^ tables lie in LDS position by position, a row per k3 of the PB pairs'
+// tensors: with compile-time offsets a thread reads its row from one address
+// register.  Rows of an odd number of 16-byte units spread eight consecutive
+// rows over all banks.
+template <typename T, int FAM, int PB>
+constexpr int pwl_row()
+{
+    constexpr int t = PB * pwl_nc<FAM>();
+    constexpr int u = (t + 1) / 2;
+    return sizeof(T) == 4 ? 2 * (u | 1) : (t | 1);
+}
+
+// the (a, b) and (b, a) blocks of stored pair B on one Fourier position.
+// N (FAM 0): K^_ab = sigma T, K^_ba = T (the sum runs over m' - m), the
+// adjoint moves sigma to the (b, a) block; K (FAM 1): K^_ab = T,
+// K^_ba = sigma T (the sum runs over m - m'); no adjoint
+template <int B, int FAM, bool CONJ, typename T>
+__device__ __forceinline__ void pwl_pair(c2<T> (&acc)[12], const c2<T> (&x)[12], const c2<T>* row)
+{
+    constexpr int la = 3 * kPwlPairs[B][0], lb = 3 * kPwlPairs[B][1];
     constexpr bool sig = (la == 0) != (lb == 0);
     constexpr int NC = pwl_nc<FAM>();
+    constexpr bool nab = FAM == 0 && sig && !CONJ, nba = sig && (FAM == 1 || CONJ);
     c2<T> N[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        c2<T> t = NTT[(B * NC + c) * n3p1 + kk];
-        if (pwl_neg(nm, B * NC + c)) t = mk<T>(-t.x, -t.y);
-        N[c] = conj ? vie::conj(t) : t;
-    }
-    T sab, sba;
+    for (int c = 0; c < NC; ++c) N[c] = row[c];
     if constexpr (FAM == 0) {
-        sab = (sig && !conj) ? (T)-1 : (T)1;
-        sba = (sig && conj) ? (T)-1 : (T)1;
-    } else {
-        sab = (T)1;
-        sba = sig ? (T)-1 : (T)1;
-    }
-    c2<T> y[3];
-    const c2<T> xb[3] = {x[3 * lb], x[3 * lb + 1], x[3 * lb + 2]};
-    if constexpr (FAM == 0) sym3(N, xb, y);
-    else asym3(N, xb, y);
+        constexpr int at[3][3] = {{0, 3, 4}, {3, 1, 5}, {4, 5, 2}};
 #pragma unroll
-    for (int q = 0; q < 3; ++q) acc[3 * la + q] = acc[3 * la + q] + sab * y[q];
-    if constexpr (la != lb) {
-        const c2<T> xa[3] = {x[3 * la], x[3 * la + 1], x[3 * la + 2]};
-        if constexpr (FAM == 0) sym3(N, xa, y);
-        else asym3(N, xa, y);
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) acc[3 * lb + q] = acc[3 * lb + q] + sba * y[q];
-    }
-}
-
-template <int FAM, typename T, int... B>
-__device__ __forceinline__ void pwl_all_pairs(c2<T> (&acc)[12], const c2<T> (&x)[12], const c2<T>* NTT, int n3p1,
-                                              int kk, unsigned long long nm, bool conj,
-                                              std::integer_sequence<int, B...>)
-{
-    (pwl_pair<B, FAM, T>(acc, x, NTT, n3p1, kk, nm, conj), ...);
-}
-
-// mixed-radix LDS transform of the 12 P pencils (sequence-major); LC > 0:
-// the length is known at compile time
-template <int DIR, int MAXE, int LC, typename T>
-__device__ __forceinline__ void pwl_fft(c2<T>* X, int nseq, int L3, const FftPlan& pl, const c2<T>* tws, int tid)
-{
-    if constexpr (LC == 252) {   // the head grid's z length (126 voxels)
-        stage_r<7, DIR, false, MAXE>(X, nseq, LC, 1, LC, 1, tws, tid, kNTZ);
-        stage_r<4, DIR, false, MAXE>(X, nseq, LC, 1, LC, 7, tws, tid, kNTZ);
-        stage_r<3, DIR, false, MAXE>(X, nseq, LC, 1, LC, 28, tws, tid, kNTZ);
-        stage_r<3, DIR, false, MAXE>(X, nseq, LC, 1, LC, 84, tws, tid, kNTZ);
+            for (int q = 0; q < 3; ++q) {
+                cmac<nab>(acc[la + p], N[at[p][q]], x[lb + q]);
+                if constexpr (la != lb) cmac<nba>(acc[lb + p], N[at[p][q]], x[la + q]);
+            }
     } else {
-        fft_lds_len<DIR, false, MAXE, LC>(X, nseq, L3, 1, pl, tws, tid, kNTZ);
+        // Kt_qp = -Kt_pq, zero diagonal (eq. 5: Kt_pq = eps_psq F_s)
+        cmac<false>(acc[la], N[0], x[lb + 1]);
+        cmac<false>(acc[la], N[1], x[lb + 2]);
+        cmac<true>(acc[la + 1], N[0], x[lb]);
+        cmac<false>(acc[la + 1], N[2], x[lb + 2]);
+        cmac<true>(acc[la + 2], N[1], x[lb]);
+        cmac<true>(acc[la + 2], N[2], x[lb + 1]);
+        if constexpr (la != lb) {
+            cmac<nba>(acc[lb], N[0], x[la + 1]);
+            cmac<nba>(acc[lb], N[1], x[la + 2]);
+            cmac<!nba>(acc[lb + 1], N[0], x[la]);
+            cmac<nba>(acc[lb + 1], N[2], x[la + 2]);
+            cmac<!nba>(acc[lb + 2], N[1], x[la]);
+            cmac<!nba>(acc[lb + 2], N[2], x[la + 1]);
+        }
     }
 }
 
-// W_c(k2) = G_c x2 U2_c(k2, :) (r1 x r3) for every component of the ten
-// blocks and every canonical k2 in [0, n2], once per matvec:
-// Wg[((k2 * 10 nc) + nc b + c) * rmax^2 + al * r3 + ga] (nc components per
-// block).  The z pass then only contracts the x row and the z factor per
-// pencil group.
-template <typename T, int FAM>
-__global__ void __launch_bounds__(kNT) k_pwl_w(const PwlBlock<T>* __restrict__ blk, int rmax, c2<T>* __restrict__ Wg)
-{
-    constexpr int NC = pwl_nc<FAM>(), C0 = 6 - NC;
-    const int k2 = blockIdx.x, bc = blockIdx.y;
-    const int b = bc / NC, c = C0 + bc - NC * b;
-    const OpView& v = blk[b].v;
-    const int r1 = v.r[c][0], r2 = v.r[c][1], r3 = v.r[c][2];
-    const c2<T>* Gc = blk[b].core + v.core_off[c];
-    const c2<T>* U2 = blk[b].fac + v.fac_off[c][1] + (long)k2 * r2;
-    c2<T>* out = Wg + ((size_t)k2 * 10 * NC + bc) * rmax * rmax;
-    for (int e = threadIdx.x; e < r1 * r3; e += kNT) {
-        const int al = e / r3, ga = e - al * r3;
-        c2<T> s = mk<T>(0, 0);
-        for (int be = 0; be < r2; ++be) fma_c(s, Gc[((long)al * r2 + be) * r3 + ga], U2[be]);
-        out[e] = s;
-    }
-}
+// PB: pairs whose tables are in LDS together
+template <typename T, int G, int FAM, bool CONJ, int PB>
+struct PwlZ {
+    static constexpr int NC = pwl_nc<FAM>(), ROW = pwl_row<T, FAM, PB>();
+    static constexpr int NSEQ = 12 * G, S = NSEQ + 1;
+    const PwlZArgs& a;
+    const MixPlan& p;
+    const PwlBlock<T>* blk;
+    const c2<T>* V;     // this group's row of the first tensor
+    c2<T>* buf;
+    c2<T>* tab;
+    const c2<T>* tws;
+    int tid, nt;
+    int k1, k2;         // canonical
+    int i0, j0;         // first pencil (kx, ky) of the group
+    bool m1, m2;        // whether the group holds the mirror along x, y
 
-template <typename T, int MAXE, int EPT, int LC, int FAM>
-__global__ void __launch_bounds__(kNTZ) k_pwl_z(c2<T>* __restrict__ S2, FftPlan pl, const c2<T>* __restrict__ tw,
-                                               PwlZArgs a, const PwlBlock<T>* __restrict__ blk,
-                                               const c2<T>* __restrict__ Wg)
+    // pencil pe = s1 | s2 << 1 of the group (G = 2: along x only)
+    __device__ __forceinline__ bool exists(int pe) const { return (!(pe & 1) || m1) && (!(pe & 2) || m2); }
+    __device__ __forceinline__ long base(int s, long rhs) const
+    {
+        const int comp = s / G, pe = s % G;
+        const int i = (pe & 1) ? a.L1 - i0 : i0, j = (pe & 2) ? a.L2 - j0 : j0;
+        return (((rhs * 12 + comp) * a.L2 + j) * a.L1 + i) * a.n[2];
+    }
+
+    // inputs of butterfly e of the first stage
+    __device__ __forceinline__ void load(c2<T> (&v)[8], const c2<T>* __restrict__ S2, int e, long rhs) const
+    {
+        const int s = mix_div(e, p.m_s0), j = e - s * p.s0;
+        const bool ex = e < NSEQ * p.s0 && exists(s % G);
+        const c2<T>* src = S2 + (ex ? base(s, rhs) + j : 0);
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = ex && 2 * r < p.r0 ? src[r * p.s0] : mk<T>(0, 0);
+    }
+
+    template <int R>
+    __device__ __forceinline__ void first_fwd(c2<T> (&v)[8], const c2<T>* __restrict__ S2, long rhs) const
+    {
+        const int total = NSEQ * p.s0;
+#pragma unroll 1
+        for (int e = tid; e < total; e += nt) {
+            if (e != tid) load(v, S2, e, rhs);
+            const int s = mix_div(e, p.m_s0), j = e - s * p.s0;
+            c2<T> o[R];
+            dft_half_in<R>(v, o);
+            c2<T>* q = buf + j * S + s;
+            q[0] = o[0];
+#pragma unroll
+            for (int r = 1; r < R; ++r) q[r * p.s0 * S] = mix_tw<-1>(o[r], tws, r * j);
+        }
+    }
+
+    template <int R>
+    __device__ __forceinline__ void last_inv(c2<T>* __restrict__ S2, long rhs) const
+    {
+        constexpr int H = R / 2;
+        const int total = NSEQ * p.s0;
+#pragma unroll 1
+        for (int e = tid; e < total; e += nt) {
+            const int s = mix_div(e, p.m_s0), j = e - s * p.s0;
+            if (!exists(s % G)) continue;
+            c2<T> v[R], o[H];
+            const c2<T>* q = buf + j * S + s;
+            v[0] = q[0];
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[r] = mix_tw<1>(q[r * p.s0 * S], tws, r * j);
+            dft_half_out<R>(v, o);
+            c2<T>* dst = S2 + base(s, rhs) + j;
+#pragma unroll
+            for (int r = 0; r < H; ++r) dst[r * p.s0] = o[r];
+        }
+    }
+
+    // the last forward / first inverse stage in place (no twiddles)
+    template <int R, int DIR>
+    __device__ __forceinline__ void inner() const
+    {
+        const int total = NSEQ * (p.L / R);
+#pragma unroll 1
+        for (int e = tid; e < total; e += nt) {
+            const int s = e % NSEQ, b = e / NSEQ;
+            c2<T>* q = buf + b * R * S + s;
+            c2<T> v[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r] = q[r * S];
+            dft_mix<R, DIR>(v);
+#pragma unroll
+            for (int r = 0; r < R; ++r) q[r * S] = v[r];
+        }
+    }
+    template <int DIR>
+    __device__ __forceinline__ void inner_any() const
+    {
+        switch (p.rl) {
+        case 2: inner<2, DIR>(); break;
+        case 3: inner<3, DIR>(); break;
+        case 4: inner<4, DIR>(); break;
+        case 5: inner<5, DIR>(); break;
+        case 6: inner<6, DIR>(); break;
+        case 7: inner<7, DIR>(); break;
+        case 8: inner<8, DIR>(); break;
+        case 9: inner<9, DIR>(); break;
+        case 10: inner<10, DIR>(); break;
+        case 12: inner<12, DIR>(); break;
+        case 15: inner<15, DIR>(); break;
+        case 16: inner<16, DIR>(); break;
+        default: return;
+        }
+        __syncthreads();
+    }
+
+    // sA, sB = sum over g of V rows (this group's, and with TWO its neighbour's
+    // at k1 + 1) times the z factors of one tensor at k3: sixteen factors in
+    // flight, skipped in fours beyond the rank (within four the V rows are
+    // zero there and the last factor stands in)
+    template <bool TWO>
+    __device__ __forceinline__ void contract(int t, int b0, int k3, c2<T>& sA, c2<T>& sB) const
+    {
+        const int b = b0 + t / NC, c = 6 - NC + t % NC;
+        const int r3 = blk[b].v.r[c][2];
+        const c2<T>* U3 = blk[b].fac + blk[b].v.fac3t_off[c] + min(k3, a.n[2]);
+        const c2<T>* va = V + (long)(NC * b0 + t) * (a.n[0] + 1) * a.rs;
+        c2<T> eA = mk<T>(0, 0), eB = mk<T>(0, 0);   // even g (odd ones in sA, sB): shorter sums round less
+        sA = mk<T>(0, 0);
+        sB = mk<T>(0, 0);
+        constexpr int CH = sizeof(T) == 4 ? 16 : 8;
+        for (int g0 = 0; g0 < r3; g0 += CH) {
+            c2<T> u[CH], wA[CH], wB[CH];
+#pragma unroll
+            for (int h = 0; h < CH; h += 4) {
+                if (g0 + h < r3) {
+#pragma unroll
+                    for (int q = h; q < h + 4; ++q) u[q] = ldg(U3 + (long)min(g0 + q, r3 - 1) * (a.n[2] + 1));
+                }
+            }
+            // the whole V rows at once (scalar loads beside the factors')
+#pragma unroll
+            for (int q = 0; q < CH; ++q) {
+                wA[q] = va[g0 + q];
+                if (TWO) wB[q] = va[a.rs + g0 + q];
+            }
+#pragma unroll
+            for (int h = 0; h < CH; h += 4) {
+                if (g0 + h < r3) {
+#pragma unroll
+                    for (int q = h; q < h + 4; ++q) {
+                        fma_c(q & 1 ? sA : eA, wA[q], u[q]);
+                        if (TWO) fma_c(q & 1 ? sB : eB, wB[q], u[q]);
+                    }
+                }
+            }
+        }
+        sA = sA + eA;
+        sB = sB + eB;
+        if (CONJ) {
+            sA.y = -sA.y;
+            sB.y = -sB.y;
+        }
+    }
+
+    // N^ tables of pairs b0 .. b0 + nb: a wavefront takes 64 k3 of one tensor
+    // at a time (uniform V row, coalesced z factors)
+    __device__ __forceinline__ void tables(int b0, int nb) const
+    {
+        const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6, lane = tid & 63;
+        const int tensors = nb * NC, total = tensors * ((a.n[2] + 64) >> 6);
+        for (int task = wv; task < total; task += nw) {
+            const int t = task % tensors, k3 = (task / tensors) * 64 + lane;
+            c2<T> sA, sB;
+            contract<false>(t, b0, k3, sA, sB);
+            if (k3 <= a.n[2]) tab[k3 * ROW + t] = sA;
+        }
+    }
+
+    // all ten pairs' tables of two neighbouring groups with one pass over the
+    // z factors: the second group's wait in registers (at most kPwlHold tasks
+    // a wavefront) until the first group is done
+    __device__ __forceinline__ void tables_two(c2<T> (&hold)[kPwlHold]) const
+    {
+        const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6, lane = tid & 63;
+        const int total = 10 * NC * ((a.n[2] + 64) >> 6);
+#pragma unroll
+        for (int i = 0; i < kPwlHold; ++i) {
+            const int task = wv + i * nw;
+            if (task < total) {
+                const int t = task % (10 * NC), k3 = (task / (10 * NC)) * 64 + lane;
+                c2<T> sA;
+                contract<true>(t, 0, k3, sA, hold[i]);
+                if (k3 <= a.n[2]) tab[k3 * ROW + t] = sA;
+            }
+        }
+    }
+    __device__ __forceinline__ void tables_held(const c2<T> (&hold)[kPwlHold]) const
+    {
+        const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nt >> 6, lane = tid & 63;
+        const int total = 10 * NC * ((a.n[2] + 64) >> 6);
+#pragma unroll
+        for (int i = 0; i < kPwlHold; ++i) {
+            const int task = wv + i * nw;
+            if (task < total) {
+                const int t = task % (10 * NC), k3 = (task / (10 * NC)) * 64 + lane;
+                if (k3 <= a.n[2]) tab[k3 * ROW + t] = hold[i];
+            }
+        }
+    }
+
+    __device__ __forceinline__ void read(c2<T> (&x)[12], const c2<T>* cell, const T (&d)[12]) const
+    {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) x[c] = d[c] * cell[c * G];
+    }
+
+    template <int B>
+    __device__ __forceinline__ void pair(c2<T> (&acc)[12], c2<T> (&x)[12], const c2<T>* cell, const T (&d)[12],
+                                         const c2<T>* row) const
+    {
+        if constexpr (PB < 10 && B % PB == 0) {   // the next batch of tables
+            if (B > 0) __syncthreads();
+            tables(B, PB < 10 - B ? PB : 10 - B);
+            __syncthreads();
+            read(x, cell, d);
+        }
+        pwl_pair<B, FAM, CONJ>(acc, x, row + NC * (B % PB));
+        // finish this pair before the next one's table reads: otherwise all
+        // sixty entries are read first and spilled
+#pragma unroll
+        for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[c].x), "+v"(acc[c].y));
+    }
+    template <int... B>
+    __device__ __forceinline__ void pairs(c2<T> (&acc)[12], const c2<T>* cell, const T (&d)[12], const c2<T>* row,
+                                          std::integer_sequence<int, B...>) const
+    {
+        c2<T> x[12];
+        if constexpr (PB == 10) read(x, cell, d);
+        (pair<B>(acc, x, cell, d, row), ...);
+    }
+
+    __device__ __forceinline__ void product() const
+    {
+        const int n3 = a.n[2], groups = p.L / p.rl, total = G * p.L;
+        // slot and pencil of this thread: along the groups for an odd last
+        // radix (LDS stride 2 x odd), along the pencils first for an even one
+        const int e = min(tid, total - 1);
+        int pe, b, q;
+        if (p.rl & 1) {
+            q = e / groups;
+            b = e - q * groups;
+            pe = q / p.rl;
+            q -= pe * p.rl;
+        } else {
+            pe = e % G;
+            const int t = e / G;
+            q = t / groups;
+            b = t - q * groups;
+        }
+        const int k = mix_freq(p, b) + q * groups;
+        const bool f3 = k > n3;
+        const int kk = f3 ? p.L - k : k;
+        // signs of the mirrored axes (a group of one or two pencils may lie
+        // beyond the octant as a whole)
+        const T sx = ((pe & 1) != 0) != (i0 != k1) ? (T)-1 : (T)1;
+        const T sy = ((pe & 2) != 0) != (j0 != k2) ? (T)-1 : (T)1;
+        const T sz = f3 ? (T)-1 : (T)1;
+        const T d[12] = {sx, sy, sz, (T)1, sx * sy, sx * sz, sx * sy, (T)1, sy * sz, sx * sz, sy * sz, (T)1};
+        c2<T>* cell = buf + (b * p.rl + q) * S + pe;
+        c2<T> acc[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = mk<T>(0, 0);
+        pairs(acc, cell, d, tab + kk * ROW, std::make_integer_sequence<int, 10>{});
+        const T o = FAM ? sx * sy * sz : (T)1;
+        if (tid < total) {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) cell[c * G] = (FAM ? o * d[c] : d[c]) * acc[c];
+        }
+    }
+};
+
+template <typename T, int G, int FAM, bool CONJ, int PB>
+__global__ void __launch_bounds__(pwl_max_nt<T>())
+    k_pwl_z(c2<T>* __restrict__ S2, const c2<T>* __restrict__ tw, PwlZArgs a, MixPlan p,
+            const PwlBlock<T>* __restrict__ blk, const c2<T>* __restrict__ V)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    using Z = PwlZ<T, G, FAM, CONJ, PB>;
     const int n1 = a.n[0], n2 = a.n[1];
-    const int n3 = LC ? LC / 2 : a.n[2];
-    const int L1 = a.L[0], L2 = a.L[1], L3 = LC ? LC : a.L[2];
-    S2 += (long)blockIdx.y * 12 * L2 * L1 * n3;   // right-hand side
-    const int rmax = a.rmax;
-    const int tid = threadIdx.x;
-    constexpr int NC = pwl_nc<FAM>(), C0 = 6 - NC;
-
-    // ---- the pencils of this workgroup: (k1, k2) and its mirrors
-    int k1, k2, f1base = 0, f2base = 0;
-    int P = 0;
-    int pk1[4], pk2[4], pf1[4], pf2[4];
-    {
-        const int bidx = blockIdx.x;
-        if (a.G == 4) {
-            k1 = bidx % (n1 + 1);
-            k2 = bidx / (n1 + 1);
-        } else if (a.G == 2) {
-            k1 = bidx % (n1 + 1);
-            const int kk2 = bidx / (n1 + 1);
-            k2 = kk2 <= n2 ? kk2 : L2 - kk2;
-            f2base = kk2 > n2;
-        } else {
-            const int kk1 = bidx % L1, kk2 = bidx / L1;
-            k1 = kk1 <= n1 ? kk1 : L1 - kk1;
-            f1base = kk1 > n1;
-            k2 = kk2 <= n2 ? kk2 : L2 - kk2;
-            f2base = kk2 > n2;
-        }
-        const bool m1 = (a.G >= 2) && k1 > 0 && k1 < n1;
-        const bool m2 = (a.G == 4) && k2 > 0 && k2 < n2;
-        for (int s2 = 0; s2 <= (m2 ? 1 : 0); ++s2)
-            for (int s1 = 0; s1 <= (m1 ? 1 : 0); ++s1) {
-                const int f1 = f1base | s1, f2 = f2base | s2;
-                pk1[P] = f1 ? L1 - k1 : k1;
-                pk2[P] = f2 ? L2 - k2 : k2;
-                pf1[P] = f1;
-                pf2[P] = f2;
-                ++P;
-            }
-    }
-
-    // ---- LDS: pencils [12 * G][L3] (sequence (3 l + q) * P + pencil), the
-    // N^ tables and V of a batch of pairs, twiddles
-    c2<T>* X = reinterpret_cast<c2<T>*>(smem_raw);
-    c2<T>* NTT = X + (size_t)12 * a.G * L3;         // [pb][NC][n3 + 1]
-    c2<T>* Vc = NTT + (size_t)a.pb * NC * (n3 + 1); // [pb][NC][rmax]
-    c2<T>* tws = Vc + (size_t)a.pb * NC * rmax;     // [L3]
-    unsigned long long* negs = reinterpret_cast<unsigned long long*>(tws + L3);   // [8]
-    for (int m = tid; m < L3; m += kNTZ) tws[m] = tw[m];
-    if (tid == 0) {
-#pragma unroll
-        for (int f = 0; f < 8; ++f) negs[f] = a.neg[f];
-    }
-
-    for (int e = tid; e < 12 * P * L3; e += kNTZ) {
-        const int s = e / L3, m = e - s * L3;
-        const int comp = s / P, pe = s - comp * P;
-        c2<T> val = mk<T>(0, 0);
-        if (m < n3) val = S2[(((long)comp * L2 + pk2[pe]) * L1 + pk1[pe]) * n3 + m];
-        X[s * L3 + m] = val;
+    // XCD-wise runs of neighbouring groups (workgroups go round robin over
+    // the eight XCDs): their pencils share cache lines
+    const int nk1 = G >= 2 ? n1 + 1 : a.L1, nx = (nk1 + a.nq - 1) / a.nq, ny = G == 4 ? n2 + 1 : a.L2;
+    const int per = (nx * ny + 7) / 8;
+    const int g = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || g >= nx * ny) return;
+    c2<T>* buf = reinterpret_cast<c2<T>*>(smem_raw);                            // [L][12 G + 1]
+    c2<T>* tws = buf + (((size_t)p.L * Z::S + 1) & ~(size_t)1);                  // [L]
+    c2<T>* tab = tws + p.L;                                                     // [n3 + 1][ROW], 16-byte aligned
+    const int i0 = (g % nx) * a.nq, j0 = g / nx;
+    const int nq = min(a.nq, nk1 - i0);
+    const int k1 = i0 <= n1 ? i0 : a.L1 - i0, k2 = j0 <= n2 ? j0 : a.L2 - j0;
+    Z z{a,    p,  blk, V + ((long)k2 * 10 * Z::NC * (n1 + 1) + k1) * a.rs,
+        buf,  tab, tws, (int)threadIdx.x, (int)blockDim.x,
+        k1,   k2, i0,  j0, G >= 2 && k1 > 0 && k1 < n1, G == 4 && k2 > 0 && k2 < n2};
+    c2<T> v[8], hold[kPwlHold];
+    z.load(v, S2, z.tid, blockIdx.y);   // in flight while the tables are built
+    for (int m = z.tid; m < p.L; m += z.nt) tws[m] = tw[m];
+    if constexpr (PB == 10) {
+        if (nq == 2) z.tables_two(hold);
+        else z.tables(0, 10);
     }
     __syncthreads();
-    pwl_fft<-1, MAXE, LC>(X, 12 * P, L3, pl, tws, tid);
-
-    c2<T> acc[12][EPT];
-#pragma unroll
-    for (int c = 0; c < 12; ++c)
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) acc[c][j] = mk<T>(0, 0);
-
-    // ---- the ten pairs in batches of a.pb whose tables fit in LDS together:
-    // per batch V_c = U1_c(k1, :) W_c(k2) of every component, then the
-    // N^_c(k1, k2, k3) tables for k3 in [0, n3], then the (a, b) and (b, a)
-    // blocks of every pair on every owned position
-#pragma unroll 1
-    for (int b0 = 0; b0 < 10; b0 += a.pb) {
-        const int nb = min(a.pb, 10 - b0);
-        for (int e = tid; e < nb * NC * rmax; e += kNTZ) {
-            const int bc = e / rmax, ga = e - bc * rmax;
-            const int b = b0 + bc / NC, c = C0 + bc % NC;
-            const OpView& v = blk[b].v;
-            const int r1 = v.r[c][0], r3 = v.r[c][2];
-            if (ga < r3) {
-                const c2<T>* U1 = blk[b].fac + v.fac_off[c][0] + (long)k1 * r1;
-                const c2<T>* W = Wg + ((size_t)k2 * 10 * NC + NC * b + c - C0) * rmax * rmax + ga;
-                c2<T> s0 = mk<T>(0, 0), s1 = mk<T>(0, 0);
-                int al = 0;
-                for (; al + 4 <= r1; al += 4) {
-                    const c2<T> w0 = W[al * r3], w1 = W[(al + 1) * r3], w2 = W[(al + 2) * r3], w3 = W[(al + 3) * r3];
-                    fma_c(s0, U1[al], w0);
-                    fma_c(s1, U1[al + 1], w1);
-                    fma_c(s0, U1[al + 2], w2);
-                    fma_c(s1, U1[al + 3], w3);
-                }
-                for (; al < r1; ++al) fma_c(s0, U1[al], W[al * r3]);
-                Vc[e] = s0 + s1;
+    for (int i = 0; i < nq; ++i) {
+        if (i > 0) {
+            if constexpr (PB == 10) z.tables_held(hold);   // its first use is barriers away
+        }
+        for (int rhs = blockIdx.y; rhs < a.nrhs; rhs += gridDim.y) {
+            // the stages' addresses are cheap to form again and too many to
+            // keep in registers from one pass of this loop to the next
+            asm volatile("" : "+v"(z.tid));
+            switch (p.r0) {
+            case 2: z.template first_fwd<2>(v, S2, rhs); break;
+            case 4: z.template first_fwd<4>(v, S2, rhs); break;
+            case 6: z.template first_fwd<6>(v, S2, rhs); break;
+            case 8: z.template first_fwd<8>(v, S2, rhs); break;
+            case 10: z.template first_fwd<10>(v, S2, rhs); break;
+            case 12: z.template first_fwd<12>(v, S2, rhs); break;
+            case 14: z.template first_fwd<14>(v, S2, rhs); break;
+            default: z.template first_fwd<16>(v, S2, rhs); break;
             }
-        }
-        __syncthreads();
-        for (int e = tid; e < nb * NC * (n3 + 1); e += kNTZ) {
-            // z factor read column-major ([g][k3]): consecutive threads take
-            // consecutive k3; four rows in flight
-            const int bc = e / (n3 + 1), kk = e - bc * (n3 + 1);
-            const int b = b0 + bc / NC, c = C0 + bc % NC;
-            const OpView& v = blk[b].v;
-            const int r3 = v.r[c][2];
-            const long st = n3 + 1;
-            const c2<T>* U3 = blk[b].fac + v.fac3t_off[c] + kk;
-            const c2<T>* vc = Vc + bc * rmax;
-            c2<T> s0 = mk<T>(0, 0), s1 = mk<T>(0, 0);
-            int ga = 0;
-            for (; ga + 4 <= r3; ga += 4) {
-                const c2<T> u0 = U3[ga * st], u1 = U3[(ga + 1) * st], u2 = U3[(ga + 2) * st], u3 = U3[(ga + 3) * st];
-                fma_c(s0, vc[ga], u0);
-                fma_c(s1, vc[ga + 1], u1);
-                fma_c(s0, vc[ga + 2], u2);
-                fma_c(s1, vc[ga + 3], u3);
+            __syncthreads();
+            if (p.r1 > 1) {
+                mix_middle_any<-1, Z::NSEQ, Z::S>(buf, p, tws, z.tid, z.nt);
+                __syncthreads();
             }
-            for (; ga < r3; ++ga) fma_c(s0, vc[ga], U3[ga * st]);
-            NTT[e] = s0 + s1;
-        }
-        __syncthreads();
-
-#pragma unroll
-        for (int j = 0; j < EPT; ++j) {
-            const int e = tid + j * kNTZ;
-            if (e < P * L3) {
-                const int pe = e / L3, m = e - pe * L3;
-                const int f3 = m > n3;
-                const int kk = f3 ? L3 - m : m;
-                c2<T> x[12];
-#pragma unroll
-                for (int c = 0; c < 12; ++c) x[c] = X[(c * P + pe) * L3 + m];
-                const unsigned fb = (unsigned)pf1[pe] | ((unsigned)pf2[pe] << 1) | ((unsigned)f3 << 2);
-                const unsigned long long nm = negs[fb];
-                if (nb == 10) {
-                    c2<T> ac[12];
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) ac[c] = acc[c][j];
-                    pwl_all_pairs<FAM, T>(ac, x, NTT, n3 + 1, kk, nm, a.conj != 0,
-                                          std::make_integer_sequence<int, 10>{});
-#pragma unroll
-                    for (int c = 0; c < 12; ++c) acc[c][j] = ac[c];
-                    continue;
-                }
-#pragma unroll 1
-                for (int bi = 0; bi < nb; ++bi) {
-                    const int b = b0 + bi;
-                    const int la = kPwlPairs[b][0], lb = kPwlPairs[b][1];
-                    const T sig = ((la == 0) != (lb == 0)) ? (T)-1 : (T)1;
-                    // factors of the (a, b) and (b, a) blocks (as pwl_pair)
-                    const T sab = FAM ? (T)1 : (a.conj ? (T)1 : sig);
-                    const T sba = FAM ? sig : (a.conj ? sig : (T)1);
-                    c2<T> Nc[NC];
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        c2<T> t = NTT[(bi * NC + c) * (n3 + 1) + kk];
-                        if (pwl_neg(nm, b * NC + c)) t = mk<T>(-t.x, -t.y);
-                        Nc[c] = a.conj ? vie::conj(t) : t;
-                    }
-                    // register arrays need compile-time indices: select the rows
-                    c2<T> xa[3], xb[3], y[3];
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) {
-                        xa[q] = mk<T>(0, 0);
-                        xb[q] = mk<T>(0, 0);
-#pragma unroll
-                        for (int l = 0; l < 4; ++l) {
-                            if (l == la) xa[q] = x[3 * l + q];
-                            if (l == lb) xb[q] = x[3 * l + q];
-                        }
-                    }
-                    if constexpr (FAM == 0) sym3(Nc, xb, y);
-                    else asym3(Nc, xb, y);
-#pragma unroll
-                    for (int q = 0; q < 3; ++q)
-#pragma unroll
-                        for (int l = 0; l < 4; ++l)
-                            if (l == la) acc[3 * l + q][j] = acc[3 * l + q][j] + sab * y[q];
-                    if (la != lb) {
-                        if constexpr (FAM == 0) sym3(Nc, xa, y);
-                        else asym3(Nc, xa, y);
-#pragma unroll
-                        for (int q = 0; q < 3; ++q)
-#pragma unroll
-                            for (int l = 0; l < 4; ++l)
-                                if (l == lb) acc[3 * l + q][j] = acc[3 * l + q][j] + sba * y[q];
-                    }
-                }
+            z.template inner_any<-1>();
+            z.product();
+            __syncthreads();
+            z.template inner_any<1>();
+            if (p.r1 > 1) {
+                mix_middle_any<1, Z::NSEQ, Z::S>(buf, p, tws, z.tid, z.nt);
+                __syncthreads();
             }
+            switch (p.r0) {
+            case 2: z.template last_inv<2>(S2, rhs); break;
+            case 4: z.template last_inv<4>(S2, rhs); break;
+            case 6: z.template last_inv<6>(S2, rhs); break;
+            case 8: z.template last_inv<8>(S2, rhs); break;
+            case 10: z.template last_inv<10>(S2, rhs); break;
+            case 12: z.template last_inv<12>(S2, rhs); break;
+            case 14: z.template last_inv<14>(S2, rhs); break;
+            default: z.template last_inv<16>(S2, rhs); break;
+            }
+            // the next right-hand side's, or the next group's first
+            if (rhs + (int)gridDim.y < a.nrhs) z.load(v, S2, z.tid, rhs + gridDim.y);
+            else if (i + 1 < nq) {
+                z.k1 = ++z.i0;
+                z.m1 = G >= 2 && z.k1 > 0 && z.k1 < n1;
+                z.load(v, S2, z.tid, blockIdx.y);
+            }
+            __syncthreads();   // the slots are reused
         }
-        __syncthreads();
-    }
-
-    // ---- outputs back into the pencils, inverse FFT, cropped store
-#pragma unroll
-    for (int j = 0; j < EPT; ++j) {
-        const int e = tid + j * kNTZ;
-        if (e < P * L3) {
-            const int pe = e / L3, m = e - pe * L3;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) X[(c * P + pe) * L3 + m] = acc[c][j];
-        }
-    }
-    __syncthreads();
-    pwl_fft<1, MAXE, LC>(X, 12 * P, L3, pl, tws, tid);
-    for (int e = tid; e < 12 * P * n3; e += kNTZ) {
-        const int s = e / n3, m = e - s * n3;
-        const int comp = s / P, pe = s - comp * P;
-        S2[(((long)comp * L2 + pk2[pe]) * L1 + pk1[pe]) * n3 + m] = X[s * L3 + m];
     }
 }
 
-// Fourier positions per thread of the z kernel in complex64 (G L3 <= EPT 512):
-// 2 lets four mirror pencils share each table at z lengths up to 256
-#ifndef VIE_PWL_EPT32
-#define VIE_PWL_EPT32 2
-#endif
-
+// The shapes of the z pass, best first: the largest mirror group (it shares
+// its tables) whose positions have a thread each, with as many pairs' tables
+// in LDS as fit beside the group's pencils.  The last ones of each type fit
+// every z length up to 512.
+struct PwlShape {
+    int G, PB;
+};
 template <typename T>
-constexpr int pwl_ept()
-{
-    return sizeof(T) == 4 ? VIE_PWL_EPT32 : 1;
-}
+constexpr PwlShape kPwlShapes[] = {{4, 10}, {4, 5}, {2, 10}, {2, 5}, {2, 2}};
+template <>
+constexpr PwlShape kPwlShapes<double>[] = {{4, 10}, {4, 5}, {2, 10}, {2, 5}, {2, 2}, {1, 5}, {1, 2}, {1, 1}};
 
-template <typename T>
-size_t pwl_z_lds(const OpView& v, int rmax, int nc, int G, int pb)
+template <typename T, int FAM, int G, int PB>
+size_t pwl_z_lds(const OpView& v)
 {
-    return sizeof(c2<T>) * ((size_t)12 * G * v.L[2] + (size_t)pb * nc * ((v.n[2] + 1) + rmax) + v.L[2]) +
-           8 * sizeof(unsigned long long);
-}
-
-// pencils per workgroup for the z pass (the largest mirror group whose
-// pencils fit the threads) and the pairs per table batch (as many as the LDS
-// then holds); G = 0: does not fit
-template <typename T>
-void pwl_z_shape(const DeviceOp& op, int rmax, int nc, int& G, int& pb)
-{
-    for (G = 4; G >= 1; G /= 2)
-        if ((size_t)G * op.view.L[2] <= (size_t)pwl_ept<T>() * kNTZ &&
-            pwl_z_lds<T>(op.view, rmax, nc, G, 1) <= op.max_lds)
-            break;
-    if (G < 1) {
-        G = 0;
-        return;
-    }
-    for (pb = 10; pb > 1; --pb)
-        if (pwl_z_lds<T>(op.view, rmax, nc, G, pb) <= op.max_lds) break;
+    const size_t pencils = ((size_t)v.L[2] * (12 * G + 1) + 1) & ~(size_t)1;
+    return sizeof(c2<T>) * (pencils + v.L[2] + (size_t)(v.n[2] + 1) * pwl_row<T, FAM, PB>());
 }
 
 int pwl_op_nc(const vie_pwl_op& P)
@@ -463,66 +575,93 @@ int pwl_op_nc(const vie_pwl_op& P)
     return P.fam ? pwl_nc<1>() : pwl_nc<0>();
 }
 
-// complex elements of the W buffer (every k2 of every block component)
-size_t pwl_w_elems(const vie_pwl_op& P)
+// largest z rank of the stored tensors, in whole batches of sixteen
+int pwl_v_stride(const vie_pwl_op& P)
 {
-    return (size_t)(P.blk[0]->d.view.n[1] + 1) * 10 * pwl_op_nc(P) * P.rmax * P.rmax;
+    int rs = 1;
+    for (int b = 0; b < 10; ++b)
+        for (int c = P.fam ? 3 : 0; c < 6; ++c) rs = std::max(rs, P.blk[b]->d.view.r[c][2]);
+    return (rs + 15) & ~15;
 }
 
-template <typename T, int FAM>
-auto pwl_z_kernel(int L3)
+// complex elements of the V rows
+size_t pwl_v_elems(const vie_pwl_op& P)
 {
-    constexpr int EPT = pwl_ept<T>();
-    constexpr int MAXE = 12 * EPT;
-    return L3 == 512 ? k_pwl_z<T, MAXE, EPT, 512, FAM>
-           : L3 == 256 ? k_pwl_z<T, MAXE, EPT, 256, FAM>
-           : L3 == 128 ? k_pwl_z<T, MAXE, EPT, 128, FAM>
-           : L3 == 64 ? k_pwl_z<T, MAXE, EPT, 64, FAM>
-           : L3 == 300 ? k_pwl_z<T, MAXE, EPT, 300, FAM>
-           : L3 == 252 ? k_pwl_z<T, MAXE, EPT, 252, FAM>
-           : L3 == 240 ? k_pwl_z<T, MAXE, EPT, 240, FAM>
-           : L3 == 180 ? k_pwl_z<T, MAXE, EPT, 180, FAM>
-           : L3 == 120 ? k_pwl_z<T, MAXE, EPT, 120, FAM>
-           : L3 == 60 ? k_pwl_z<T, MAXE, EPT, 60, FAM>
-           : k_pwl_z<T, MAXE, EPT, 0, FAM>;
+    const OpView& v = P.blk[0]->d.view;
+    return (size_t)(v.n[0] + 1) * (v.n[1] + 1) * 10 * pwl_op_nc(P) * pwl_v_stride(P);
+}
+
+// S2, then S1, in whose place the V rows live while S1 is dead (between Y+ and
+// Y-); they exceed it only where the z ranks come near 0.4 n3
+size_t pwl_ws_elems(const vie_pwl_op& P, int nrhs)
+{
+    const OpView& v = P.blk[0]->d.view;
+    const size_t nb = 4 * (size_t)nrhs;
+    const size_t s2 = (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nb, s1 = (size_t)3 * v.n[2] * v.L[0] * v.n[1] * nb;
+    return s2 + std::max(s1, pwl_v_elems(P));
+}
+
+template <typename T, int FAM, bool CONJ, int G, int PB>
+bool try_pwl_z(const DeviceOp& op, int max_pb, PwlZArgs za, const MixPlan& p, c2<T>* S2, const c2<T>* tw,
+               const PwlBlock<T>* blk, const c2<T>* V, hipStream_t s)
+{
+    const OpView& v = op.view;
+    const size_t lds = pwl_z_lds<T, FAM, G, PB>(v);
+    if (PB > max_pb || G * v.L[2] > pwl_max_nt<T>() || lds > op.max_lds) return false;
+    // two neighbouring groups a workgroup halve the z factor reads, which set
+    // the pace of a single one; not where the table tasks exceed what the
+    // wavefronts can hold, or where the grid would drop below two workgroups
+    // per CU
+    const int nk1 = G >= 2 ? v.n[0] + 1 : v.L[0], ny = G == 4 ? v.n[1] + 1 : v.L[1];
+    const int tasks = 10 * pwl_nc<FAM>() * ((v.n[2] + 64) / 64);
+    int waves = (G * v.L[2] + 63) / 64;
+    za.nq = 1;
+    if (G == 4 && PB == 10 && (long)nk1 * ny >= 1024 && tasks <= kPwlHold * (pwl_max_nt<T>() / 64)) {
+        za.nq = 2;
+        waves = std::max(waves, (tasks + kPwlHold - 1) / kPwlHold);
+    }
+    const int nblk = 8 * (((nk1 + za.nq - 1) / za.nq * ny + 7) / 8);
+    // right-hand sides share a workgroup's tables where all ten pairs stay in
+    // LDS and the grid still holds four workgroups per CU
+    int gy = za.nrhs;
+    if (PB == 10)
+        for (gy = 1; gy < za.nrhs && (long)nblk * gy < 1024;) ++gy;
+    auto kern = k_pwl_z<T, G, FAM, CONJ, PB>;
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL(kern, dim3(nblk, gy), dim3(64 * waves), lds, s, S2, tw, za, p, blk, V);
+    return true;
+}
+
+template <typename T, int FAM, bool CONJ, int... I>
+bool try_pwl_shapes(const DeviceOp& op, int max_pb, const PwlZArgs& za, const MixPlan& p, c2<T>* S2,
+                    const c2<T>* tw, const PwlBlock<T>* blk, const c2<T>* V, hipStream_t s,
+                    std::integer_sequence<int, I...>)
+{
+    return (try_pwl_z<T, FAM, CONJ, kPwlShapes<T>[I].G, kPwlShapes<T>[I].PB>(op, max_pb, za, p, S2, tw, blk, V, s) ||
+            ...);
 }
 
 template <typename T>
-hipError_t launch_pwl_z(const vie_pwl_op& P, int conj, c2<T>* S2, c2<T>* Wg, int nrhs, hipStream_t s,
+hipError_t launch_pwl_z(const vie_pwl_op& P, int conj, c2<T>* S2, c2<T>* V, int nrhs, hipStream_t s,
                         std::string& err)
 {
     const DeviceOp& op = P.blk[0]->d;
     const OpView& v = op.view;
-    const int nc = pwl_op_nc(P), c0 = 6 - nc;
-    int G = 0, pb = 1;
-    pwl_z_shape<T>(op, P.rmax, nc, G, pb);
-    // tuning override: at most this many pairs per table batch (same results)
-    if (const char* e = getenv("VIE_PWL_PAIRS_PER_BATCH")) pb = std::max(1, std::min(pb, atoi(e)));
-    if (G == 0) {
-        err = "the piecewise-linear z pass does not fit in LDS (z length or ranks too large)";
+    const int nc = pwl_op_nc(P);
+    int max_pb = 10;
+    // tuning override: at most this many pairs per table batch where a shape has so few
+    if (const char* e = getenv("VIE_PWL_PAIRS_PER_BATCH")) max_pb = std::max(1, std::min(max_pb, atoi(e)));
+    MixPlan p;
+    if (!mix_plan(v.L[2], 16, p)) {
+        err = "the piecewise-linear z pass has no plan for this z length";
         return hipErrorInvalidValue;
     }
     PwlZArgs za;
-    for (int a = 0; a < 3; ++a) {
-        za.n[a] = v.n[a];
-        za.L[a] = v.L[a];
-    }
-    za.G = G;
-    za.conj = conj;
-    za.rmax = P.rmax;
-    za.pb = pb;
-    for (int f = 0; f < 8; ++f) za.neg[f] = 0;
-    for (int b = 0; b < 10; ++b)
-        for (int c = 0; c < nc; ++c) {
-            const int lm = P.blk[b]->d.view.lmask;
-            const int om = view_odd(P.fam, lm, c0 + c, 0) | (view_odd(P.fam, lm, c0 + c, 1) << 1) |
-                           (view_odd(P.fam, lm, c0 + c, 2) << 2);
-            for (int f = 0; f < 8; ++f)
-                if (__builtin_popcount(om & f) & 1) za.neg[f] |= 1ull << (b * nc + c);
-        }
-    const int n1 = v.n[0], n2 = v.n[1];
-    const int nblk = G == 4 ? (n1 + 1) * (n2 + 1) : (G == 2 ? (n1 + 1) * v.L[1] : v.L[0] * v.L[1]);
-    const size_t lds = pwl_z_lds<T>(v, P.rmax, nc, G, pb);
+    for (int a = 0; a < 3; ++a) za.n[a] = v.n[a];
+    za.L1 = v.L[0];
+    za.L2 = v.L[1];
+    za.nrhs = nrhs;
+    za.rs = pwl_v_stride(P);
     const c2<T>* tw;
     const PwlBlock<T>* blk;
     if constexpr (sizeof(T) == 8) {
@@ -532,13 +671,20 @@ hipError_t launch_pwl_z(const vie_pwl_op& P, int conj, c2<T>* S2, c2<T>* Wg, int
         tw = op.tw32[2];
         blk = P.dev32;
     }
-    if (P.fam) hipLaunchKernelGGL((k_pwl_w<T, 1>), dim3(n2 + 1, 10 * nc), dim3(kNT), 0, s, blk, P.rmax, Wg);
-    else hipLaunchKernelGGL((k_pwl_w<T, 0>), dim3(n2 + 1, 10 * nc), dim3(kNT), 0, s, blk, P.rmax, Wg);
-    const int L3 = v.L[2];
-    auto kern = P.fam ? pwl_z_kernel<T, 1>(L3) : pwl_z_kernel<T, 0>(L3);
-    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kern, dim3(nblk, nrhs), dim3(kNTZ), lds, s, S2, op.plan[2], tw, za, blk, (const c2<T>*)Wg);
-    return hipGetLastError();
+    const int lanes = v_rows_lanes<T>(v.n[0] + 1, P.rmax, za.rs);
+    const size_t vlds = v_rows_lds<T>(lanes, P.rmax, za.rs);
+    auto kv = P.fam ? k_pwl_v<T, 1> : k_pwl_v<T, 0>;
+    (void)hipFuncSetAttribute((const void*)kv, hipFuncAttributeMaxDynamicSharedMemorySize, (int)vlds);
+    hipLaunchKernelGGL(kv, dim3(v.n[1] + 1, 10 * nc), dim3(kVNT), vlds, s, blk, lanes, P.rmax, za.rs, V);
+    constexpr auto shapes = std::make_integer_sequence<int, (int)std::size(kPwlShapes<T>)>{};
+    for (int m : {max_pb, 10}) {   // an override that no shape serves is left out
+        const bool ok = P.fam  ? try_pwl_shapes<T, 1, false>(op, m, za, p, S2, tw, blk, V, s, shapes)
+                        : conj ? try_pwl_shapes<T, 0, true>(op, m, za, p, S2, tw, blk, V, s, shapes)
+                               : try_pwl_shapes<T, 0, false>(op, m, za, p, S2, tw, blk, V, s, shapes);
+        if (ok) return hipGetLastError();
+    }
+    err = "the piecewise-linear z pass does not fit in LDS (z length too large)";
+    return hipErrorInvalidValue;
 }
 
 // TV: vector element type, T: compute type (T = float with TV = double: the
@@ -552,12 +698,11 @@ hipError_t pwl_matvec(const vie_pwl_op& P, int mode, const c2<TV>* eps, const c2
     const int nb = 4 * nrhs;   // groups of three components through the pulse passes
     c2<T>* S2 = ws;
     c2<T>* S1 = ws + (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nb;
-    c2<T>* Wg = ws + matvec_ws_elems(op, nb);
     const bool conj = (mode == MODE_AH || mode == MODE_NH);
     // X+ : x -> S1, Y+ : S1 -> S2, Z : S2 in place, Y- : S2 -> S1, X- : S1 -> y
     hipError_t e = run_pass<TV, T>(op, 0, mode, 0, eps, x, nullptr, S1, nb, s, nullptr, err, false, nullptr);
     if (e == hipSuccess) e = run_pass<TV, T>(op, 1, mode, 0, eps, x, S1, S2, nb, s, nullptr, err, false, nullptr);
-    if (e == hipSuccess) e = launch_pwl_z<T>(P, conj ? 1 : 0, S2, Wg, nrhs, s, err);
+    if (e == hipSuccess) e = launch_pwl_z<T>(P, conj ? 1 : 0, S2, S1, nrhs, s, err);
     if (e == hipSuccess) e = run_pass<TV, T>(op, 3, mode, 0, eps, x, S2, S1, nb, s, nullptr, err, false, nullptr);
     if (e == hipSuccess) e = run_pass<TV, T>(op, 4, mode, 0, eps, x, S1, y, nb, s, nullptr, err, false, nullptr);
     return e;
@@ -587,7 +732,7 @@ size_t vie_pwl_workspace_bytes(const vie_pwl_op* op, int dtype, int nrhs)
 {
     if (!op || !op->blk[0] || nrhs < 1) return 0;
     const size_t el = dtype == VIE_C128 ? sizeof(c2<double>) : sizeof(c2<float>);
-    return (matvec_ws_elems(op->blk[0]->d, 4 * nrhs) + pwl_w_elems(*op)) * el;
+    return pwl_ws_elems(*op, nrhs) * el;
 }
 
 vie_status vie_pwl_op_query(const vie_pwl_op* op, int n[3], int ranks[10][6][3])
