@@ -627,7 +627,7 @@ hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<
             err = "dense spectrum not materialised";
             return hipErrorInvalidValue;
         }
-        if (allow_fast && z_pass_fast<T>(op, mode, recon, nrhs, S2, tw[2], core, fac, dense, s))
+        if (allow_fast && zv && z_pass_fast<T>(op, mode, recon, nrhs, S2, zv, tw[2], fac, dense, s))
             return hipGetLastError();
         if (recon == 1) {
             err = "BF16 z pass could not be launched";
@@ -949,7 +949,7 @@ static hipError_t launch_batch_grouped(const std::vector<InstHost>& req, int mod
             XYGroup xg;
             ZGroup zg;
             xg.n = zg.n = 0;
-            int off = 0, rmax = 0;
+            int off = 0, rs = 0;
             const c2<T>* tw = tw_of(*req[i].op, axis);
             for (int j = i; j < count; ++j) {
                 if (done[j] || req[j].op->view.L[axis] != L) continue;
@@ -964,12 +964,13 @@ static hipError_t launch_batch_grouped(const std::vector<InstHost>& req, int mod
                     ZInst& z = zg.e[zg.n++];
                     z = ZInst{};
                     z.S2 = S2;
+                    // S1 is dead between Y+ and Y-: it holds the V rows
+                    z.V = S1;
+                    if (op.nhat_source != 1) launch_zv<T>(op, S1, s);
                     if constexpr (sizeof(T) == 8) {
-                        z.core = op.d64.core;
                         z.fac = op.d64.fac;
                         z.dense = op.dense64;
                     } else {
-                        z.core = op.d32.core;
                         z.fac = op.d32.fac;
                         z.dense = op.dense32;
                     }
@@ -977,11 +978,12 @@ static hipError_t launch_batch_grouped(const std::vector<InstHost>& req, int mod
                     z.za.v = v;
                     z.za.conj = conj;
                     z.za.dense = op.nhat_source == 1;
-                    z.za.chunk = op.zchunk;
-                    z.nbx = (v.n[1] + 1) * ((v.n[0] + 1 + op.zchunk - 1) / op.zchunk);
+                    z.za.rs = zv_stride(v);
+                    z_fast_shape(op, h.nact, sizeof(c2<T>), z.za.chunk, z.nbx, z.gy);
+                    z.nrhs = h.nact;
                     z.off = off;
-                    off += z.nbx * h.nact;
-                    rmax = std::max(rmax, v.rmax);
+                    off += z.nbx * z.gy;
+                    rs = std::max(rs, z.za.rs);
                 } else {
                     const int W = xy_fast_tile<TV, T>(L);
                     XYInst& e = xg.e[xg.n++];
@@ -999,7 +1001,7 @@ static hipError_t launch_batch_grouped(const std::vector<InstHost>& req, int mod
                 }
             }
             if (off == 0) continue;
-            const bool ok = p == 2 ? z_group_fast<T>(L, conj, recon, rmax, req[i].op->max_lds, zg, off, tw, s)
+            const bool ok = p == 2 ? z_group_fast<T>(L, conj, recon, rs, req[i].op->max_lds, zg, off, tw, s)
                                    : xy_group_fast<TV, T>(kind, L, xg, off, tw, s);
             if (!ok) {
                 err = "grouped register-FFT launch not available for this batch";

@@ -10,12 +10,16 @@
 // through per-pencil LDS slices (stride PL = L + L/8 + 1 complex, odd so
 // that both row-wise and pencil-wise walks are free of bank conflicts).
 //
-// Z pass: a block owns one canonical k2 (and its mirror L2 - k2) and a
-// chunk of k1 quads.  W_c(k2) = G_c x2 U2_c(k2, :) is built once per block;
-// per quad V_c = U1_c(k1, :) W_c and N^_c(k1, k2, k3) = sum_g V_c[g]
-// U3_c(k3, g) for k3 in [0, n3] go to LDS, and each thread transforms the
-// three components of its pencil in registers, so the 3 x 3 component
-// product is thread-local.
+// Z pass: the rows V_c(k1, k2, :) = U1_c(k1, :) (G_c x2 U2_c(k2, :)) come from a
+// kernel that runs first (k_zv, matvec_mix.hip).  A block owns one canonical
+// k2 (and its mirror L2 - k2) and a chunk of k1 quads, two at a time: it
+// builds both quads' tables N^_c(k1, k2, k3) = sum_g V_c[g] U3_c(k3, g) for k3 in
+// [0, n3] in LDS, and each thread then transforms the three components of its
+// pencils in registers, so the 3 x 3 component product is thread-local.  A
+// pencil's threads share one wavefront, so between the tables of one pair
+// and the next the wavefronts run free of barriers, through every right-hand
+// side of the block, and both quads' pencils are on their way while the
+// tables are built.
 #include <hip/hip_runtime.h>
 
 #include "reg_fft.h"
@@ -424,21 +428,24 @@ __device__ __forceinline__ int zsign(int c, int f1, int f2, int f3)
 }
 
 // Load the three components of a pencil into the input layout of the
-// forward plan (positions >= n3 are the zero padding).
+// forward plan (positions >= n3 are the zero padding).  S2: the right-hand
+// side's first component (uniform); off: bytes to this lane's first element
+// of the pencil, below 2^31 for every grid up to 256^3 complex128, so that an
+// access needs one address register.
 template <typename T, int L3, int TPP, int R0>
-__device__ __forceinline__ void z_load(c2<T> (&d)[3][8], const c2<T>* __restrict__ S2, long base, long cstride, int t,
+__device__ __forceinline__ void z_load(c2<T> (&d)[3][8], const c2<T>* __restrict__ S2, unsigned off, long cstride,
                                        bool exists)
 {
     constexpr int E = 8;
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int q = 0; q < 3; ++q) {
+        const c2<T>* p = reinterpret_cast<const c2<T>*>(reinterpret_cast<const char*>(S2 + q * cstride) + off);
 #pragma unroll
         for (int u = 0; u < E / R0; ++u)
 #pragma unroll
-            for (int r = 0; r < R0; ++r) {
-                const int pos = t + TPP * u + r * (L3 / R0);
-                d[q][u * R0 + r] = (exists && r < R0 / 2) ? S2[base + q * cstride + pos] : mk<T>(0, 0);
-            }
+            for (int r = 0; r < R0; ++r)
+                d[q][u * R0 + r] = (exists && r < R0 / 2) ? p[TPP * u + r * (L3 / R0)] : mk<T>(0, 0);
+    }
 }
 
 // 3x3 component product in the output layout of the forward plan; FAM 1
@@ -477,15 +484,17 @@ __device__ __forceinline__ void z_product(c2<T> (&d)[3][8], const c2<T>* NTt, in
 }
 
 template <typename T, int L3, int TPP, int RIL>
-__device__ __forceinline__ void z_store(const c2<T> (&d)[3][8], c2<T>* __restrict__ S2, long base, long cstride, int t)
+__device__ __forceinline__ void z_store(const c2<T> (&d)[3][8], c2<T>* __restrict__ S2, unsigned off, long cstride)
 {
     constexpr int E = 8;
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
+    for (int q = 0; q < 3; ++q) {
+        c2<T>* p = reinterpret_cast<c2<T>*>(reinterpret_cast<char*>(S2 + q * cstride) + off);
 #pragma unroll
         for (int u = 0; u < E / RIL; ++u)
 #pragma unroll
-            for (int r = 0; r < RIL / 2; ++r) S2[base + q * cstride + t + TPP * u + r * (L3 / RIL)] = d[q][u * RIL + r];
+            for (int r = 0; r < RIL / 2; ++r) p[TPP * u + r * (L3 / RIL)] = d[q][u * RIL + r];
+    }
 }
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -501,17 +510,16 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // 32-wide step, and receives output rows 4 (l / 16) .. +3 of column l mod 16.
 template <int L3>
 __device__ __forceinline__ void z_tables_mfma(const OpView& v, const unsigned short* __restrict__ f3m,
-                                              const c2<float>* Vc, c2<float>* tabA, c2<float>* tabB, int tid,
-                                              int nt)
+                                              const c2<float>* Vc, int rs, c2<float>* tabA, c2<float>* tabB,
+                                              int tid, int nt)
 {
     constexpr int N3 = L3 / 2;
     constexpr int NTILE = (N3 + 1 + 15) / 16;
-    const int rmax = v.rmax;
     const int lane = tid & 63, wv = tid >> 6, nwv = nt >> 6;
     const int col = lane & 15, grp = lane >> 4;
     float* fa = reinterpret_cast<float*>(tabA);
     float* fb = reinterpret_cast<float*>(tabB);
-    const c2<float>* vq = Vc + ((col >> 1) & 1) * 6 * rmax;
+    const c2<float>* vq = Vc + ((col >> 1) & 1) * 6 * rs;
 #pragma unroll 1
     for (int c = 0; c < 6; ++c) {
         const int r3 = v.r[c][2], rh = v.rh[c];
@@ -524,7 +532,7 @@ __device__ __forceinline__ void z_tables_mfma(const OpView& v, const unsigned sh
                 const bool hi = k >= rh;
                 const int g = hi ? k - rh : k;
                 const bool ok = (col < 4) & (k < 2 * rh) & (g < r3);
-                const c2<float> w = vq[c * rmax + (ok ? g : 0)];
+                const c2<float> w = vq[c * rs + (ok ? g : 0)];
                 const float re = hi ? -w.y : w.x, im = hi ? w.x : w.y;
                 bop[st][e] = (__bf16)(ok ? ((col & 1) ? im : re) : 0.f);
             }
@@ -568,10 +576,10 @@ typedef __attribute__((ext_vector_type(4))) float f32x4m;
 // even / odd g) keep consecutive MFMAs independent.
 template <int L3>
 __device__ __forceinline__ void z_tables_mfma32(const OpView& v, const c2<float>* __restrict__ fac,
-                                                const c2<float>* Vc, c2<float>* tabA, c2<float>* tabB, int tid)
+                                                const c2<float>* Vc, int rs, c2<float>* tabA, c2<float>* tabB,
+                                                int tid)
 {
     constexpr int N3 = L3 / 2;
-    const int rmax = v.rmax;
     const int lane = tid & 63, wv = tid >> 6;
     const int k3 = 64 * wv + lane;
     const int qrow = lane & 3;
@@ -580,7 +588,7 @@ __device__ __forceinline__ void z_tables_mfma32(const OpView& v, const c2<float>
     for (int c = 0; c < 6; ++c) {
         const int r3 = v.r[c][2];
         const c2<float>* U3 = fac + v.fac3t_off[c] + k3;
-        const c2<float>* vq = Vc + qd * 6 * rmax + c * rmax;
+        const c2<float>* vq = Vc + (qd * 6 + c) * rs;
         f32x4m acc[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         for (int g0 = 0; g0 < r3; g0 += 8) {
             // eight z-factor rows in flight, then their 16 products
@@ -609,48 +617,80 @@ __device__ __forceinline__ void z_tables_mfma32(const OpView& v, const c2<float>
         const int c = tid >> 1, q = tid & 1;
         const int r3 = v.r[c][2];
         const c2<float>* U3 = fac + v.fac3t_off[c] + N3;
-        const c2<float>* vq = Vc + q * 6 * rmax + c * rmax;
+        const c2<float>* vq = Vc + (q * 6 + c) * rs;
         c2<float> acc = mk<float>(0, 0);
         for (int g = 0; g < r3; ++g) fma_c(acc, vq[g], U3[(long)g * (N3 + 1)]);
         (q ? tabB : tabA)[c * (N3 + 1) + N3] = acc;
     }
 }
 
-// REC: 0 = N^ tables in T on the vector ALUs, 1 = BF16 z factors on MFMA
+// One quad's pencils through forward FFTs, product and inverse FFTs.
+template <typename T, int L3, bool CONJ, int FAM>
+__device__ __forceinline__ void z_forward(c2<T> (&d)[3][8], c2<T>* slice, int t, const c2<T>* tws)
+{
+    constexpr int TPP = L3 / 8;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) RegPlan<L3>::template fwd<T, TPP, 1, -1>(d[q], slice, 0, t, tws);
+}
+template <typename T, int L3>
+__device__ __forceinline__ void z_inverse(c2<T> (&d)[3][8], c2<T>* slice, int t, const c2<T>* tws)
+{
+    constexpr int TPP = L3 / 8;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) RegPlan<L3>::template inv<T, TPP, 1, 1>(d[q], slice, 0, t, tws);
+}
+
+// Quad A's table takes the place of the FFT slices where the pencils and two
+// tables would leave one workgroup per CU (complex128 at 512): then the
+// forward FFTs end before the tables and a workgroup takes one right-hand side.
+template <typename T, int L3>
+constexpr bool z_shared_table()
+{
+    return sizeof(T) == 8 && L3 == 512;
+}
+
+// REC: 0 = N^ tables in T (complex64: on MFMA), 1 = BF16 z factors on MFMA
 // (T = float), 2 = a K operator (antisymmetric product, K parities; tables
 // on the vector ALUs).
 // One workgroup of the z pass: bx = canonical k2 + (n2 + 1) * chunk index,
-// b = compact right-hand side.
+// right-hand sides b, b + bstep, .. below nrhs.
 template <typename T, int L3, bool CONJ, int REC>
 __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __restrict__ tw, const ZFastArgs& a,
-                                       const c2<T>* __restrict__ core, const c2<T>* __restrict__ fac,
+                                       const c2<T>* __restrict__ V, const c2<T>* __restrict__ fac,
                                        const c2<T>* __restrict__ dense, const unsigned short* __restrict__ f3m,
-                                       int bx, int b)
+                                       int bx, int b, int bstep, int nrhs)
 {
     constexpr int TPP = L3 / 8;
     constexpr int NT = 4 * TPP;
     constexpr int P = PL<L3>::value;
     constexpr int N3 = L3 / 2;
     constexpr int NTS = 6 * (N3 + 1);                            // N^ table entries per quad
+    constexpr int FAM = REC == 2 ? 1 : 0;
+    constexpr int NC = FAM ? 3 : 6;
+    constexpr bool SHARED = z_shared_table<T, L3>();
     using Plan = RegPlan<L3>;
     const OpView& v = a.v;
     const int n1 = v.n[0], n2 = v.n[1];
     const int L1 = v.L[0], L2 = v.L[1];
-    const int rmax = v.rmax;
+    const int rs = a.rs;
     const int tid = threadIdx.x;
-    const int pe = tid / TPP, t = tid % TPP;
+    const int pe = tid / TPP;
+    int t = tid % TPP;
     const int s1 = pe & 1, s2 = pe >> 1;
+    // The steps' LDS and twiddle addresses are cheap to form from t; kept from
+    // one step to the next (as the compiler would) they do not fit the
+    // registers beside the pencils.
+    auto renew = [&]() { asm volatile("" : "+v"(t)); };
 
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    // X: per-pencil FFT transpose slices [4][P]; after the forward FFT of the
-    // first quad of a pair the same region holds its N^ table, the second
-    // quad's table has a region of its own
+    // X: per-pencil FFT transpose slices [4][P]; NTA, NTB: the pair's tables
+    // [6][N3 + 1]; Vc: the pair's V rows [2][6][rs]
     c2<T>* X = reinterpret_cast<c2<T>*>(smem_raw);
-    c2<T>* NTB = X + 4 * P;                                     // [6][N3+1]
-    c2<T>* Wc = NTB + NTS;                                      // [6][wst]
-    const int wst = v.cp ? rmax : rmax * rmax;                  // W_c stride per component
-    c2<T>* Vc = Wc + 6 * wst;                                   // [2][6][rmax]
-    c2<T>* tws = Vc + 12 * rmax;                                // [Plan::TW]
+    c2<T>* NTB = X + 4 * P;
+    c2<T>* NTA = SHARED ? X : NTB + NTS;
+    c2<T>* Vc = NTB + (SHARED ? 1 : 2) * NTS;
+    c2<T>* tws = Vc + 12 * rs;                                  // [Plan::TW]
+    c2<T>* slice = X + pe * P;
     Plan::fill_tw(tws, tw, tid, NT);
 
     const int k2 = bx % (n2 + 1);
@@ -659,163 +699,138 @@ __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __re
     const bool m2 = k2 > 0 && k2 < n2;
     const int pk2 = s2 ? L2 - k2 : k2;
     const long cstride = (long)L2 * L1 * N3;
-
-    // ---- W_c(k2) = G_c x2 U2_c(k2, :) for the six components; for a
-    //      superdiagonal core (Tucker+CP, eq. 17) only its diagonal
-    //      W_c[l] = G_c[l,l,l] U2_c(k2, l) is nonzero and is all that is kept
-    if (!a.dense && v.cp) {
-        for (int e = tid; e < 6 * rmax; e += NT) {
-            const int c = e / rmax, l = e - c * rmax;
-            const int R = v.r[c][0];
-            if (l < R)
-                Wc[c * wst + l] = core[v.core_off[c] + (long)l * (R * R + R + 1)] *
-                                               fac[v.fac_off[c][1] + (long)k2 * R + l];
-        }
-    } else if (!a.dense) {
-        for (int c = 0; c < 6; ++c) {
-            const int r1 = v.r[c][0], r2 = v.r[c][1], r3 = v.r[c][2];
-            const c2<T>* G = core + v.core_off[c];
-            const c2<T>* U2 = fac + v.fac_off[c][1] + (long)k2 * r2;
-            for (int e = tid; e < r1 * r3; e += NT) {
-                const int al = e / r3, ga = e - al * r3;
-                const c2<T>* g = G + (long)al * r2 * r3 + ga;
-                c2<T> acc = mk<T>(0, 0);
-                for (int b0 = 0; b0 < r2; b0 += 8) {
-                    c2<T> gv[8], uv[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        const bool ok = b0 + q < r2;
-                        gv[q] = ok ? g[(long)(b0 + q) * r3] : mk<T>(0, 0);
-                        uv[q] = ok ? U2[b0 + q] : mk<T>(0, 0);
-                    }
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) fma_c(acc, gv[q], uv[q]);
-                }
-                Wc[c * wst + e] = acc;
-            }
-        }
-    }
-    __syncthreads();
+    auto exists = [&](int k1) { return (s1 == 0 || (k1 > 0 && k1 < n1)) && (s2 == 0 || m2); };
+    auto off = [&](int k1) {
+        return (unsigned)sizeof(c2<T>) * (((unsigned)pk2 * L1 + (s1 ? L1 - k1 : k1)) * N3 + t);
+    };
+    auto of_rhs = [&](int rhs) { return S2 + (long)rhs * 3 * cstride; };
 
     for (int kA = k1b; kA < k1e; kA += 2) {
         const int kB = kA + 1;
         const bool hasB = kB < k1e;
-        // ---- quad A's pencils: loads issued first, in flight during the V phase
-        const bool m1A = kA > 0 && kA < n1;
-        const bool exA = (s1 == 0 || m1A) && (s2 == 0 || m2);
-        const long baseA = (((long)b * 3 * L2 + pk2) * L1 + (s1 ? L1 - kA : kA)) * N3;
-        c2<T> d[3][8];
-        z_load<T, L3, TPP, Plan::RF0>(d, S2, baseA, cstride, t, exA);
-        // ---- V_c = U1_c(k1, :) W_c for both quads of the pair (for a
-        //      superdiagonal core the element-wise product with its diagonal)
-        if (!a.dense && v.cp) {
-            for (int e = tid; e < 12 * rmax; e += NT) {
-                const int qd = e / (6 * rmax), rem = e - qd * 6 * rmax;
-                const int c = rem / rmax, l = rem - c * rmax;
-                const int R = v.r[c][0];
-                if (l < R && (qd == 0 || hasB))
-                    Vc[e] = fac[v.fac_off[c][0] + (long)(qd ? kB : kA) * R + l] * Wc[c * wst + l];
-            }
-        } else if (!a.dense) {
-            for (int e = tid; e < 12 * rmax; e += NT) {
-                const int qd = e / (6 * rmax), rem = e - qd * 6 * rmax;
-                const int c = rem / rmax, ga = rem - c * rmax;
-                const int r1 = v.r[c][0], r3 = v.r[c][2];
-                const int k1 = qd ? kB : kA;
-                if (ga < r3 && (qd == 0 || hasB)) {
-                    const c2<T>* U1 = fac + v.fac_off[c][0] + (long)k1 * r1;
-                    const c2<T>* w = Wc + c * wst + ga;
-                    c2<T> acc = mk<T>(0, 0);
-                    for (int a0 = 0; a0 < r1; a0 += 8) {
-                        c2<T> uv[8];
-#pragma unroll
-                        for (int q = 0; q < 8; ++q) uv[q] = a0 + q < r1 ? U1[a0 + q] : mk<T>(0, 0);
-#pragma unroll
-                        for (int q = 0; q < 8; ++q)
-                            if (a0 + q < r1) fma_c(acc, uv[q], w[(a0 + q) * r3]);
-                    }
-                    Vc[e] = acc;
-                }
+        const bool exA = exists(kA), exB = hasB && exists(kB);
+        // ---- the pencils' loads go out first
+        c2<T> dA[3][8], dB[3][8];
+        if (sizeof(T) == 4 || SHARED) z_load<T, L3, TPP, Plan::RF0>(dA, of_rhs(b), off(kA), cstride, exA);
+        if (sizeof(T) == 4) z_load<T, L3, TPP, Plan::RF0>(dB, of_rhs(b), off(kB), cstride, exB);
+        if (!a.dense) {
+            for (int e = tid; e < 2 * NC * rs; e += NT) {
+                const int qd = e / (NC * rs), rem = e - qd * NC * rs;
+                const int c = rem / rs, g = rem - c * rs;
+                Vc[(qd * 6 + 6 - NC + c) * rs + g] =
+                    (qd == 0 || hasB) ? V[(((long)k2 * NC + c) * (n1 + 1) + kA + qd) * rs + g] : mk<T>(0, 0);
             }
         }
-        // ---- quad A: forward FFT
-#pragma unroll
-        for (int q = 0; q < 3; ++q) Plan::template fwd<T, TPP, 1, -1>(d[q], X + pe * P, 0, t, tws);
-        __syncthreads();   // slices free, Vc complete
+        __syncthreads();   // V rows, twiddles; the tables' previous readers are done
+        if constexpr (SHARED) {
+            z_forward<T, L3, CONJ, FAM>(dA, slice, t, tws);
+            __syncthreads();   // slices free
+        }
 
         // ---- N^ tables of both quads: each z-factor element is loaded once
         //      and used for the two quads
         if (!a.dense && REC == 1) {
-            if constexpr (REC == 1) z_tables_mfma<L3>(v, f3m, Vc, X, NTB, tid, NT);
-#ifndef VIE_Z_TABLES_VALU
-        } else if (!a.dense && sizeof(T) == 4) {
-            if constexpr (sizeof(T) == 4) z_tables_mfma32<L3>(v, fac, Vc, X, NTB, tid);
-#endif
+            if constexpr (REC == 1) z_tables_mfma<L3>(v, f3m, Vc, rs, NTA, NTB, tid, NT);
+        } else if (!a.dense && sizeof(T) == 4 && REC == 0) {
+            if constexpr (sizeof(T) == 4) z_tables_mfma32<L3>(v, fac, Vc, rs, NTA, NTB, tid);
         } else if (!a.dense) {
-            for (int e = tid; e < NTS; e += NT) {
-                const int c = e / (N3 + 1), kk = e - c * (N3 + 1);
+            for (int e = tid; e < NC * (N3 + 1); e += NT) {
+                const int c = 6 - NC + e / (N3 + 1), kk = e % (N3 + 1);
                 const int r3 = v.r[c][2];
                 const c2<T>* U3 = fac + v.fac3t_off[c] + kk;
-                const c2<T>* va = Vc + c * rmax;
-                const c2<T>* vb = Vc + 6 * rmax + c * rmax;
+                const c2<T>* va = Vc + c * rs;
+                const c2<T>* vb = Vc + (6 + c) * rs;
                 c2<T> accA = mk<T>(0, 0), accB = mk<T>(0, 0);
                 for (int g0 = 0; g0 < r3; g0 += 8) {
                     c2<T> uv[8];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        uv[q] = g0 + q < r3 ? U3[(long)(g0 + q) * (N3 + 1)] : mk<T>(0, 0);
+                    for (int q = 0; q < 8; ++q) uv[q] = U3[(long)min(g0 + q, r3 - 1) * (N3 + 1)];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        if (g0 + q < r3) {
-                            fma_c(accA, va[g0 + q], uv[q]);
-                            fma_c(accB, vb[g0 + q], uv[q]);
-                        }
+                    for (int q = 0; q < 8; ++q) {   // (V rows are zero beyond r3)
+                        fma_c(accA, va[g0 + q], uv[q]);
+                        fma_c(accB, vb[g0 + q], uv[q]);
                     }
                 }
-                X[e] = accA;
-                NTB[e] = accB;
+                NTA[c * (N3 + 1) + kk] = accA;
+                NTB[c * (N3 + 1) + kk] = accB;
             }
         } else {
             const long per = (long)(n1 + 1) * (n2 + 1) * (N3 + 1);
             for (int e = tid; e < NTS; e += NT) {
                 const int c = e / (N3 + 1), kk = e - c * (N3 + 1);
                 const c2<T>* src = dense + c * per + (long)k2 * (n1 + 1) * (N3 + 1) + kk;
-                X[e] = src[(long)kA * (N3 + 1)];
+                NTA[e] = src[(long)kA * (N3 + 1)];
                 if (hasB) NTB[e] = src[(long)kB * (N3 + 1)];
             }
         }
         __syncthreads();   // tables complete
-        z_product<T, L3, TPP, Plan::RFL, CONJ, REC == 2 ? 1 : 0>(d, X, t, s1, s2);
-        __syncthreads();   // table A consumed: the slices are reused by the inverse FFT
-#pragma unroll
-        for (int q = 0; q < 3; ++q) Plan::template inv<T, TPP, 1, 1>(d[q], X + pe * P, 0, t, tws);
-        if (exA) z_store<T, L3, TPP, Plan::RIL>(d, S2, baseA, cstride, t);
 
-        // ---- quad B
-        if (hasB) {
-            const bool m1B = kB > 0 && kB < n1;
-            const bool exB = (s1 == 0 || m1B) && (s2 == 0 || m2);
-            const long baseB = (((long)b * 3 * L2 + pk2) * L1 + (s1 ? L1 - kB : kB)) * N3;
-            // each wavefront now only touches its own pencil slice until the end of the pair
-            z_load<T, L3, TPP, Plan::RF0>(d, S2, baseB, cstride, t, exB);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) Plan::template fwd<T, TPP, 1, -1>(d[q], X + pe * P, 0, t, tws);
-            z_product<T, L3, TPP, Plan::RFL, CONJ, REC == 2 ? 1 : 0>(d, NTB, t, s1, s2);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) Plan::template inv<T, TPP, 1, 1>(d[q], X + pe * P, 0, t, tws);
-            if (exB) z_store<T, L3, TPP, Plan::RIL>(d, S2, baseB, cstride, t);
+        if constexpr (SHARED) {
+            renew();
+            z_product<T, L3, TPP, Plan::RFL, CONJ, FAM>(dA, NTA, t, s1, s2);
+            __syncthreads();   // table A consumed: the slices are reused by the inverse FFT
+            renew();
+            z_inverse<T, L3>(dA, slice, t, tws);
+            if (exA) z_store<T, L3, TPP, Plan::RIL>(dA, of_rhs(b), off(kA), cstride);
+            if (hasB) {
+                z_load<T, L3, TPP, Plan::RF0>(dB, of_rhs(b), off(kB), cstride, exB);
+                renew();
+                z_forward<T, L3, CONJ, FAM>(dB, slice, t, tws);
+                renew();
+                z_product<T, L3, TPP, Plan::RFL, CONJ, FAM>(dB, NTB, t, s1, s2);
+                renew();
+                z_inverse<T, L3>(dB, slice, t, tws);
+                if (exB) z_store<T, L3, TPP, Plan::RIL>(dB, of_rhs(b), off(kB), cstride);
+            }
+        } else if constexpr (sizeof(T) == 8) {
+            // one set of pencils at a time (the registers hold no second one)
+            for (int rhs = b; rhs < nrhs; rhs += bstep)
+#pragma unroll 1
+                for (int i = 0; i < (hasB ? 2 : 1); ++i) {
+                    renew();
+                    const bool ex = i ? exB : exA;
+                    z_load<T, L3, TPP, Plan::RF0>(dA, of_rhs(rhs), off(kA + i), cstride, ex);
+                    z_forward<T, L3, CONJ, FAM>(dA, slice, t, tws);
+                    renew();
+                    z_product<T, L3, TPP, Plan::RFL, CONJ, FAM>(dA, i ? NTB : NTA, t, s1, s2);
+                    renew();
+                    z_inverse<T, L3>(dA, slice, t, tws);
+                    if (ex) z_store<T, L3, TPP, Plan::RIL>(dA, of_rhs(rhs), off(kA + i), cstride);
+                }
+        } else {
+            for (int rhs = b; rhs < nrhs; rhs += bstep) {
+                const bool more = rhs + bstep < nrhs;
+                renew();
+                z_forward<T, L3, CONJ, FAM>(dA, slice, t, tws);
+                renew();
+                z_product<T, L3, TPP, Plan::RFL, CONJ, FAM>(dA, NTA, t, s1, s2);
+                renew();
+                z_inverse<T, L3>(dA, slice, t, tws);
+                if (exA) z_store<T, L3, TPP, Plan::RIL>(dA, of_rhs(rhs), off(kA), cstride);
+                if (more) z_load<T, L3, TPP, Plan::RF0>(dA, of_rhs(rhs + bstep), off(kA), cstride, exA);
+                if (hasB) {
+                    renew();
+                    z_forward<T, L3, CONJ, FAM>(dB, slice, t, tws);
+                    renew();
+                    z_product<T, L3, TPP, Plan::RFL, CONJ, FAM>(dB, NTB, t, s1, s2);
+                    renew();
+                    z_inverse<T, L3>(dB, slice, t, tws);
+                    if (exB) z_store<T, L3, TPP, Plan::RIL>(dB, of_rhs(rhs), off(kB), cstride);
+                    if (more) z_load<T, L3, TPP, Plan::RF0>(dB, of_rhs(rhs + bstep), off(kB), cstride, exB);
+                }
+            }
         }
-        __syncthreads();   // Vc, NTB and the slices are reused by the next pair
+        if (SHARED) __syncthreads();   // the slices and table B are reused by the next pair
     }
 }
 
 template <typename T, int L3, bool CONJ, int REC>
 __global__ void __launch_bounds__(4 * (L3 / 8), sizeof(T) == 4 ? 3 : 2)
-    k_z_fast(c2<T>* __restrict__ S2, const c2<T>* __restrict__ tw, ZFastArgs a, const c2<T>* __restrict__ core,
-             const c2<T>* __restrict__ fac, const c2<T>* __restrict__ dense,
-             const unsigned short* __restrict__ f3m)
+    k_z_fast(c2<T>* __restrict__ S2, const c2<T>* __restrict__ tw, ZFastArgs a, const c2<T>* __restrict__ V,
+             const c2<T>* __restrict__ fac, const c2<T>* __restrict__ dense, const unsigned short* __restrict__ f3m,
+             int nrhs)
 {
-    z_body<T, L3, CONJ, REC>(S2, tw, a, core, fac, dense, f3m, blockIdx.x, blockIdx.y);
+    z_body<T, L3, CONJ, REC>(S2, tw, a, V, fac, dense, f3m, blockIdx.x, blockIdx.y, gridDim.y, nrhs);
 }
 
 // Grouped launch over instances with the same z length (offsets ascending).
@@ -827,8 +842,8 @@ __global__ void __launch_bounds__(4 * (L3 / 8), sizeof(T) == 4 ? 3 : 2)
     while (i + 1 < g.n && (int)blockIdx.x >= g.e[i + 1].off) ++i;
     const ZInst& in = g.e[i];
     const int local = blockIdx.x - in.off;
-    z_body<T, L3, CONJ, REC>((c2<T>*)in.S2, tw, in.za, (const c2<T>*)in.core, (const c2<T>*)in.fac,
-                             (const c2<T>*)in.dense, in.f3m, local % in.nbx, local / in.nbx);
+    z_body<T, L3, CONJ, REC>((c2<T>*)in.S2, tw, in.za, (const c2<T>*)in.V, (const c2<T>*)in.fac,
+                             (const c2<T>*)in.dense, in.f3m, local % in.nbx, local / in.nbx, in.gy, in.nrhs);
 }
 
 // ---------------------------------------------------------------------------
@@ -897,28 +912,42 @@ static bool dispatch_xy(int L, const void* in, void* out, const c2<TV>* x, const
 }
 
 template <typename T, int L3>
-static size_t zfast_lds(const OpView& v)
+static size_t zfast_lds(int rs)
 {
     static_assert(6 * (L3 / 2 + 1) <= 4 * PL<L3>::value, "N^ table must fit in the FFT slices");
-    // W_c holds r1 x r3 per component, or the R diagonal weights of a
-    // superdiagonal (Tucker+CP) core
-    const size_t wst = v.cp ? (size_t)v.rmax : (size_t)v.rmax * v.rmax;
-    return sizeof(c2<T>) * ((size_t)4 * PL<L3>::value + 6 * (L3 / 2 + 1) + 6 * wst + 12 * v.rmax +
-                            RegPlan<L3>::TW);
+    return sizeof(c2<T>) * ((size_t)4 * PL<L3>::value + (z_shared_table<T, L3>() ? 1 : 2) * 6 * (L3 / 2 + 1) +
+                            12 * rs + RegPlan<L3>::TW);
+}
+
+void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int& chunk, int& nbx, int& gy)
+{
+    const OpView& v = op.view;
+    const int n1p1 = v.n[0] + 1, n2p1 = v.n[1] + 1;
+    // a chunk only saves twiddle fills: halve it until the grid holds sixteen
+    // workgroups per CU (the autotuned length is the limit)
+    chunk = op.zchunk;
+    while (chunk > 2 && (long)n2p1 * ((n1p1 + chunk - 1) / chunk) < 4096) chunk /= 2;
+    nbx = n2p1 * ((n1p1 + chunk - 1) / chunk);
+    // right-hand sides share a workgroup's tables as far as the grid holds
+    // eight workgroups per CU
+    gy = 1;
+    if (elem_bytes == 16 && v.L[2] == 512) gy = nrhs;   // z_shared_table
+    while (gy < nrhs && (long)nbx * gy < 2048) ++gy;
 }
 
 template <typename T, int L3>
 static hipError_t launch_z(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, const c2<T>* tw,
-                           const c2<T>* core, const c2<T>* fac, const c2<T>* dense, hipStream_t s)
+                           const c2<T>* V, const c2<T>* fac, const c2<T>* dense, hipStream_t s)
 {
     const OpView& v = op.view;
     ZFastArgs za;
     za.v = v;
     za.conj = (mode == MODE_AH || mode == MODE_NH);
     za.dense = op.nhat_source == 1;
-    za.chunk = op.zchunk;
-    int nchunk = (v.n[0] + 1 + za.chunk - 1) / za.chunk;
-    size_t lds = zfast_lds<T, L3>(v);
+    za.rs = zv_stride(v);
+    int nbx, gy;
+    z_fast_shape(op, nrhs, sizeof(c2<T>), za.chunk, nbx, gy);
+    size_t lds = zfast_lds<T, L3>(za.rs);
     if (lds > op.max_lds) return hipErrorInvalidValue;
     auto kern = za.conj ? k_z_fast<T, L3, true, 0> : k_z_fast<T, L3, false, 0>;
     if constexpr (sizeof(T) == 4) {
@@ -926,8 +955,8 @@ static hipError_t launch_z(const DeviceOp& op, int mode, int recon, int nrhs, c2
     }
     if (v.fam == 1) kern = k_z_fast<T, L3, false, 2>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kern, dim3((v.n[1] + 1) * nchunk, nrhs), dim3(4 * (L3 / 8)), lds, s, S2, tw, za, core, fac,
-                       dense, (const unsigned short*)op.b16.fac3m);
+    hipLaunchKernelGGL(kern, dim3(nbx, gy), dim3(4 * (L3 / 8)), lds, s, S2, tw, za, V, fac, dense,
+                       (const unsigned short*)op.b16.fac3m, nrhs);
     return hipGetLastError();
 }
 
@@ -991,24 +1020,31 @@ bool bf16_recon_available(const DeviceOp& op)
 }
 
 template <typename T>
-bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, const c2<T>* tw, const c2<T>* core,
+bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, c2<T>* V, const c2<T>* tw,
                  const c2<T>* fac, const c2<T>* dense, hipStream_t s)
 {
     const OpView& v = op.view;
     // K operators: forward product only (the API rejects the others)
     if (v.fam != 0 && (mode == MODE_AH || mode == MODE_NH || recon == 1)) return false;
     if (recon == 1 && (sizeof(T) != 4 || !bf16_recon_available(op))) return false;
+    const int rs = zv_stride(v);
     switch (v.L[2]) {
     case 512:
-        if (zfast_lds<T, 512>(v) > op.max_lds) return false;
-        return launch_z<T, 512>(op, mode, recon, nrhs, S2, tw, core, fac, dense, s) == hipSuccess;
+        if (zfast_lds<T, 512>(rs) > op.max_lds) return false;
+        break;
     case 256:
-        if (zfast_lds<T, 256>(v) > op.max_lds) return false;
-        return launch_z<T, 256>(op, mode, recon, nrhs, S2, tw, core, fac, dense, s) == hipSuccess;
+        if (zfast_lds<T, 256>(rs) > op.max_lds) return false;
+        break;
     case 128:
-        if (zfast_lds<T, 128>(v) > op.max_lds) return false;
-        return launch_z<T, 128>(op, mode, recon, nrhs, S2, tw, core, fac, dense, s) == hipSuccess;
+        if (zfast_lds<T, 128>(rs) > op.max_lds) return false;
+        break;
     default: return false;
+    }
+    if (op.nhat_source != 1) launch_zv<T>(op, V, s);
+    switch (v.L[2]) {
+    case 512: return launch_z<T, 512>(op, mode, recon, nrhs, S2, tw, V, fac, dense, s) == hipSuccess;
+    case 256: return launch_z<T, 256>(op, mode, recon, nrhs, S2, tw, V, fac, dense, s) == hipSuccess;
+    default: return launch_z<T, 128>(op, mode, recon, nrhs, S2, tw, V, fac, dense, s) == hipSuccess;
     }
 }
 
@@ -1063,12 +1099,9 @@ bool xy_group_fast(int kind, int L, const XYGroup& g, int nblocks, const c2<T>* 
 }
 
 template <typename T, int L3>
-static void launch_z_group(int conj, int recon, int rmax, const ZGroup& g, int nblocks, const c2<T>* tw,
-                           hipStream_t s)
+static void launch_z_group(int conj, int recon, int rs, const ZGroup& g, int nblocks, const c2<T>* tw, hipStream_t s)
 {
-    OpView dummy{};
-    dummy.rmax = rmax;
-    size_t lds = zfast_lds<T, L3>(dummy);
+    size_t lds = zfast_lds<T, L3>(rs);
     auto kern = conj ? k_z_fast_multi<T, L3, true, 0> : k_z_fast_multi<T, L3, false, 0>;
     if constexpr (sizeof(T) == 4) {
         if (recon == 1) kern = conj ? k_z_fast_multi<T, L3, true, 1> : k_z_fast_multi<T, L3, false, 1>;
@@ -1078,23 +1111,21 @@ static void launch_z_group(int conj, int recon, int rmax, const ZGroup& g, int n
 }
 
 template <typename T>
-bool z_group_fast(int L3, int conj, int recon, int rmax, size_t max_lds, const ZGroup& g, int nblocks,
+bool z_group_fast(int L3, int conj, int recon, int rs, size_t max_lds, const ZGroup& g, int nblocks,
                   const c2<T>* tw, hipStream_t s)
 {
-    OpView dummy{};
-    dummy.rmax = rmax;
     switch (L3) {
     case 512:
-        if (zfast_lds<T, 512>(dummy) > max_lds) return false;
-        launch_z_group<T, 512>(conj, recon, rmax, g, nblocks, tw, s);
+        if (zfast_lds<T, 512>(rs) > max_lds) return false;
+        launch_z_group<T, 512>(conj, recon, rs, g, nblocks, tw, s);
         return true;
     case 256:
-        if (zfast_lds<T, 256>(dummy) > max_lds) return false;
-        launch_z_group<T, 256>(conj, recon, rmax, g, nblocks, tw, s);
+        if (zfast_lds<T, 256>(rs) > max_lds) return false;
+        launch_z_group<T, 256>(conj, recon, rs, g, nblocks, tw, s);
         return true;
     case 128:
-        if (zfast_lds<T, 128>(dummy) > max_lds) return false;
-        launch_z_group<T, 128>(conj, recon, rmax, g, nblocks, tw, s);
+        if (zfast_lds<T, 128>(rs) > max_lds) return false;
+        launch_z_group<T, 128>(conj, recon, rs, g, nblocks, tw, s);
         return true;
     default: return false;
     }
@@ -1118,9 +1149,9 @@ template bool z_group_fast<double>(int, int, int, int, size_t, const ZGroup&, in
 VIE_XYF_INST(float, float)
 VIE_XYF_INST(double, double)
 VIE_XYF_INST(double, float)
-template bool z_pass_fast<float>(const DeviceOp&, int, int, int, c2<float>*, const c2<float>*, const c2<float>*,
+template bool z_pass_fast<float>(const DeviceOp&, int, int, int, c2<float>*, c2<float>*, const c2<float>*,
                                  const c2<float>*, const c2<float>*, hipStream_t);
-template bool z_pass_fast<double>(const DeviceOp&, int, int, int, c2<double>*, const c2<double>*,
-                                  const c2<double>*, const c2<double>*, const c2<double>*, hipStream_t);
+template bool z_pass_fast<double>(const DeviceOp&, int, int, int, c2<double>*, c2<double>*, const c2<double>*,
+                                  const c2<double>*, const c2<double>*, hipStream_t);
 
 }  // namespace vie

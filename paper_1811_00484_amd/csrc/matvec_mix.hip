@@ -393,15 +393,15 @@ bool xy_pass_mix(const DeviceOp& op, int kind, const void* in, void* out, const 
 // branch).  One workgroup per (k2, c).
 template <typename T>
 __global__ void __launch_bounds__(kVNT) k_zv(OpView v, const c2<T>* __restrict__ core, const c2<T>* __restrict__ fac,
-                                             int lanes, int rs, c2<T>* __restrict__ V)
+                                             int rs, c2<T>* __restrict__ V)
 {
     const int k2 = blockIdx.x, nc = gridDim.y, ci = blockIdx.y, c = 6 - nc + ci;
     const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
     v_rows<T>(core + v.core_off[c], fac + v.fac_off[c][0], fac + v.fac_off[c][1] + (long)k2 * r2, v.r[c][0], r2,
-              v.r[c][2], n1p1, lanes, v.rmax, rs, v.cp, V + ((long)k2 * nc + ci) * n1p1 * rs);
+              v.r[c][2], n1p1, v.rmax, rs, v.cp, V + ((long)k2 * nc + ci) * n1p1 * rs);
 }
 
-static int zv_stride(const OpView& v)
+int zv_stride(const OpView& v)
 {
     int rs = 1;
     for (int c = v.fam ? 3 : 0; c < 6; ++c) rs = rs > v.r[c][2] ? rs : v.r[c][2];
@@ -414,14 +414,21 @@ size_t zv_elems(const OpView& v)
 }
 
 template <typename T>
-static void launch_zv(const DeviceOp& op, const c2<T>* core, const c2<T>* fac, c2<T>* V, hipStream_t s)
+void launch_zv(const DeviceOp& op, c2<T>* V, hipStream_t s)
 {
     const OpView& v = op.view;
-    const int rs = zv_stride(v), lanes = v_rows_lanes<T>(v.n[0] + 1, v.rmax, rs);
-    const size_t lds = v_rows_lds<T>(lanes, v.rmax, rs);
+    const c2<T>*core, *fac;
+    if constexpr (sizeof(T) == 8) {
+        core = op.d64.core;
+        fac = op.d64.fac;
+    } else {
+        core = op.d32.core;
+        fac = op.d32.fac;
+    }
+    const int rs = zv_stride(v);
+    const size_t lds = v_rows_lds<T>(v.rmax, rs);
     (void)hipFuncSetAttribute((const void*)k_zv<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_zv<T>, dim3(v.n[1] + 1, v.fam ? 3 : 6), dim3(kVNT), lds, s, v, core, fac, lanes,
-                       rs, V);
+    hipLaunchKernelGGL(k_zv<T>, dim3(v.n[1] + 1, v.fam ? 3 : 6), dim3(kVNT), lds, s, v, core, fac, rs, V);
 }
 
 // ---------------------------------------------------------------------------
@@ -686,15 +693,13 @@ template <typename T>
 bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hipStream_t s)
 {
     const OpView& v = op.view;
-    const c2<T>*tw, *core, *fac, *dense;
+    const c2<T>*tw, *fac, *dense;
     if constexpr (sizeof(T) == 8) {
         tw = op.tw64[2];
-        core = op.d64.core;
         fac = op.d64.fac;
         dense = op.dense64;
     } else {
         tw = op.tw32[2];
-        core = op.d32.core;
         fac = op.d32.fac;
         dense = op.dense32;
     }
@@ -721,7 +726,7 @@ bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hip
     a.nq = (long)(v.n[0] + 1) * (v.n[1] + 1) >= 1024 && lds_of(2) <= op.max_lds / 2 ? 2 : 1;
     const size_t lds = lds_of(a.nq);
     if (lds > op.max_lds) return false;
-    if (!a.dense) launch_zv<T>(op, core, fac, V, s);
+    if (!a.dense) launch_zv<T>(op, V, s);
     const int nblk = 8 * (((v.n[0] + a.nq) / a.nq * (v.n[1] + 1) + 7) / 8);
     // right-hand sides share the tables of a workgroup as far as the grid
     // still holds eight workgroups per CU
@@ -742,6 +747,8 @@ bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hip
 VIE_MIX_INST(float, float)
 VIE_MIX_INST(double, double)
 VIE_MIX_INST(double, float)
+template void launch_zv<float>(const DeviceOp&, c2<float>*, hipStream_t);
+template void launch_zv<double>(const DeviceOp&, c2<double>*, hipStream_t);
 template bool z_pass_mix<float>(const DeviceOp&, int, int, c2<float>*, c2<float>*, hipStream_t);
 template bool z_pass_mix<double>(const DeviceOp&, int, int, c2<double>*, c2<double>*, hipStream_t);
 

@@ -97,8 +97,8 @@ constexpr int pwl_nc()
 // sixteen, so that the z pass reads and sums without a branch): one workgroup
 // per (k2, tensor).
 template <typename T, int FAM>
-__global__ void __launch_bounds__(kVNT) k_pwl_v(const PwlBlock<T>* __restrict__ blk, int lanes, int rmax,
-                                                int rs, c2<T>* __restrict__ V)
+__global__ void __launch_bounds__(kVNT) k_pwl_v(const PwlBlock<T>* __restrict__ blk, int rmax, int rs,
+                                                c2<T>* __restrict__ V)
 {
     constexpr int NC = pwl_nc<FAM>();
     const int k2 = blockIdx.x, bc = blockIdx.y;
@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(kVNT) k_pwl_v(const PwlBlock<T>* __restrict__ 
     const OpView& v = blk[b].v;
     const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
     v_rows<T>(blk[b].core + v.core_off[c], blk[b].fac + v.fac_off[c][0], blk[b].fac + v.fac_off[c][1] + (long)k2 * r2,
-              v.r[c][0], r2, v.r[c][2], n1p1, lanes, rmax, rs, false, V + ((long)k2 * 10 * NC + bc) * n1p1 * rs);
+              v.r[c][0], r2, v.r[c][2], n1p1, rmax, rs, false, V + ((long)k2 * 10 * NC + bc) * n1p1 * rs);
 }
 
 // ---------------------------------------------------------------------------
@@ -671,11 +671,10 @@ hipError_t launch_pwl_z(const vie_pwl_op& P, int conj, c2<T>* S2, c2<T>* V, int 
         tw = op.tw32[2];
         blk = P.dev32;
     }
-    const int lanes = v_rows_lanes<T>(v.n[0] + 1, P.rmax, za.rs);
-    const size_t vlds = v_rows_lds<T>(lanes, P.rmax, za.rs);
+    const size_t vlds = v_rows_lds<T>(P.rmax, za.rs);
     auto kv = P.fam ? k_pwl_v<T, 1> : k_pwl_v<T, 0>;
     (void)hipFuncSetAttribute((const void*)kv, hipFuncAttributeMaxDynamicSharedMemorySize, (int)vlds);
-    hipLaunchKernelGGL(kv, dim3(v.n[1] + 1, 10 * nc), dim3(kVNT), vlds, s, blk, lanes, P.rmax, za.rs, V);
+    hipLaunchKernelGGL(kv, dim3(v.n[1] + 1, 10 * nc), dim3(kVNT), vlds, s, blk, P.rmax, za.rs, V);
     constexpr auto shapes = std::make_integer_sequence<int, (int)std::size(kPwlShapes<T>)>{};
     for (int m : {max_pb, 10}) {   // an override that no shape serves is left out
         const bool ok = P.fam  ? try_pwl_shapes<T, 1, false>(op, m, za, p, S2, tw, blk, V, s, shapes)

@@ -6,43 +6,52 @@
 // of U1 in registers and W read by broadcast, the sums transposed through LDS
 // into one contiguous run.  With lanes on the columns instead, every factor
 // read served eight lanes only and the vector memory unit set the pace
-// (60 tensors on 121 x 121 (k1, k2): 137 us).
+// (60 tensors on 121 x 121 (k1, k2): 137 us, 65 now).
 #pragma once
 #include "dev_common.h"
 
 namespace vie {
 
-constexpr int kVChunk = 16;   // x ranks per register chunk
-constexpr int kVNT = 256;     // threads per workgroup: `lanes` k1 at a time, 256 / lanes shares of the columns
+constexpr int kVNT = 256;     // threads per workgroup: 64 k1 at a time, four shares of the columns
 
-__host__ __device__ inline int v_rows_pad(int r) { return (r + kVChunk - 1) / kVChunk * kVChunk; }
+// W rows in batches of eight, whole sixteens wherever more than eight are left
+__host__ __device__ inline int v_rows_pad(int r) { return r % 16 > 8 ? (r + 15) / 16 * 16 : (r + 7) / 8 * 8; }
 __host__ __device__ inline int v_rows_row(int rmax, int rs) { return (rmax > rs ? rmax : rs) | 1; }
 
-// lanes: 64, 128 or 256, as few as one sweep needs and as the tile's 64 KB allow
 template <typename T>
-inline int v_rows_lanes(int n1p1, int rmax, int rs)
+inline size_t v_rows_lds(int rmax, int rs)
 {
-    int lanes = n1p1 <= 64 ? 64 : n1p1 <= 128 ? 128 : 256;
-    while (lanes > 64 && (size_t)lanes * v_rows_row(rmax, rs) * sizeof(c2<T>) > 65536) lanes /= 2;
-    return lanes;
+    return sizeof(c2<T>) * ((size_t)rmax * ((rmax + 15) / 16 * 16) + (size_t)64 * v_rows_row(rmax, rs));
 }
-template <typename T>
-inline size_t v_rows_lds(int lanes, int rmax, int rs)
+
+// sums of x ranks a0 .. a0 + CH for this lane's row, columns share, share + 4, ..
+template <int CH, typename T>
+__device__ __forceinline__ void v_rows_sums(const c2<T> (&u)[16], const c2<T>* Wt, int wrow, int a0, int share, int r3,
+                                            int rs, c2<T>* mine)
 {
-    return sizeof(c2<T>) * ((size_t)rmax * v_rows_pad(rmax) + (size_t)lanes * v_rows_row(rmax, rs));
+#pragma unroll 2
+    for (int ga = share; ga < rs; ga += kVNT / 64) {
+        c2<T> acc = a0 ? mine[ga] : mk<T>(0, 0), odd = mk<T>(0, 0);
+        if (ga < r3) {
+            const c2<T>* w = Wt + ga * wrow + a0;
+#pragma unroll
+            for (int q = 0; q < CH; ++q) fma_c(q & 1 ? odd : acc, u[q], w[q]);
+        }
+        mine[ga] = acc + odd;
+    }
 }
 
 // out[k1 rs + g] for k1 in [0, n1p1), zero for g in [r3, rs); cp: a
 // superdiagonal core.  rmax: as given to v_rows_lds.
 template <typename T>
 __device__ __forceinline__ void v_rows(const c2<T>* G, const c2<T>* U1, const c2<T>* U2, int r1, int r2, int r3,
-                                       int n1p1, int lanes, int rmax, int rs, bool cp,
+                                       int n1p1, int rmax, int rs, bool cp,
                                        c2<T>* __restrict__ out)
 {
     extern __shared__ __align__(16) unsigned char v_smem[];
     const int row = v_rows_row(rmax, rs), wrow = v_rows_pad(r1);
     c2<T>* Wt = reinterpret_cast<c2<T>*>(v_smem);                // [r3][wrow], zero beyond r1
-    c2<T>* tile = Wt + (size_t)rmax * v_rows_pad(rmax);          // [lanes][row]
+    c2<T>* tile = Wt + (size_t)rmax * ((rmax + 15) / 16 * 16);   // [64][row]
     const int tid = threadIdx.x;
     constexpr int nt = kVNT;
     if (cp) {
@@ -59,50 +68,42 @@ __device__ __forceinline__ void v_rows(const c2<T>* G, const c2<T>* U1, const c2
         c2<T> acc = mk<T>(0, 0);
         if (al < r1) {
             const c2<T>* g = G + (long)al * r2 * r3 + ga;
-            for (int b0 = 0; b0 < r2; b0 += 8) {
-                c2<T> gv[8], uv[8];
+            for (int b0 = 0; b0 < r2; b0 += 16) {
+                c2<T> gv[16], uv[16];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
+                for (int q = 0; q < 16; ++q) {
                     const int b = min(b0 + q, r2 - 1);
                     gv[q] = ldg(g + (long)b * r3);
                     uv[q] = ldg(U2 + b);
                 }
 #pragma unroll
-                for (int q = 0; q < 8; ++q)
+                for (int q = 0; q < 16; ++q)
                     if (b0 + q < r2) fma_c(acc, gv[q], uv[q]);
             }
         }
         Wt[ga * wrow + al] = acc;
     }
-    const int lane = tid % lanes, share = tid / lanes, shares = nt / lanes;
-    for (int k0 = 0; k0 < n1p1; k0 += lanes) {
-        const int rows = min(lanes, n1p1 - k0);
+    const int lane = tid % 64, share = tid / 64;
+    for (int k0 = 0; k0 < n1p1; k0 += 64) {
+        const int rows = min(64, n1p1 - k0);
         for (int e = tid; e < rows * r1; e += nt) {
             const int k = e / r1;
             tile[k * row + e - k * r1] = ldg(U1 + (long)k0 * r1 + e);
         }
         __syncthreads();   // W and the tile's rows of U1
         c2<T>* mine = tile + lane * row;
-        c2<T> u[kVChunk];
+        c2<T> u[16];
 #pragma unroll
-        for (int q = 0; q < kVChunk; ++q) u[q] = q < r1 && lane < rows ? mine[q] : mk<T>(0, 0);
+        for (int q = 0; q < 16; ++q) u[q] = q < r1 && lane < rows ? mine[q] : mk<T>(0, 0);
         __syncthreads();   // the rows are replaced by the sums
-        for (int a0 = 0; a0 < r1; a0 += kVChunk) {
+        for (int a0 = 0; a0 < r1; a0 += 16) {
             if (a0 > 0) {
 #pragma unroll
-                for (int q = 0; q < kVChunk; ++q)
+                for (int q = 0; q < 16; ++q)
                     u[q] = a0 + q < r1 && lane < rows ? ldg(U1 + (long)(k0 + lane) * r1 + a0 + q) : mk<T>(0, 0);
             }
-#pragma unroll 2
-            for (int ga = share; ga < rs; ga += shares) {
-                c2<T> acc = a0 ? mine[ga] : mk<T>(0, 0), odd = mk<T>(0, 0);
-                if (ga < r3) {
-                    const c2<T>* w = Wt + ga * wrow + a0;
-#pragma unroll
-                    for (int q = 0; q < kVChunk; ++q) fma_c(q & 1 ? odd : acc, u[q], w[q]);
-                }
-                mine[ga] = acc + odd;
-            }
+            if (r1 - a0 <= 8) v_rows_sums<8>(u, Wt, wrow, a0, share, r3, rs, mine);
+            else v_rows_sums<16>(u, Wt, wrow, a0, share, r3, rs, mine);
         }
         __syncthreads();
         for (int e = tid; e < rows * rs; e += nt) {

@@ -1148,10 +1148,10 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
     double best = 1e300;
     auto run = [&]() -> bool {
         if (dtype == VIE_C128)
-            return z_pass_fast<double>(d, MODE_A, 0, nrhs, (c2<double>*)ws, d.tw64[2], d.d64.core, d.d64.fac,
-                                       d.dense64, s);
-        return z_pass_fast<float>(d, MODE_A, 0, nrhs, (c2<float>*)ws, d.tw32[2], d.d32.core, d.d32.fac, d.dense32,
-                                  s);
+            return z_pass_fast<double>(d, MODE_A, 0, nrhs, (c2<double>*)ws, (c2<double>*)ws + s2, d.tw64[2],
+                                       d.d64.fac, d.dense64, s);
+        return z_pass_fast<float>(d, MODE_A, 0, nrhs, (c2<float>*)ws, (c2<float>*)ws + s2, d.tw32[2], d.d32.fac,
+                                  d.dense32, s);
     };
     for (int k = 0; k < 4 && e == hipSuccess; ++k) {
         d.zchunk = cand[k];

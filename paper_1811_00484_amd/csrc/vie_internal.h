@@ -103,6 +103,7 @@ struct ZFastArgs {
     int conj;
     int dense;
     int chunk;     // k1 quads per workgroup
+    int rs;        // V row length (zv_stride)
 };
 
 // Per-instance descriptors of a grouped register-FFT launch (one launch per
@@ -120,13 +121,15 @@ struct XYInst {
 };
 struct ZInst {
     void* S2;
-    const void* core;
+    const void* V;
     const void* fac;
     const void* dense;
     const unsigned short* f3m;
     ZFastArgs za;
     int off;    // first workgroup of the instance
-    int nbx;    // workgroups per right-hand side
+    int nbx;    // workgroups per share of the right-hand sides
+    int gy;     // shares: right-hand sides b, b + gy, ..
+    int nrhs;
 };
 
 // One instance of a multi-instance matvec (several grids, one launch per pass).
@@ -221,12 +224,19 @@ bool xy_ident_fast(int kind, int L, const void* in, void* out, const c2<T>* x, c
 template <typename TV, typename T>
 bool xy_pass_mix(const DeviceOp& op, int kind, const void* in, void* out, const c2<TV>* x, const c2<TV>* eps,
                  int mode, int nrhs, const int* rhs_map, bool ident, hipStream_t s);
-size_t zv_elems(const OpView& v);   // complex elements of the z pass's V tables
+// V rows of the z pass (k_zv): row length, complex elements, the kernel
+int zv_stride(const OpView& v);
+size_t zv_elems(const OpView& v);
+template <typename T>
+void launch_zv(const DeviceOp& op, c2<T>* V, hipStream_t s);
+// launch shape of the register-FFT z pass: k1 quads per workgroup, workgroups
+// per share of the right-hand sides, shares
+void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int& chunk, int& nbx, int& gy);
 template <typename T>
 bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hipStream_t s);
 // recon 1: N^ tables from the BF16 z factors on MFMA (T = float only)
 template <typename T>
-bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, const c2<T>* tw, const c2<T>* core,
+bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, c2<T>* V, const c2<T>* tw,
                  const c2<T>* fac, const c2<T>* dense, hipStream_t s);
 // whether the BF16 MFMA reconstruction can run for this operator
 bool bf16_recon_available(const DeviceOp& op);
@@ -238,7 +248,7 @@ int xy_fast_tile(int L);   // pencils per workgroup of the X/Y kernels at length
 template <typename TV, typename T>
 bool xy_group_fast(int kind, int L, const XYGroup& g, int nblocks, const c2<T>* tw, hipStream_t s);
 template <typename T>
-bool z_group_fast(int L3, int conj, int recon, int rmax, size_t max_lds, const ZGroup& g, int nblocks,
+bool z_group_fast(int L3, int conj, int recon, int rs, size_t max_lds, const ZGroup& g, int nblocks,
                   const c2<T>* tw, hipStream_t s);
 // 0 = choose per pass (register FFT where the length allows), 1 = generic kernels only
 extern int g_kernel_path;

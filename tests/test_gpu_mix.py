@@ -114,3 +114,27 @@ def test_dense_spectrum(dt):
         _check(n, dt, 2)
     finally:
         vie.set_nhat(op, "tucker")
+
+
+# the register-FFT z pass on the same problems: an odd number of k1 quads, right-hand
+# sides that share a workgroup's tables, and (complex128 at 512) a table in the
+# place of the FFT slices
+@pytest.mark.parametrize("n,nrhs", [((60, 40, 64), 5), ((42, 50, 128), 3), ((7, 6, 256), 2)])
+@pytest.mark.parametrize("dt", list(TOL))
+def test_register_z_pass_shares_tables(n, nrhs, dt):
+    _check(n, dt, nrhs)
+
+
+@pytest.mark.parametrize("n", [(60, 40, 64), (5, 6, 256)])
+def test_register_z_pass_at_the_largest_rank(n):
+    _check(n, torch.complex64, 1, rank=40)
+
+
+def test_bf16_right_hand_sides_equal_single_calls():
+    n = (60, 40, 64)
+    op, _ = _problem(n)
+    rng = np.random.default_rng(8)
+    x = to_dev(_cx(rng, (5, 3, n[2], n[1], n[0])), torch.complex64)
+    y = vie.matvec(op, x, kind="N", recon="bf16")
+    for s in range(5):
+        assert torch.equal(y[s], vie.matvec(op, x[s].contiguous(), kind="N", recon="bf16"))
