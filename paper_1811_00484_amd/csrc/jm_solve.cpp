@@ -146,8 +146,8 @@ vie_status gmres_run(long n, const KLayout& L, FA apply, FI apply_inner, bool re
             e = kr_mdot<TK>(V, n, n, j + 2, V, wo, n, dmap, 1, partial, dh1, st);
             if (e == hipSuccess) e = kr_maxpy<TK>(V, wo, n, V, n, n, j + 1, j + 2, dh1, -1.0, n, dmap, 1, st);
             if (e == hipSuccess) e = kr_mdot<TK>(V, n, n, j + 1, V, wo, n, dmap, 1, partial, dh2, st);
-            if (e == hipSuccess) e = kr_maxpy<TK>(V, wo, n, V, n, n, j + 1, j + 1, dh2, -1.0, n, dmap, 1, st);
-            if (e == hipSuccess) e = kr_norm2<TK>(V, wo, n, n, dmap, 1, partial, dnrm, st);
+            if (e == hipSuccess)
+                e = kr_maxpy<TK>(V, wo, n, V, n, n, j + 1, j + 1, dh2, -1.0, n, dmap, 1, st, partial, dnrm);
             if (e == hipSuccess) e = hipMemcpyAsync(h1.data(), dh1, sizeof(c2<double>) * (j + 2), hipMemcpyDeviceToHost, st);
             if (e == hipSuccess) e = hipMemcpyAsync(h2.data(), dh2, sizeof(c2<double>) * (j + 1), hipMemcpyDeviceToHost, st);
             if (e == hipSuccess) e = sync_copy(&hn, dnrm, sizeof(hn));

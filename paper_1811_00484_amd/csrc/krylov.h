@@ -12,11 +12,12 @@ int krylov_nblk(long n);   // per-system partial count for a vector of n complex
 template <typename TK>
 hipError_t kr_mdot(const c2<TK>* V, long vstride, long sstride, int nvec, const c2<TK>* W, long wvoff, long n,
                    const int* map, int nact, c2<double>* partial, c2<double>* out, hipStream_t st);
-// W[s] += sign * sum_v V_v[s] coef[a*cstride + v]
+// W[s] += sign * sum_v V_v[s] coef[a*cstride + v]; with norm2, also
+// norm2[a].x = the new ||W[s]||^2 (partial as for kr_mdot)
 template <typename TK>
 hipError_t kr_maxpy(c2<TK>* W, long wvoff, long wsstride, const c2<TK>* V, long vstride, long sstride, int nvec,
                     int cstride, const c2<double>* coef, double sign, long n, const int* map, int nact,
-                    hipStream_t st);
+                    hipStream_t st, c2<double>* partial = nullptr, c2<double>* norm2 = nullptr);
 // out[a].x = ||W[s]||^2
 template <typename TK>
 hipError_t kr_norm2(const c2<TK>* W, long wvoff, long sstride, long n, const int* map, int nact,

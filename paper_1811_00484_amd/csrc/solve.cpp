@@ -285,8 +285,8 @@ vie_status run_multi(std::vector<Inst<TK>>& I, int mode, const vie_solve_opts& o
                 // (w is basis slot j + 1, so it is the last of the j + 2 dots)
                 e = kr_mdot<TK>(in.V, vstride, n, j + 2, in.V, wvoff, n, in.dmap, nr, in.partial, in.dh1, st);
                 if (e == hipSuccess)
-                    e = kr_maxpy<TK>(in.V, wvoff, n, in.V, vstride, n, j + 1, j + 2, in.dh1, -1.0, n, in.dmap, nr, st);
-                if (e == hipSuccess) e = kr_norm2<TK>(in.V, wvoff, n, n, in.dmap, nr, in.partial, in.dnrm, st);
+                    e = kr_maxpy<TK>(in.V, wvoff, n, in.V, vstride, n, j + 1, j + 2, in.dh1, -1.0, n, in.dmap, nr, st,
+                                     in.partial, in.dnrm);
                 std::vector<c2<double>> h1((size_t)nr * (j + 2)), h2((size_t)nr * (j + 1)), hb(nr);
                 if (e == hipSuccess)
                     e = hipMemcpyAsync(h1.data(), in.dh1, sizeof(c2<double>) * h1.size(), hipMemcpyDeviceToHost, st);
@@ -310,8 +310,7 @@ vie_status run_multi(std::vector<Inst<TK>>& I, int mode, const vie_solve_opts& o
                     e = kr_mdot<TK>(in.V, vstride, n, j + 1, in.V, wvoff, n, in.dmap, nr, in.partial, in.dh2, st);
                     if (e == hipSuccess)
                         e = kr_maxpy<TK>(in.V, wvoff, n, in.V, vstride, n, j + 1, j + 1, in.dh2, -1.0, n, in.dmap, nr,
-                                         st);
-                    if (e == hipSuccess) e = kr_norm2<TK>(in.V, wvoff, n, n, in.dmap, nr, in.partial, in.dnrm, st);
+                                         st, in.partial, in.dnrm);
                     if (e == hipSuccess)
                         e = hipMemcpyAsync(h2.data(), in.dh2, sizeof(c2<double>) * h2.size(), hipMemcpyDeviceToHost,
                                            st);
