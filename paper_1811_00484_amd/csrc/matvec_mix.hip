@@ -398,7 +398,7 @@ __global__ void __launch_bounds__(kVNT) k_zv(OpView v, const c2<T>* __restrict__
     const int k2 = blockIdx.x, nc = gridDim.y, ci = blockIdx.y, c = 6 - nc + ci;
     const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
     v_rows<T>(core + v.core_off[c], fac + v.fac_off[c][0], fac + v.fac_off[c][1] + (long)k2 * r2, v.r[c][0], r2,
-              v.r[c][2], n1p1, v.rmax, rs, v.cp, V + ((long)k2 * nc + ci) * n1p1 * rs);
+              v.r[c][2], r2 * v.r[c][2], v.r[c][2], 1, n1p1, v.rmax, rs, v.cp, V + ((long)k2 * nc + ci) * n1p1 * rs);
 }
 
 int zv_stride(const OpView& v)

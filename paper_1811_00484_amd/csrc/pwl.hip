@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(kVNT) k_pwl_v(const PwlBlock<T>* __restrict__ 
     const OpView& v = blk[b].v;
     const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
     v_rows<T>(blk[b].core + v.core_off[c], blk[b].fac + v.fac_off[c][0], blk[b].fac + v.fac_off[c][1] + (long)k2 * r2,
-              v.r[c][0], r2, v.r[c][2], n1p1, rmax, rs, false, V + ((long)k2 * 10 * NC + bc) * n1p1 * rs);
+              v.r[c][0], r2, v.r[c][2], r2 * v.r[c][2], v.r[c][2], 1, n1p1, rmax, rs, false, V + ((long)k2 * 10 * NC + bc) * n1p1 * rs);
 }
 
 // ---------------------------------------------------------------------------

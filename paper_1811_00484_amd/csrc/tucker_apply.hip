@@ -4,21 +4,26 @@
 // Sec. V-B (Table II, timed in Table IV), done in one pass over x and y with
 // no buffer for D.
 //
-//   Tucker: W(k)   = G x3 U3(k, :)           (r1 x r2 per k; first kernel)
-//           V(j,k) = W(k) U2(j, :)^T          (r1 per (j, k); second kernel)
+//   Tucker: W(k)   = G x3 U3(k, :)           (r1 x r2, in LDS)
+//           V(j,k) = W(k) U2(j, :)^T          (r1 per (j, k); one workgroup per k)
 //   CP:     V_l(j,k) = lambda_l U2(j, l) U3(k, l) (the 4-D loop of Sec. V-B)
-//   then    D(i,j,k) = U1(i, :) . V(j, k), y = D .* x   (third kernel)
-// The third kernel walks the (i, j) plane flat (consecutive threads take
-// consecutive i, wrapping into the next j), so no lane idles on ragged n1;
-// each thread keeps its row U1(i, :) in registers (read coalesced from a
-// transposed copy) and reads V(j, k) through the cache (the lanes of a
-// wavefront share one or two j), for KT consecutive k.  HBM traffic: x in,
-// y out, and V (r1 complex per (j, k)).
+//   then    D(i,j,k) = U1(i, :) . V(j, k), y = D .* x   (last kernel)
+// The last kernel gives a workgroup a tile of i and a run of (j, k) rows: a
+// thread keeps U1(i, :) of its i in registers for the whole run, and the rows
+// V(j, k), the same for every lane, come by scalar loads, so that the inner
+// product costs its multiply-adds and nothing else.  HBM traffic: x in, y out,
+// and V (r1 complex per (j, k)).
+//
+// 300^3, rank 25, complex128, MI355X: 0.94 ms with V read through the vector
+// memory unit by every lane (16 rows of k per thread) and W through HBM;
+// 0.32 ms now, of which 0.25 apply (3.5 TB/s of x and y; three wavefronts a SIMD
+// hold their 25 factors, the scalar loads of V set the pace).
 #include <hip/hip_runtime.h>
 
 #include <string>
 
 #include "vie.h"
+#include "v_rows.h"
 #include "vie_internal.h"
 
 namespace vie {
@@ -31,42 +36,31 @@ namespace {
 using namespace vie;
 
 constexpr int kRMax = 32;    // largest rank per mode
-constexpr int kKT = 16;      // k rows per workgroup of the apply kernel
-constexpr int kNT = 256;     // threads per workgroup of the apply kernel ((i, j) positions)
+constexpr int kNT = 64;      // threads per workgroup of the apply kernel, one i each
+constexpr int kRun = 32;     // (j, k) rows per workgroup of the apply kernel
 
+// V(j, k) of a Tucker form: one workgroup per k contracts the core with
+// U3(k, :) and applies it to every row of U2.
 template <typename T>
-__global__ void __launch_bounds__(256) k_core_z(const c2<T>* __restrict__ G, const c2<T>* __restrict__ U3, int r1,
-                                                int r2, int r3, c2<T>* __restrict__ W)
+__global__ void __launch_bounds__(kVNT) k_vk(const c2<T>* __restrict__ G, const c2<T>* __restrict__ U2,
+                                             const c2<T>* __restrict__ U3, c2<T>* __restrict__ V, int n2, int r1, int r2,
+                                             int r3)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int k = blockIdx.y;
-    if (e >= r1 * r2) return;
-    const c2<T>* g = G + (long)e * r3;
-    const c2<T>* u = U3 + (long)k * r3;
-    c2<T> acc = mk<T>(0, 0);
-    for (int c = 0; c < r3; ++c) fma_c(acc, g[c], u[c]);
-    W[(long)k * r1 * r2 + e] = acc;
+    const long k = blockIdx.x;
+    v_rows<T>(G, U2, U3 + k * r3, r2, r3, r1, r3, 1, r2 * r3, n2, kRMax, r1, false, V + k * n2 * r1);
 }
 
-template <typename T, bool CP>
-__global__ void __launch_bounds__(256) k_vjk(const c2<T>* __restrict__ W, const c2<T>* __restrict__ lam,
-                                             const c2<T>* __restrict__ U2, const c2<T>* __restrict__ U3,
-                                             c2<T>* __restrict__ V, int n2, int n3, int r1, int r2, int r3)
+template <typename T>
+__global__ void __launch_bounds__(256) k_vjk_cp(const c2<T>* __restrict__ lam, const c2<T>* __restrict__ U2,
+                                                const c2<T>* __restrict__ U3, c2<T>* __restrict__ V, int n2, int n3,
+                                                int r)
 {
     const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long)n3 * n2 * r1) return;
-    const int a = (int)(e % r1);
-    const long jk = e / r1;
+    if (e >= (long)n3 * n2 * r) return;
+    const int a = (int)(e % r);
+    const long jk = e / r;
     const int j = (int)(jk % n2), k = (int)(jk / n2);
-    c2<T> v = mk<T>(0, 0);
-    if constexpr (CP) {
-        v = lam[a] * (U2[(long)j * r2 + a] * U3[(long)k * r3 + a]);
-    } else {
-        const c2<T>* w = W + ((long)k * r1 + a) * r2;
-        const c2<T>* u = U2 + (long)j * r2;
-        for (int b = 0; b < r2; ++b) fma_c(v, w[b], u[b]);
-    }
-    V[e] = v;
+    V[e] = lam[a] * (U2[(long)j * r + a] * U3[(long)k * r + a]);
 }
 
 // U1 (n1 x r1) into U1T (r1 x n1), so that the apply kernel's lanes read
@@ -81,30 +75,50 @@ __global__ void __launch_bounds__(256) k_transpose(const c2<T>* __restrict__ U1,
     U1T[e] = U1[(long)i * r1 + a];
 }
 
-template <typename T>
+template <typename T, int R>
 __global__ void __launch_bounds__(kNT) k_apply(const c2<T>* __restrict__ V, const c2<T>* __restrict__ U1T,
-                                               const c2<T>* __restrict__ x, c2<T>* __restrict__ y, int n1,
-                                               int n2, int n3, int r1)
+                                               const c2<T>* __restrict__ x, c2<T>* __restrict__ y, int n1, long rows)
 {
-    const long p = (long)blockIdx.x * kNT + threadIdx.x;
-    const long plane = (long)n1 * n2;
-    if (p >= plane) return;
-    const int i = (int)(p % n1), j = (int)(p / n1);
-    c2<T> u[kRMax];
+    const int i = blockIdx.y * kNT + threadIdx.x;
+    const int il = min(i, n1 - 1);   // lanes beyond the row compute and do not store
+    c2<T> u[R];
 #pragma unroll
-    for (int a = 0; a < kRMax; ++a) u[a] = a < r1 ? U1T[(long)a * n1 + i] : mk<T>(0, 0);
-    const int k0 = blockIdx.y * kKT;
-    const int kend = min(kKT, n3 - k0);
-    for (int kk = 0; kk < kend; ++kk) {
-        const int k = k0 + kk;
-        const c2<T>* v = V + ((long)k * n2 + j) * r1;
-        c2<T> d = mk<T>(0, 0);
+    for (int a = 0; a < R; ++a) u[a] = U1T[(long)a * n1 + il];
+    const long r0 = (long)blockIdx.x * kRun;
+    const int nr = (int)min((long)kRun, rows - r0);
+    const c2<T>* v = V + r0 * R;
+    const c2<T>* xr = x + r0 * n1 + il;
+    c2<T>* yr = y + r0 * n1 + il;
+    // four rows of x in flight while the four before them are worked on
+    c2<T> next[4], cur[4];
 #pragma unroll
-        for (int a = 0; a < kRMax; ++a)
-            if (a < r1) fma_c(d, u[a], v[a]);
-        const long o = (long)k * plane + p;
-        y[o] = d * x[o];
+    for (int q = 0; q < 4; ++q) next[q] = xr[(long)min(q, nr - 1) * n1];
+    for (int q0 = 0; q0 < nr; q0 += 4) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            cur[q] = next[q];
+            next[q] = xr[(long)min(q0 + 4 + q, nr - 1) * n1];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q0 + q >= nr) break;
+            c2<T> d = mk<T>(0, 0);
+#pragma unroll
+            for (int a = 0; a < R; ++a) fma_c(d, u[a], v[(q0 + q) * R + a]);
+            if (i < n1) yr[(long)(q0 + q) * n1] = d * cur[q];
+        }
     }
+}
+
+template <typename T, int R>
+void launch_apply(int r, const c2<T>* V, const c2<T>* U1T, const c2<T>* x, c2<T>* y, const int n[3], hipStream_t s)
+{
+    if constexpr (R > 1) {
+        if (r < R) return launch_apply<T, R - 1>(r, V, U1T, x, y, n, s);
+    }
+    const long rows = (long)n[1] * n[2];
+    hipLaunchKernelGGL((k_apply<T, R>), dim3((unsigned)((rows + kRun - 1) / kRun), (n[0] + kNT - 1) / kNT), dim3(kNT), 0,
+                       s, V, U1T, x, y, n[0], rows);
 }
 
 template <typename T>
@@ -113,25 +127,20 @@ hipError_t run(const int n[3], const int r[3], int cp, const void* core, const v
 {
     const c2<T>* G = (const c2<T>*)core;
     c2<T>* U1T = (c2<T>*)ws;
-    c2<T>* W = U1T + (size_t)n[0] * r[0];
-    c2<T>* V = W + (cp ? 0 : (size_t)n[2] * r[0] * r[1]);
+    c2<T>* V = U1T + (size_t)n[0] * r[0];
     hipLaunchKernelGGL((k_transpose<T>), dim3((unsigned)(((long)n[0] * r[0] + 255) / 256)), dim3(256), 0, s,
                        (const c2<T>*)u1, U1T, n[0], r[0]);
-    const long nv = (long)n[2] * n[1] * r[0];
-    const dim3 gv((unsigned)((nv + 255) / 256));
     if (cp) {
-        hipLaunchKernelGGL((k_vjk<T, true>), gv, dim3(256), 0, s, nullptr, G, (const c2<T>*)u2, (const c2<T>*)u3, V,
-                           n[1], n[2], r[0], r[1], r[2]);
+        const long nv = (long)n[2] * n[1] * r[0];
+        hipLaunchKernelGGL((k_vjk_cp<T>), dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, G, (const c2<T>*)u2,
+                           (const c2<T>*)u3, V, n[1], n[2], r[0]);
     } else {
-        dim3 gz((r[0] * r[1] + 255) / 256, n[2]);
-        hipLaunchKernelGGL((k_core_z<T>), gz, dim3(256), 0, s, G, (const c2<T>*)u3, r[0], r[1], r[2], W);
-        hipLaunchKernelGGL((k_vjk<T, false>), gv, dim3(256), 0, s, (const c2<T>*)W, nullptr, (const c2<T>*)u2,
-                           (const c2<T>*)u3, V, n[1], n[2], r[0], r[1], r[2]);
+        const size_t lds = v_rows_lds<T>(kRMax, r[0]);
+        (void)hipFuncSetAttribute((const void*)k_vk<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        hipLaunchKernelGGL((k_vk<T>), dim3(n[2]), dim3(kVNT), lds, s, G, (const c2<T>*)u2, (const c2<T>*)u3, V, n[1],
+                           r[0], r[1], r[2]);
     }
-    const long plane = (long)n[0] * n[1];
-    dim3 grid((unsigned)((plane + kNT - 1) / kNT), (n[2] + kKT - 1) / kKT);
-    hipLaunchKernelGGL((k_apply<T>), grid, dim3(kNT), 0, s, (const c2<T>*)V, (const c2<T>*)U1T, (const c2<T>*)x,
-                       (c2<T>*)y, n[0], n[1], n[2], r[0]);
+    launch_apply<T, kRMax>(r[0], V, U1T, (const c2<T>*)x, (c2<T>*)y, n, s);
     return hipGetLastError();
 }
 

@@ -42,11 +42,12 @@ __device__ __forceinline__ void v_rows_sums(const c2<T> (&u)[16], const c2<T>* W
 }
 
 // out[k1 rs + g] for k1 in [0, n1p1), zero for g in [r3, rs); cp: a
-// superdiagonal core.  rmax: as given to v_rows_lds.
+// superdiagonal core.  rmax: as given to v_rows_lds.  g1, g2, g3: strides of
+// the core along the contracted x rank, the contracted y rank and g.
 template <typename T>
 __device__ __forceinline__ void v_rows(const c2<T>* G, const c2<T>* U1, const c2<T>* U2, int r1, int r2, int r3,
-                                       int n1p1, int rmax, int rs, bool cp,
-                                       c2<T>* __restrict__ out)
+                                       int g1, int g2, int g3, int n1p1, int rmax,
+                                       int rs, bool cp, c2<T>* __restrict__ out)
 {
     extern __shared__ __align__(16) unsigned char v_smem[];
     const int row = v_rows_row(rmax, rs), wrow = v_rows_pad(r1);
@@ -67,13 +68,13 @@ __device__ __forceinline__ void v_rows(const c2<T>* G, const c2<T>* U1, const c2
         const int al = e / r3, ga = e - al * r3;
         c2<T> acc = mk<T>(0, 0);
         if (al < r1) {
-            const c2<T>* g = G + (long)al * r2 * r3 + ga;
+            const c2<T>* g = G + (long)al * g1 + (long)ga * g3;
             for (int b0 = 0; b0 < r2; b0 += 16) {
                 c2<T> gv[16], uv[16];
 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
                     const int b = min(b0 + q, r2 - 1);
-                    gv[q] = ldg(g + (long)b * r3);
+                    gv[q] = ldg(g + (long)b * g2);
                     uv[q] = ldg(U2 + b);
                 }
 #pragma unroll
