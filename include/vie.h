@@ -320,9 +320,10 @@ vie_status vie_compress_pwl_k(const int n[3], const double* green_pwl_k, const v
 vie_status vie_pwl_op_query(const vie_pwl_op* op, int n[3], int ranks[10][6][3]);
 
 /* DEVICE workspace of vie_matvec_pwl in bytes for nrhs vectors: their 12
- * padded components through the five passes and the core products
- * W_c(k2) = G_c x2 U2_c(k2, :) of the sixty (K: thirty) components for k2 in
- * [0, n2] (shared by the vectors) */
+ * padded components through the five passes; the rows
+ * V_c(k1, k2, :) = U1_c(k1, :) (G_c x2 U2_c(k2, :)) of the sixty (K: thirty)
+ * components, shared by the vectors, take the place of the first
+ * intermediate, which grows to hold them where the z ranks come near 0.4 n3 */
 size_t vie_pwl_workspace_bytes(const vie_pwl_op* op, int dtype, int nrhs);
 
 /*
@@ -401,8 +402,10 @@ vie_status vie_op_densify(vie_op* op, int with_c128);
 /* Select VIE_NHAT_TUCKER or VIE_NHAT_DENSE for subsequent matvecs. */
 vie_status vie_op_set_nhat(vie_op* op, int source);
 
-/* Device workspace (bytes) that vie_matvec / vie_matvec_adjoint need for
- * `nrhs` right-hand sides at precision `dtype` (18 n1 n2 n3 complex per rhs). */
+/* Device workspace (bytes) of vie_matvec / vie_matvec_adjoint for `nrhs`
+ * right-hand sides at precision `dtype`: 18 n1 n2 n3 complex per rhs, which
+ * is also the least they accept, and more where the z rank comes near n3 (the
+ * z pass then takes such a grid in one piece instead of several). */
 size_t vie_workspace_bytes(const vie_op* op, int dtype, int nrhs);
 
 /*

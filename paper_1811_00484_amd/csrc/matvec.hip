@@ -542,14 +542,14 @@ static int tile_width(size_t max_lds, int L)
     return W;
 }
 
+static size_t s2_elems(const OpView& v, int nrhs) { return (size_t)3 * v.L[1] * v.L[0] * v.n[2] * (size_t)nrhs; }
+static size_t s1_elems(const OpView& v, int nrhs) { return (size_t)3 * v.n[2] * v.L[0] * v.n[1] * (size_t)nrhs; }
+
+size_t matvec_ws_least(const DeviceOp& op, int nrhs) { return s2_elems(op.view, nrhs) + s1_elems(op.view, nrhs); }
+
 size_t matvec_ws_elems(const DeviceOp& op, int nrhs)
 {
-    const OpView& v = op.view;
-    size_t s2 = (size_t)3 * v.L[1] * v.L[0] * v.n[2];
-    size_t s1 = (size_t)3 * v.n[2] * v.L[0] * v.n[1];
-    // S1 also holds the z pass's V tables (larger than S1 only on grids whose
-    // z rank reaches n3)
-    return s2 * (size_t)nrhs + std::max(s1 * (size_t)nrhs, zv_elems(v));
+    return s2_elems(op.view, nrhs) + std::max(s1_elems(op.view, nrhs), zv_elems(op.view));
 }
 
 template <typename T>
@@ -575,13 +575,13 @@ static size_t z_lds_bytes(const OpView& v, int G)
 // (out), 4 reads S3 (in) and writes y (out).  ident (passes 0 and 4 only):
 // the transform is replaced by the identity, so only the pass's index maps
 // (padding, transposes, cropping; pass 4 with the bare epilogue) remain.
-// zv: scratch of zv_elems() for pass 2's V tables; without it (a caller that
-// has none, vie_debug_pass under stream capture) the z pass of the lengths
-// without a register-FFT kernel contracts the cores in every workgroup.
+// zv: scratch of zv_cap elements for pass 2's V rows; without room for one
+// k2's (no scratch: vie_debug_pass under stream capture; grids of a few
+// voxels) the z pass contracts the cores in every workgroup.
 template <typename TV, typename T>
 hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<TV>* eps, const c2<TV>* x,
                     const void* in, void* out, int nrhs, hipStream_t s, const int* rhs_map, std::string& err,
-                    bool ident, c2<T>* zv)
+                    bool ident, c2<T>* zv, size_t zv_cap)
 {
     const OpView& v = op.view;
     const int n1 = v.n[0], n2 = v.n[1], n3 = v.n[2];
@@ -627,13 +627,13 @@ hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<
             err = "dense spectrum not materialised";
             return hipErrorInvalidValue;
         }
-        if (allow_fast && zv && z_pass_fast<T>(op, mode, recon, nrhs, S2, zv, tw[2], fac, dense, s))
+        if (allow_fast && zv && z_pass_fast<T>(op, mode, recon, nrhs, S2, zv, zv_cap, tw[2], fac, dense, s))
             return hipGetLastError();
         if (recon == 1) {
             err = "BF16 z pass could not be launched";
             return hipErrorInvalidValue;
         }
-        if (zv && z_pass_mix<T>(op, mode, nrhs, S2, zv, s)) return hipGetLastError();
+        if (zv && z_pass_mix<T>(op, mode, nrhs, S2, zv, zv_cap, s)) return hipGetLastError();
         int G = 4;
         while (G > 1 && z_lds_bytes<T>(v, G) > op.max_lds) G /= 2;
         size_t lds = z_lds_bytes<T>(v, G);
@@ -655,12 +655,12 @@ hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<
 
 template <typename TV, typename T>
 hipError_t launch_matvec(const DeviceOp& op, int mode, int recon, const c2<TV>* eps, const c2<TV>* x,
-                         c2<TV>* y, int nrhs, c2<T>* ws, hipStream_t s, const int* rhs_map,
+                         c2<TV>* y, int nrhs, c2<T>* ws, size_t ws_elems, hipStream_t s, const int* rhs_map,
                          std::string& err)
 {
-    const OpView& v = op.view;
+    const size_t s2 = s2_elems(op.view, nrhs);
     c2<T>* S2 = ws;
-    c2<T>* S1 = ws + (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nrhs;
+    c2<T>* S1 = ws + s2;
     if (recon == 1 && (sizeof(T) != 4 || g_kernel_path != 0 || !bf16_recon_available(op))) {
         err = "BF16 reconstruction needs complex64, the register-FFT z pass (2 n3 = 128, 256 or 512) "
               "and z ranks <= 32";
@@ -671,7 +671,8 @@ hipError_t launch_matvec(const DeviceOp& op, int mode, int recon, const c2<TV>* 
     void* const outs[5] = {S1, S2, S2, S1, y};
     for (int p = 0; p < 5; ++p) {
         // S1 is dead between Y+ and Y-: the z pass's V tables take its place
-        hipError_t e = run_pass<TV, T>(op, p, mode, recon, eps, x, ins[p], outs[p], nrhs, s, rhs_map, err, false, S1);
+        hipError_t e = run_pass<TV, T>(op, p, mode, recon, eps, x, ins[p], outs[p], nrhs, s, rhs_map, err, false, S1,
+                                       ws_elems - s2);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -679,22 +680,22 @@ hipError_t launch_matvec(const DeviceOp& op, int mode, int recon, const c2<TV>* 
 
 template hipError_t run_pass<float, float>(const DeviceOp&, int, int, int, const c2<float>*, const c2<float>*,
                                            const void*, void*, int, hipStream_t, const int*, std::string&, bool,
-                                           c2<float>*);
+                                           c2<float>*, size_t);
 template hipError_t run_pass<double, double>(const DeviceOp&, int, int, int, const c2<double>*, const c2<double>*,
                                              const void*, void*, int, hipStream_t, const int*, std::string&, bool,
-                                             c2<double>*);
+                                             c2<double>*, size_t);
 template hipError_t run_pass<double, float>(const DeviceOp&, int, int, int, const c2<double>*, const c2<double>*,
                                             const void*, void*, int, hipStream_t, const int*, std::string&, bool,
-                                            c2<float>*);
+                                            c2<float>*, size_t);
 
 template hipError_t launch_matvec<float, float>(const DeviceOp&, int, int, const c2<float>*, const c2<float>*,
-                                                c2<float>*, int, c2<float>*, hipStream_t, const int*,
+                                                c2<float>*, int, c2<float>*, size_t, hipStream_t, const int*,
                                                 std::string&);
 template hipError_t launch_matvec<double, double>(const DeviceOp&, int, int, const c2<double>*,
-                                                  const c2<double>*, c2<double>*, int, c2<double>*, hipStream_t,
+                                                  const c2<double>*, c2<double>*, int, c2<double>*, size_t, hipStream_t,
                                                   const int*, std::string&);
 template hipError_t launch_matvec<double, float>(const DeviceOp&, int, int, const c2<double>*,
-                                                 const c2<double>*, c2<double>*, int, c2<float>*, hipStream_t,
+                                                 const c2<double>*, c2<double>*, int, c2<float>*, size_t, hipStream_t,
                                                  const int*, std::string&);
 
 // ----------------------- multi-instance launcher ------------------------
@@ -966,7 +967,7 @@ static hipError_t launch_batch_grouped(const std::vector<InstHost>& req, int mod
                     z.S2 = S2;
                     // S1 is dead between Y+ and Y-: it holds the V rows
                     z.V = S1;
-                    if (op.nhat_source != 1) launch_zv<T>(op, S1, s);
+                    if (op.nhat_source != 1) launch_zv<T>(op, S1, 0, v.n[1] + 1, s);
                     if constexpr (sizeof(T) == 8) {
                         z.fac = op.d64.fac;
                         z.dense = op.dense64;
@@ -979,7 +980,9 @@ static hipError_t launch_batch_grouped(const std::vector<InstHost>& req, int mod
                     z.za.conj = conj;
                     z.za.dense = op.nhat_source == 1;
                     z.za.rs = zv_stride(v);
-                    z_fast_shape(op, h.nact, sizeof(c2<T>), z.za.chunk, z.nbx, z.gy);
+                    z.za.k20 = 0;
+                    z.za.k2n = v.n[1] + 1;
+                    z_fast_shape(op, h.nact, sizeof(c2<T>), z.za.k2n, z.za.chunk, z.nbx, z.gy);
                     z.nrhs = h.nact;
                     z.off = off;
                     off += z.nbx * z.gy;
@@ -1022,7 +1025,8 @@ hipError_t launch_batch(const std::vector<InstHost>& req, int mode, int recon, I
     if (req.size() == 1 || g_batch_mode == 0) {
         for (const InstHost& h : req) {
             hipError_t e = launch_matvec<TV, T>(*h.op, mode, recon, (const c2<TV>*)h.eps, (const c2<TV>*)h.x,
-                                                (c2<TV>*)h.y, h.nact, (c2<T>*)h.ws, st, h.map, err);
+                                                (c2<TV>*)h.y, h.nact, (c2<T>*)h.ws, matvec_ws_elems(*h.op, h.nact), st, h.map,
+                                                err);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;

@@ -27,6 +27,8 @@
 // bound it at three wavefronts a SIMD.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "reg_fft.h"
 #include "vie_internal.h"
 
@@ -657,7 +659,7 @@ constexpr bool z_shared_table()
 // REC: 0 = N^ tables in T (complex64: on MFMA), 1 = BF16 z factors on MFMA
 // (T = float), 2 = a K operator (antisymmetric product, K parities; tables
 // on the vector ALUs).
-// One workgroup of the z pass: bx = canonical k2 + (n2 + 1) * chunk index,
+// One workgroup of the z pass: bx = canonical k2 - k20 + k2n * chunk index,
 // right-hand sides b, b + bstep, .. below nrhs.
 template <typename T, int L3, bool CONJ, int REC>
 __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __restrict__ tw, const ZFastArgs& a,
@@ -698,8 +700,8 @@ __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __re
     c2<T>* slice = X + pe * P;
     Plan::fill_tw(tws, tw, tid, NT);
 
-    const int k2 = bx % (n2 + 1);
-    const int k1b = (bx / (n2 + 1)) * a.chunk;
+    const int k2l = bx % a.k2n, k2 = a.k20 + k2l;
+    const int k1b = (bx / a.k2n) * a.chunk;
     const int k1e = min(n1 + 1, k1b + a.chunk);
     const bool m2 = k2 > 0 && k2 < n2;
     const int pk2 = s2 ? L2 - k2 : k2;
@@ -723,7 +725,7 @@ __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __re
                 const int qd = e / (NC * rs), rem = e - qd * NC * rs;
                 const int c = rem / rs, g = rem - c * rs;
                 Vc[(qd * 6 + 6 - NC + c) * rs + g] =
-                    (qd == 0 || hasB) ? V[(((long)k2 * NC + c) * (n1 + 1) + kA + qd) * rs + g] : mk<T>(0, 0);
+                    (qd == 0 || hasB) ? V[(((long)k2l * NC + c) * (n1 + 1) + kA + qd) * rs + g] : mk<T>(0, 0);
             }
         }
         __syncthreads();   // V rows, twiddles; the tables' previous readers are done
@@ -751,10 +753,14 @@ __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __re
 #pragma unroll
                     for (int q = 0; q < 8; ++q) uv[q] = U3[(long)min(g0 + q, r3 - 1) * (N3 + 1)];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) {   // (V rows are zero beyond r3)
-                        fma_c(accA, va[g0 + q], uv[q]);
-                        fma_c(accB, vb[g0 + q], uv[q]);
-                    }
+                    for (int h = 0; h < 8; h += 4)
+                        if (g0 + h < r3) {
+#pragma unroll
+                            for (int q = h; q < h + 4; ++q) {   // (V rows are zero beyond r3)
+                                fma_c(accA, va[g0 + q], uv[q]);
+                                fma_c(accB, vb[g0 + q], uv[q]);
+                            }
+                        }
                 }
                 NTA[c * (N3 + 1) + kk] = accA;
                 NTB[c * (N3 + 1) + kk] = accB;
@@ -924,15 +930,15 @@ static size_t zfast_lds(int rs)
                             12 * rs + RegPlan<L3>::TW);
 }
 
-void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int& chunk, int& nbx, int& gy)
+void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int k2n, int& chunk, int& nbx, int& gy)
 {
     const OpView& v = op.view;
-    const int n1p1 = v.n[0] + 1, n2p1 = v.n[1] + 1;
+    const int n1p1 = v.n[0] + 1;
     // a chunk only saves twiddle fills: halve it until the grid holds sixteen
     // workgroups per CU (the autotuned length is the limit)
     chunk = op.zchunk;
-    while (chunk > 2 && (long)n2p1 * ((n1p1 + chunk - 1) / chunk) < 4096) chunk /= 2;
-    nbx = n2p1 * ((n1p1 + chunk - 1) / chunk);
+    while (chunk > 2 && (long)k2n * ((n1p1 + chunk - 1) / chunk) < 4096) chunk /= 2;
+    nbx = k2n * ((n1p1 + chunk - 1) / chunk);
     // right-hand sides share a workgroup's tables as far as the grid holds
     // eight workgroups per CU
     gy = 1;
@@ -941,8 +947,8 @@ void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int& chunk, int&
 }
 
 template <typename T, int L3>
-static hipError_t launch_z(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, const c2<T>* tw,
-                           const c2<T>* V, const c2<T>* fac, const c2<T>* dense, hipStream_t s)
+static hipError_t launch_z(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, const c2<T>* tw, c2<T>* V,
+                           int slab, const c2<T>* fac, const c2<T>* dense, hipStream_t s)
 {
     const OpView& v = op.view;
     ZFastArgs za;
@@ -950,8 +956,6 @@ static hipError_t launch_z(const DeviceOp& op, int mode, int recon, int nrhs, c2
     za.conj = (mode == MODE_AH || mode == MODE_NH);
     za.dense = op.nhat_source == 1;
     za.rs = zv_stride(v);
-    int nbx, gy;
-    z_fast_shape(op, nrhs, sizeof(c2<T>), za.chunk, nbx, gy);
     size_t lds = zfast_lds<T, L3>(za.rs);
     if (lds > op.max_lds) return hipErrorInvalidValue;
     auto kern = za.conj ? k_z_fast<T, L3, true, 0> : k_z_fast<T, L3, false, 0>;
@@ -960,8 +964,15 @@ static hipError_t launch_z(const DeviceOp& op, int mode, int recon, int nrhs, c2
     }
     if (v.fam == 1) kern = k_z_fast<T, L3, false, 2>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kern, dim3(nbx, gy), dim3(4 * (L3 / 8)), lds, s, S2, tw, za, V, fac, dense,
-                       (const unsigned short*)op.b16.fac3m, nrhs);
+    const int n2p1 = v.n[1] + 1;
+    for (za.k20 = 0; za.k20 < n2p1; za.k20 += slab) {
+        za.k2n = std::min(slab, n2p1 - za.k20);
+        if (!za.dense) launch_zv<T>(op, V, za.k20, za.k2n, s);
+        int nbx, gy;
+        z_fast_shape(op, nrhs, sizeof(c2<T>), za.k2n, za.chunk, nbx, gy);
+        hipLaunchKernelGGL(kern, dim3(nbx, gy), dim3(4 * (L3 / 8)), lds, s, S2, tw, za, (const c2<T>*)V, fac, dense,
+                           (const unsigned short*)op.b16.fac3m, nrhs);
+    }
     return hipGetLastError();
 }
 
@@ -1025,14 +1036,15 @@ bool bf16_recon_available(const DeviceOp& op)
 }
 
 template <typename T>
-bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, c2<T>* V, const c2<T>* tw,
-                 const c2<T>* fac, const c2<T>* dense, hipStream_t s)
+bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, c2<T>* V, size_t vcap,
+                 const c2<T>* tw, const c2<T>* fac, const c2<T>* dense, hipStream_t s)
 {
     const OpView& v = op.view;
     // K operators: forward product only (the API rejects the others)
     if (v.fam != 0 && (mode == MODE_AH || mode == MODE_NH || recon == 1)) return false;
     if (recon == 1 && (sizeof(T) != 4 || !bf16_recon_available(op))) return false;
-    const int rs = zv_stride(v);
+    const int rs = zv_stride(v), slab = op.nhat_source == 1 ? v.n[1] + 1 : zv_slab(v, vcap);
+    if (slab < 1) return false;
     switch (v.L[2]) {
     case 512:
         if (zfast_lds<T, 512>(rs) > op.max_lds) return false;
@@ -1045,11 +1057,10 @@ bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, c
         break;
     default: return false;
     }
-    if (op.nhat_source != 1) launch_zv<T>(op, V, s);
     switch (v.L[2]) {
-    case 512: return launch_z<T, 512>(op, mode, recon, nrhs, S2, tw, V, fac, dense, s) == hipSuccess;
-    case 256: return launch_z<T, 256>(op, mode, recon, nrhs, S2, tw, V, fac, dense, s) == hipSuccess;
-    default: return launch_z<T, 128>(op, mode, recon, nrhs, S2, tw, V, fac, dense, s) == hipSuccess;
+    case 512: return launch_z<T, 512>(op, mode, recon, nrhs, S2, tw, V, slab, fac, dense, s) == hipSuccess;
+    case 256: return launch_z<T, 256>(op, mode, recon, nrhs, S2, tw, V, slab, fac, dense, s) == hipSuccess;
+    default: return launch_z<T, 128>(op, mode, recon, nrhs, S2, tw, V, slab, fac, dense, s) == hipSuccess;
     }
 }
 
@@ -1154,9 +1165,9 @@ template bool z_group_fast<double>(int, int, int, int, size_t, const ZGroup&, in
 VIE_XYF_INST(float, float)
 VIE_XYF_INST(double, double)
 VIE_XYF_INST(double, float)
-template bool z_pass_fast<float>(const DeviceOp&, int, int, int, c2<float>*, c2<float>*, const c2<float>*,
+template bool z_pass_fast<float>(const DeviceOp&, int, int, int, c2<float>*, c2<float>*, size_t, const c2<float>*,
                                  const c2<float>*, const c2<float>*, hipStream_t);
-template bool z_pass_fast<double>(const DeviceOp&, int, int, int, c2<double>*, c2<double>*, const c2<double>*,
+template bool z_pass_fast<double>(const DeviceOp&, int, int, int, c2<double>*, c2<double>*, size_t, const c2<double>*,
                                   const c2<double>*, const c2<double>*, hipStream_t);
 
 }  // namespace vie

@@ -28,6 +28,8 @@
 // index instructions, on large grids the traffic of the five passes.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "mix_fft.h"
 #include "v_rows.h"
 #include "vie_internal.h"
@@ -389,23 +391,23 @@ bool xy_pass_mix(const DeviceOp& op, int kind, const void* in, void* out, const 
 // ---------------------------------------------------------------------------
 // V tables: V[((k2 nc + c) (n1 + 1) + k1) rs + g], c the stored components (six,
 // or K's three), zero for g beyond the component's z rank (rs: the largest one
-// in whole batches of eight, so that the z pass reads and sums without a
+// in whole fours, so that the z pass reads and sums four at a time without a
 // branch).  One workgroup per (k2, c).
 template <typename T>
 __global__ void __launch_bounds__(kVNT) k_zv(OpView v, const c2<T>* __restrict__ core, const c2<T>* __restrict__ fac,
-                                             int rs, c2<T>* __restrict__ V)
+                                             int rs, int k20, c2<T>* __restrict__ V)
 {
-    const int k2 = blockIdx.x, nc = gridDim.y, ci = blockIdx.y, c = 6 - nc + ci;
+    const int k2 = k20 + blockIdx.x, nc = gridDim.y, ci = blockIdx.y, c = 6 - nc + ci;
     const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
     v_rows<T>(core + v.core_off[c], fac + v.fac_off[c][0], fac + v.fac_off[c][1] + (long)k2 * r2, v.r[c][0], r2,
-              v.r[c][2], r2 * v.r[c][2], v.r[c][2], 1, n1p1, v.rmax, rs, v.cp, V + ((long)k2 * nc + ci) * n1p1 * rs);
+              v.r[c][2], r2 * v.r[c][2], v.r[c][2], 1, n1p1, v.rmax, rs, v.cp, V + ((long)blockIdx.x * nc + ci) * n1p1 * rs);
 }
 
 int zv_stride(const OpView& v)
 {
     int rs = 1;
     for (int c = v.fam ? 3 : 0; c < 6; ++c) rs = rs > v.r[c][2] ? rs : v.r[c][2];
-    return (rs + 7) & ~7;
+    return (rs + 3) & ~3;
 }
 
 size_t zv_elems(const OpView& v)
@@ -413,8 +415,14 @@ size_t zv_elems(const OpView& v)
     return (size_t)(v.n[0] + 1) * (v.n[1] + 1) * (v.fam ? 3 : 6) * zv_stride(v);
 }
 
+int zv_slab(const OpView& v, size_t cap)
+{
+    const size_t per = (size_t)(v.n[0] + 1) * (v.fam ? 3 : 6) * zv_stride(v);
+    return (int)std::min<size_t>(cap / per, v.n[1] + 1);
+}
+
 template <typename T>
-void launch_zv(const DeviceOp& op, c2<T>* V, hipStream_t s)
+void launch_zv(const DeviceOp& op, c2<T>* V, int k20, int k2n, hipStream_t s)
 {
     const OpView& v = op.view;
     const c2<T>*core, *fac;
@@ -428,7 +436,7 @@ void launch_zv(const DeviceOp& op, c2<T>* V, hipStream_t s)
     const int rs = zv_stride(v);
     const size_t lds = v_rows_lds<T>(v.rmax, rs);
     (void)hipFuncSetAttribute((const void*)k_zv<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(k_zv<T>, dim3(v.n[1] + 1, v.fam ? 3 : 6), dim3(kVNT), lds, s, v, core, fac, rs, V);
+    hipLaunchKernelGGL(k_zv<T>, dim3(k2n, v.fam ? 3 : 6), dim3(kVNT), lds, s, v, core, fac, rs, k20, V);
 }
 
 // ---------------------------------------------------------------------------
@@ -441,6 +449,7 @@ struct MixZArgs {
     int conj;
     int dense;
     int rs;         // V stride per component
+    int k20, k2n;   // canonical k2 of this launch: [k20, k20 + k2n)
     int r3[6];
     int fac3t_off[6];
 };
@@ -586,10 +595,10 @@ __global__ void __launch_bounds__(512) k_mix_z(c2<T>* __restrict__ S2, const c2<
     // workgroups go round robin over the eight XCDs: give each XCD a run of
     // neighbouring quads, whose pencils share cache lines and z factors
     const int nx = (n1 + 1 + a.nq - 1) / a.nq;
-    const int per = (nx * (n2 + 1) + 7) / 8;
+    const int per = (nx * a.k2n + 7) / 8;
     const int g = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || g >= nx * (n2 + 1)) return;
-    const int kA = (g % nx) * a.nq, k2 = g / nx;
+    if ((int)(blockIdx.x >> 3) >= per || g >= nx * a.k2n) return;
+    const int kA = (g % nx) * a.nq, k2l = g / nx, k2 = a.k20 + k2l;
     const int nq = min(a.nq, n1 + 1 - kA);
     for (int m = tid; m < p.L; m += nt) tws[m] = tw[m];
 
@@ -611,7 +620,7 @@ __global__ void __launch_bounds__(512) k_mix_z(c2<T>* __restrict__ S2, const c2<
             continue;
         }
         const c2<T>* U3 = fac + a.fac3t_off[cc] + k3;
-        const c2<T>* va = V + (((long)k2 * NC + c) * (n1 + 1) + kA) * a.rs;
+        const c2<T>* va = V + (((long)k2l * NC + c) * (n1 + 1) + kA) * a.rs;
         const c2<T>* vb = nq > 1 ? va + a.rs : va;
         c2<T> s0 = mk<T>(0, 0), s1 = mk<T>(0, 0), u[8], w[8];
         // sixteen z factors in flight; rows beyond the rank meet zeros of V
@@ -621,10 +630,14 @@ __global__ void __launch_bounds__(512) k_mix_z(c2<T>* __restrict__ S2, const c2<
         };
         auto sum = [&](const c2<T>(&d)[8], int g0) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                fma_c(s0, va[g0 + q], d[q]);
-                fma_c(s1, vb[g0 + q], d[q]);
-            }
+            for (int h = 0; h < 8; h += 4)
+                if (g0 + h < r3) {
+#pragma unroll
+                    for (int q = h; q < h + 4; ++q) {
+                        fma_c(s0, va[g0 + q], d[q]);
+                        fma_c(s1, vb[g0 + q], d[q]);
+                    }
+                }
         };
         factors(u, 0);
         for (int g0 = 0; g0 < r3; g0 += 16) {
@@ -690,7 +703,7 @@ __global__ void __launch_bounds__(512) k_mix_z(c2<T>* __restrict__ S2, const c2<
 }
 
 template <typename T>
-bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hipStream_t s)
+bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, size_t vcap, hipStream_t s)
 {
     const OpView& v = op.view;
     const c2<T>*tw, *fac, *dense;
@@ -726,18 +739,23 @@ bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hip
     a.nq = (long)(v.n[0] + 1) * (v.n[1] + 1) >= 1024 && lds_of(2) <= op.max_lds / 2 ? 2 : 1;
     const size_t lds = lds_of(a.nq);
     if (lds > op.max_lds) return false;
-    if (!a.dense) launch_zv<T>(op, V, s);
-    const int nblk = 8 * (((v.n[0] + a.nq) / a.nq * (v.n[1] + 1) + 7) / 8);
-    // right-hand sides share the tables of a workgroup as far as the grid
-    // still holds eight workgroups per CU
-    int gy = 1;
-    while (gy < nrhs && (long)nblk * gy < 2048) ++gy;
+    const int n2p1 = v.n[1] + 1, slab = a.dense ? n2p1 : zv_slab(v, vcap);
+    if (slab < 1) return false;
     const int groups = 4 * (p.L / p.rl);
     int nt = 64 * ((groups + 63) / 64);
     nt = nt < 64 ? 64 : (nt > 512 ? 512 : nt);
     auto kern = v.fam ? k_mix_z<T, 1> : k_mix_z<T, 0>;
     (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kern, dim3(nblk, gy), dim3(nt), lds, s, S2, tw, a, p, (const c2<T>*)V, fac, dense);
+    for (a.k20 = 0; a.k20 < n2p1; a.k20 += slab) {
+        a.k2n = std::min(slab, n2p1 - a.k20);
+        if (!a.dense) launch_zv<T>(op, V, a.k20, a.k2n, s);
+        const int nblk = 8 * (((v.n[0] + a.nq) / a.nq * a.k2n + 7) / 8);
+        // right-hand sides share the tables of a workgroup as far as the grid
+        // still holds eight workgroups per CU
+        int gy = 1;
+        while (gy < nrhs && (long)nblk * gy < 2048) ++gy;
+        hipLaunchKernelGGL(kern, dim3(nblk, gy), dim3(nt), lds, s, S2, tw, a, p, (const c2<T>*)V, fac, dense);
+    }
     return true;
 }
 
@@ -747,9 +765,9 @@ bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hip
 VIE_MIX_INST(float, float)
 VIE_MIX_INST(double, double)
 VIE_MIX_INST(double, float)
-template void launch_zv<float>(const DeviceOp&, c2<float>*, hipStream_t);
-template void launch_zv<double>(const DeviceOp&, c2<double>*, hipStream_t);
-template bool z_pass_mix<float>(const DeviceOp&, int, int, c2<float>*, c2<float>*, hipStream_t);
-template bool z_pass_mix<double>(const DeviceOp&, int, int, c2<double>*, c2<double>*, hipStream_t);
+template void launch_zv<float>(const DeviceOp&, c2<float>*, int, int, hipStream_t);
+template void launch_zv<double>(const DeviceOp&, c2<double>*, int, int, hipStream_t);
+template bool z_pass_mix<float>(const DeviceOp&, int, int, c2<float>*, c2<float>*, size_t, hipStream_t);
+template bool z_pass_mix<double>(const DeviceOp&, int, int, c2<double>*, c2<double>*, size_t, hipStream_t);
 
 }  // namespace vie

@@ -63,7 +63,7 @@ vie_status vie_matvec_noalloc(const vie_op* op, int kind, int adjoint, int dtype
     // per-pass profiling records its own events, which this entry point does not create
     if (prof_is_enabled())
         return fail(VIE_E_UNSUPPORTED, "vie_matvec_noalloc: not available while per-pass profiling is on");
-    const size_t need = vie_workspace_bytes(op, dtype, nrhs);
+    const size_t need = matvec_ws_least(op->d, nrhs) * (dtype == VIE_C128 ? 16 : 8);
     if (need == 0 || need > kScratchBytes)
         return fail(VIE_E_ARG, "vie_matvec_noalloc: needs " + std::to_string(need) +
                                    " workspace bytes, above the fixed scratch of " +

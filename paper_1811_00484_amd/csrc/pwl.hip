@@ -699,11 +699,11 @@ hipError_t pwl_matvec(const vie_pwl_op& P, int mode, const c2<TV>* eps, const c2
     c2<T>* S1 = ws + (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nb;
     const bool conj = (mode == MODE_AH || mode == MODE_NH);
     // X+ : x -> S1, Y+ : S1 -> S2, Z : S2 in place, Y- : S2 -> S1, X- : S1 -> y
-    hipError_t e = run_pass<TV, T>(op, 0, mode, 0, eps, x, nullptr, S1, nb, s, nullptr, err, false, nullptr);
-    if (e == hipSuccess) e = run_pass<TV, T>(op, 1, mode, 0, eps, x, S1, S2, nb, s, nullptr, err, false, nullptr);
+    hipError_t e = run_pass<TV, T>(op, 0, mode, 0, eps, x, nullptr, S1, nb, s, nullptr, err, false, nullptr, 0);
+    if (e == hipSuccess) e = run_pass<TV, T>(op, 1, mode, 0, eps, x, S1, S2, nb, s, nullptr, err, false, nullptr, 0);
     if (e == hipSuccess) e = launch_pwl_z<T>(P, conj ? 1 : 0, S2, S1, nrhs, s, err);
-    if (e == hipSuccess) e = run_pass<TV, T>(op, 3, mode, 0, eps, x, S2, S1, nb, s, nullptr, err, false, nullptr);
-    if (e == hipSuccess) e = run_pass<TV, T>(op, 4, mode, 0, eps, x, S1, y, nb, s, nullptr, err, false, nullptr);
+    if (e == hipSuccess) e = run_pass<TV, T>(op, 3, mode, 0, eps, x, S2, S1, nb, s, nullptr, err, false, nullptr, 0);
+    if (e == hipSuccess) e = run_pass<TV, T>(op, 4, mode, 0, eps, x, S1, y, nb, s, nullptr, err, false, nullptr, 0);
     return e;
 }
 

@@ -788,8 +788,8 @@ vie_status matvec_common(const vie_op* op, int mode, int dtype, int recon, const
         return fail(VIE_E_UNSUPPORTED, "vie_matvec: FP64 reconstruction needs VIE_C128");
     if (dtype == VIE_C128 && (recon == VIE_RECON_FP32 || recon == VIE_RECON_BF16))
         return fail(VIE_E_UNSUPPORTED, "vie_matvec: reduced reconstruction needs VIE_C64");
-    size_t need = vie_workspace_bytes(op, dtype, nrhs);
-    if (ws_bytes < need) return fail(VIE_E_ARG, "vie_matvec: workspace too small");
+    const size_t el = dtype == VIE_C128 ? sizeof(c2<double>) : sizeof(c2<float>);
+    if (ws_bytes < matvec_ws_least(op->d, nrhs) * el) return fail(VIE_E_ARG, "vie_matvec: workspace too small");
     const OpView& v = op->d.view;
     size_t vbytes = (size_t)nrhs * 3 * v.n[0] * v.n[1] * v.n[2] * (dtype == VIE_C128 ? 16 : 8);
     const char* xb = (const char*)x;
@@ -800,11 +800,11 @@ vie_status matvec_common(const vie_op* op, int mode, int dtype, int recon, const
     hipError_t e;
     if (dtype == VIE_C128)
         e = launch_matvec<double, double>(op->d, mode, 0, (const c2<double>*)eps, (const c2<double>*)x,
-                                          (c2<double>*)y, nrhs, (c2<double>*)ws, s, rhs_map, err);
+                                          (c2<double>*)y, nrhs, (c2<double>*)ws, ws_bytes / el, s, rhs_map, err);
     else
         e = launch_matvec<float, float>(op->d, mode, recon == VIE_RECON_BF16 ? 1 : 0, (const c2<float>*)eps,
                                         (const c2<float>*)x,
-                                        (c2<float>*)y, nrhs, (c2<float>*)ws, s, rhs_map, err);
+                                        (c2<float>*)y, nrhs, (c2<float>*)ws, ws_bytes / el, s, rhs_map, err);
     if (e != hipSuccess) {
         if (!err.empty()) return fail(VIE_E_UNSUPPORTED, "vie_matvec: " + err);
         return hip_fail(e, "vie_matvec launch");
@@ -873,11 +873,11 @@ vie_status vie_matvec_jm(const vie_op* op_n, const vie_op* op_k, int dtype, doub
         // refined solve)
         std::string err;
         hipError_t he = launch_matvec<double, float>(op_n->d, MODE_N, 0, nullptr, (const c2<double>*)x,
-                                                     (c2<double>*)NX, 2, (c2<float>*)mw, (hipStream_t)stream,
+                                                     (c2<double>*)NX, 2, (c2<float>*)mw, matvec_ws_elems(op_n->d, 2), (hipStream_t)stream,
                                                      nullptr, err);
         if (he == hipSuccess)
             he = launch_matvec<double, float>(op_k->d, MODE_N, 0, nullptr, (const c2<double>*)x, (c2<double>*)KX, 2,
-                                              (c2<float>*)mw, (hipStream_t)stream, nullptr, err);
+                                              (c2<float>*)mw, matvec_ws_elems(op_k->d, 2), (hipStream_t)stream, nullptr, err);
         if (he != hipSuccess) return err.empty() ? hip_fail(he, "vie_matvec_jm") : fail(VIE_E_UNSUPPORTED, err);
     } else {
         st = matvec_common(op_n, MODE_N, dtype, VIE_RECON_AUTO, nullptr, x, NX, 2, mw, mb, stream, nullptr);
@@ -969,10 +969,10 @@ static vie_status debug_pass_common(const char* who, const vie_op* op, int pass,
     }
     if (dtype == VIE_C128)
         e = run_pass<double, double>(op->d, pass, mode, 0, (const c2<double>*)eps_c, (const c2<double>*)x, in, out,
-                                     nrhs, s, nullptr, err, ident, (c2<double>*)zv);
+                                     nrhs, s, nullptr, err, ident, (c2<double>*)zv, zv ? zv_elems(v) : 0);
     else
         e = run_pass<float, float>(op->d, pass, mode, recon == VIE_RECON_BF16 ? 1 : 0, (const c2<float>*)eps_c,
-                                   (const c2<float>*)x, in, out, nrhs, s, nullptr, err, ident, (c2<float>*)zv);
+                                   (const c2<float>*)x, in, out, nrhs, s, nullptr, err, ident, (c2<float>*)zv, zv ? zv_elems(v) : 0);
     if (zv) {
         const hipError_t es = hipStreamSynchronize(s);
         (void)hipFree(zv);
@@ -1148,9 +1148,11 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
     double best = 1e300;
     auto run = [&]() -> bool {
         if (dtype == VIE_C128)
-            return z_pass_fast<double>(d, MODE_A, 0, nrhs, (c2<double>*)ws, (c2<double>*)ws + s2, d.tw64[2],
+            return z_pass_fast<double>(d, MODE_A, 0, nrhs, (c2<double>*)ws, (c2<double>*)ws + s2,
+                                       matvec_ws_elems(d, nrhs) - s2, d.tw64[2],
                                        d.d64.fac, d.dense64, s);
-        return z_pass_fast<float>(d, MODE_A, 0, nrhs, (c2<float>*)ws, (c2<float>*)ws + s2, d.tw32[2], d.d32.fac,
+        return z_pass_fast<float>(d, MODE_A, 0, nrhs, (c2<float>*)ws, (c2<float>*)ws + s2, matvec_ws_elems(d, nrhs) - s2,
+                                  d.tw32[2], d.d32.fac,
                                   d.dense32, s);
     };
     for (int k = 0; k < 4 && e == hipSuccess; ++k) {

@@ -104,6 +104,7 @@ struct ZFastArgs {
     int dense;
     int chunk;     // k1 quads per workgroup
     int rs;        // V row length (zv_stride)
+    int k20, k2n;  // canonical k2 of this launch: [k20, k20 + k2n)
 };
 
 // Per-instance descriptors of a grouped register-FFT launch (one launch per
@@ -173,7 +174,7 @@ extern thread_local bool jm_mixed_products;
 // recon: 0 = same as T, 1 = BF16 (T = float only).
 template <typename TV, typename T>
 hipError_t launch_matvec(const DeviceOp& op, int mode, int recon, const c2<TV>* eps, const c2<TV>* x,
-                         c2<TV>* y, int nrhs, c2<T>* ws, hipStream_t s, const int* rhs_map,
+                         c2<TV>* y, int nrhs, c2<T>* ws, size_t ws_elems, hipStream_t s, const int* rhs_map,
                          std::string& err);
 
 // One pass p of the matvec on explicit buffers: 0 x -> S1, 1 S1 -> S2, 2 S2 in
@@ -182,7 +183,7 @@ hipError_t launch_matvec(const DeviceOp& op, int mode, int recon, const c2<TV>* 
 template <typename TV, typename T>
 hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<TV>* eps, const c2<TV>* x,
                     const void* in, void* out, int nrhs, hipStream_t s, const int* rhs_map, std::string& err,
-                    bool ident, c2<T>* zv);
+                    bool ident, c2<T>* zv, size_t zv_cap);
 
 // Multi-instance matvec: one launch per pass over all instances (mixed-radix
 // LDS kernels).  tab_dev: device scratch for the instance table.
@@ -197,7 +198,11 @@ hipError_t launch_nhat_samples(const DeviceOp& op, int prec, const int* idx_dev,
 // Materialise dense half-spectrum stores.
 hipError_t launch_densify(DeviceOp& op, int with_c128, hipStream_t s);
 
-size_t matvec_ws_elems(const DeviceOp& op, int nrhs);   // complex elements per workspace
+// complex elements of the workspace: S2, and S1, which is grown to hold every V
+// row where the z rank comes near n3; with the least (S1 as it is) the z pass
+// goes through such a grid in slabs of k2
+size_t matvec_ws_elems(const DeviceOp& op, int nrhs);
+size_t matvec_ws_least(const DeviceOp& op, int nrhs);
 
 // Instances per grouped launch (descriptors travel in the kernel arguments).
 constexpr int kXYGroupMax = 24;
@@ -227,17 +232,21 @@ bool xy_pass_mix(const DeviceOp& op, int kind, const void* in, void* out, const 
 // V rows of the z pass (k_zv): row length, complex elements, the kernel
 int zv_stride(const OpView& v);
 size_t zv_elems(const OpView& v);
+// how many k2 at a time `cap` elements hold (0: not one).  V lies in S1, which
+// is dead between Y+ and Y-; only grids whose z rank comes near n3 need the z
+// pass in more than one slab of k2
+int zv_slab(const OpView& v, size_t cap);
 template <typename T>
-void launch_zv(const DeviceOp& op, c2<T>* V, hipStream_t s);
-// launch shape of the register-FFT z pass: k1 quads per workgroup, workgroups
-// per share of the right-hand sides, shares
-void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int& chunk, int& nbx, int& gy);
+void launch_zv(const DeviceOp& op, c2<T>* V, int k20, int k2n, hipStream_t s);
+// launch shape of the register-FFT z pass over k2n canonical k2: k1 quads per
+// workgroup, workgroups per share of the right-hand sides, shares
+void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int k2n, int& chunk, int& nbx, int& gy);
 template <typename T>
-bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, hipStream_t s);
+bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, size_t vcap, hipStream_t s);
 // recon 1: N^ tables from the BF16 z factors on MFMA (T = float only)
 template <typename T>
-bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, c2<T>* V, const c2<T>* tw,
-                 const c2<T>* fac, const c2<T>* dense, hipStream_t s);
+bool z_pass_fast(const DeviceOp& op, int mode, int recon, int nrhs, c2<T>* S2, c2<T>* V, size_t vcap,
+                 const c2<T>* tw, const c2<T>* fac, const c2<T>* dense, hipStream_t s);
 // whether the BF16 MFMA reconstruction can run for this operator
 bool bf16_recon_available(const DeviceOp& op);
 // grouped register-FFT launches over a batch (instance tables on the device)

@@ -99,9 +99,26 @@ def test_superdiagonal_core(dt):
 
 
 @pytest.mark.parametrize("dt", list(TOL))
-def test_rank_at_its_limit_and_z_rank_equal_to_the_grid(dt):
-    # V tables larger than the intermediate they take the place of
-    _check((70, 64, 3), dt, 1, rank=64)
+@pytest.mark.parametrize("n", [(70, 64, 3), (35, 20, 2), (9, 1, 3), (4, 1, 1), (2, 3, 64), (16, 16, 16)])
+def test_v_rows_in_slabs(n, dt):
+    # V rows larger than the intermediate they take the place of: in one piece
+    # with the workspace that the library asks for, and with the least one in
+    # several slabs of k2, one k2 at a time, or not at all
+    _check(n, dt, 1, rank=64)
+    op, ref = _problem(n, rank=64)
+    rng = np.random.default_rng(9)
+    u = _cx(rng, (3, n[2], n[1], n[0]))
+    x = to_dev(u, dt)
+    y = torch.empty_like(x)
+    least = 18 * n[0] * n[1] * n[2] * x.element_size()
+    ws = torch.empty(least, dtype=torch.uint8, device=x.device)
+    lib = vie.load()
+    st = lib.vie_matvec(op.handle, vie.VIE_OP_N, vie._dt(x), 0, None, x.data_ptr(), y.data_ptr(), 1, ws.data_ptr(),
+                        least, vie._stream())
+    assert st == vie.VIE_OK
+    assert rel(y.cpu().numpy().astype(np.complex128), opm.matvec(ref, None, u, "N")) <= TOL[dt]
+    assert lib.vie_matvec(op.handle, vie.VIE_OP_N, vie._dt(x), 0, None, x.data_ptr(), y.data_ptr(), 1, ws.data_ptr(),
+                          least - 1, vie._stream()) == vie.VIE_E_ARG
 
 
 @pytest.mark.parametrize("dt", list(TOL))
