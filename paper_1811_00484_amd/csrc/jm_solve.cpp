@@ -49,14 +49,14 @@ KLayout k_layout(long n, size_t opws, int dtype, int m)
     off += al256(opws);
     L.partial = off;
     off += al256((size_t)(m + 2) * krylov_nblk(n) * 16);
+    L.nrm = off;   // norm, first and second dots: one copy brings them to the host
+    off += al256(16);
     L.h1 = off;
     off += al256((size_t)(m + 2) * 16);
     L.h2 = off;
     off += al256((size_t)(m + 2) * 16);
     L.coef = off;
     off += al256((size_t)(m + 1) * 16);
-    L.nrm = off;
-    off += al256(16);
     L.map = off;
     off += al256(sizeof(int));
     L.total = off;
@@ -113,7 +113,9 @@ vie_status gmres_run(long n, const KLayout& L, FA apply, FI apply_inner, bool re
     }
     std::vector<cd> H((size_t)(m + 1) * m), g(m + 1), sn(m);
     std::vector<double> cs(m);
-    std::vector<c2<double>> h1(m + 2), h2(m + 2);
+    const size_t at1 = (L.h1 - L.nrm) / sizeof(c2<double>), at2 = (L.h2 - L.nrm) / sizeof(c2<double>);
+    std::vector<c2<double>> hd(at2 + m + 2);   // the host's copy of nrm, h1, h2
+    c2<double>*h1 = hd.data() + at1, *h2 = hd.data() + at2;
     for (int outer = 0; bnorm > 0.0; ++outer) {
         // true residual R = b - A x
         vie_status s = apply(x, R);
@@ -148,10 +150,9 @@ vie_status gmres_run(long n, const KLayout& L, FA apply, FI apply_inner, bool re
             if (e == hipSuccess) e = kr_mdot<TK>(V, n, n, j + 1, V, wo, n, dmap, 1, partial, dh2, st);
             if (e == hipSuccess)
                 e = kr_maxpy<TK>(V, wo, n, V, n, n, j + 1, j + 1, dh2, -1.0, n, dmap, 1, st, partial, dnrm);
-            if (e == hipSuccess) e = hipMemcpyAsync(h1.data(), dh1, sizeof(c2<double>) * (j + 2), hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess) e = hipMemcpyAsync(h2.data(), dh2, sizeof(c2<double>) * (j + 1), hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess) e = sync_copy(&hn, dnrm, sizeof(hn));
+            if (e == hipSuccess) e = sync_copy(hd.data(), dnrm, sizeof(c2<double>) * (at2 + j + 1));
             if (e != hipSuccess) return hip_fail(e, who);
+            hn = hd[0];
             cd* Hc = &H[(size_t)j * (m + 1)];
             for (int i = 0; i <= j; ++i) Hc[i] = cd(h1[i].x + h2[i].x, h1[i].y + h2[i].y);
             const double hj1 = std::sqrt(std::max(hn.x, 0.0));

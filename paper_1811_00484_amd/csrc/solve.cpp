@@ -57,14 +57,14 @@ Layout layout(const DeviceOp& op, int dtype, int nrhs, int m, int refine)
     off += align256(mv_bytes);
     L.partial = off;
     off += align256((size_t)nrhs * (m + 1) * krylov_nblk(n) * 16);
+    L.nrm = off;   // right before h1: one copy brings both to the host
+    off += align256((size_t)nrhs * 16);
     L.h1 = off;
     off += align256((size_t)nrhs * (m + 1) * 16);
     L.h2 = off;
     off += align256((size_t)nrhs * (m + 1) * 16);
     L.coef = off;
     off += align256((size_t)nrhs * (m + 1) * 16);
-    L.nrm = off;
-    off += align256((size_t)nrhs * 16);
     L.map = off;
     off += align256((size_t)nrhs * 4);
     L.total = off;
@@ -125,6 +125,7 @@ struct Inst {
     c2<double>* dcoef = nullptr;
     c2<double>* dnrm = nullptr;
     int* dmap = nullptr;
+    std::vector<int> mapped;   // what dmap holds
     std::vector<double> bnorm, relres;
     std::vector<char> conv;
     std::vector<int> mvs, mv64, cycles;
@@ -150,10 +151,14 @@ vie_status run_multi(std::vector<Inst<TK>>& I, int mode, const vie_solve_opts& o
     hipError_t e;
     std::string err;
     auto upload_map = [&](Inst<TK>& in, const std::vector<int>& mp) -> hipError_t {
-        if (mp.empty()) return hipSuccess;
+        // most steps run the systems of the step before: the copy and its wait
+        // (the source is host memory) only where the set changed
+        if (mp.empty() || mp == in.mapped) return hipSuccess;
+        in.mapped.clear();
         hipError_t er = hipMemcpyAsync(in.dmap, mp.data(), sizeof(int) * mp.size(), hipMemcpyHostToDevice, st);
-        if (er != hipSuccess) return er;
-        return hipStreamSynchronize(st);
+        if (er == hipSuccess) er = hipStreamSynchronize(st);
+        if (er == hipSuccess) in.mapped = mp;
+        return er;
     };
     auto fetch = [&](void* dst, const void* src, size_t bytes) -> hipError_t {
         hipError_t er = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
@@ -287,11 +292,11 @@ vie_status run_multi(std::vector<Inst<TK>>& I, int mode, const vie_solve_opts& o
                 if (e == hipSuccess)
                     e = kr_maxpy<TK>(in.V, wvoff, n, in.V, vstride, n, j + 1, j + 2, in.dh1, -1.0, n, in.dmap, nr, st,
                                      in.partial, in.dnrm);
-                std::vector<c2<double>> h1((size_t)nr * (j + 2)), h2((size_t)nr * (j + 1)), hb(nr);
+                const size_t skip = (in.Lt.h1 - in.Lt.nrm) / sizeof(c2<double>);   // norms, then the dots
+                std::vector<c2<double>> hd(skip + (size_t)nr * (j + 2)), h2((size_t)nr * (j + 1));
+                c2<double>*hb = hd.data(), *h1 = hd.data() + skip;
                 if (e == hipSuccess)
-                    e = hipMemcpyAsync(h1.data(), in.dh1, sizeof(c2<double>) * h1.size(), hipMemcpyDeviceToHost, st);
-                if (e == hipSuccess)
-                    e = hipMemcpyAsync(hb.data(), in.dnrm, sizeof(c2<double>) * nr, hipMemcpyDeviceToHost, st);
+                    e = hipMemcpyAsync(hd.data(), in.dnrm, sizeof(c2<double>) * hd.size(), hipMemcpyDeviceToHost, st);
                 if (e == hipSuccess) e = hipStreamSynchronize(st);
                 if (e != hipSuccess) return hip_fail(e, "vie_solve arnoldi");
                 // second pass (re-orthogonalisation) unless the first one lost
@@ -315,7 +320,7 @@ vie_status run_multi(std::vector<Inst<TK>>& I, int mode, const vie_solve_opts& o
                         e = hipMemcpyAsync(h2.data(), in.dh2, sizeof(c2<double>) * h2.size(), hipMemcpyDeviceToHost,
                                            st);
                     if (e == hipSuccess)
-                        e = hipMemcpyAsync(hb.data(), in.dnrm, sizeof(c2<double>) * nr, hipMemcpyDeviceToHost, st);
+                        e = hipMemcpyAsync(hb, in.dnrm, sizeof(c2<double>) * nr, hipMemcpyDeviceToHost, st);
                 } else {
                     std::fill(h2.begin(), h2.end(), mk<double>(0, 0));
                 }
