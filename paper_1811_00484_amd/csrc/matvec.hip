@@ -982,7 +982,7 @@ static hipError_t launch_batch_grouped(const std::vector<InstHost>& req, int mod
                     z.za.rs = zv_stride(v);
                     z.za.k20 = 0;
                     z.za.k2n = v.n[1] + 1;
-                    z_fast_shape(op, h.nact, sizeof(c2<T>), z.za.k2n, z.za.chunk, z.nbx, z.gy);
+                    z_fast_shape(op, h.nact, z.za.k2n, z.za.chunk, z.nbx, z.gy);
                     z.nrhs = h.nact;
                     z.off = off;
                     off += z.nbx * z.gy;

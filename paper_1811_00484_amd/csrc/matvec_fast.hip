@@ -647,13 +647,15 @@ __device__ __forceinline__ void z_inverse(c2<T> (&d)[3][8], c2<T>* slice, int t,
     for (int q = 0; q < 3; ++q) RegPlan<L3>::template inv<T, TPP, 1, 1>(d[q], slice, 0, t, tws);
 }
 
-// Quad A's table takes the place of the FFT slices where the pencils and two
-// tables would leave one workgroup per CU (complex128 at 512): then the
-// forward FFTs end before the tables and a workgroup takes one right-hand side.
+// Quad A's table takes the place of the FFT slices at 512, where pencils and
+// two tables leave three workgroups per CU (complex128: one): then the forward
+// FFTs end before the tables and a workgroup takes one right-hand side, with
+// barriers again, but a fourth (second) workgroup hides more (256^3 product
+// 3.37 -> 3.32 ms; two wavefronts a SIMD instead of three: 3.76).
 template <typename T, int L3>
 constexpr bool z_shared_table()
 {
-    return sizeof(T) == 8 && L3 == 512;
+    return L3 == 512;
 }
 
 // REC: 0 = N^ tables in T (complex64: on MFMA), 1 = BF16 z factors on MFMA
@@ -719,7 +721,7 @@ __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __re
         // ---- the pencils' loads go out first
         c2<T> dA[3][8], dB[3][8];
         if (sizeof(T) == 4 || SHARED) z_load<T, L3, TPP, Plan::RF0>(dA, of_rhs(b), off(kA), cstride, exA);
-        if (sizeof(T) == 4) z_load<T, L3, TPP, Plan::RF0>(dB, of_rhs(b), off(kB), cstride, exB);
+        if (sizeof(T) == 4 && !SHARED) z_load<T, L3, TPP, Plan::RF0>(dB, of_rhs(b), off(kB), cstride, exB);
         if (!a.dense) {
             for (int e = tid; e < 2 * NC * rs; e += NT) {
                 const int qd = e / (NC * rs), rem = e - qd * NC * rs;
@@ -836,7 +838,7 @@ __device__ __forceinline__ void z_body(c2<T>* __restrict__ S2, const c2<T>* __re
 }
 
 template <typename T, int L3, bool CONJ, int REC>
-__global__ void __launch_bounds__(4 * (L3 / 8), sizeof(T) == 4 ? 3 : 2)
+__global__ void __launch_bounds__(4 * (L3 / 8), sizeof(T) == 4 ? (L3 == 512 ? 4 : 3) : 2)
     k_z_fast(c2<T>* __restrict__ S2, const c2<T>* __restrict__ tw, ZFastArgs a, const c2<T>* __restrict__ V,
              const c2<T>* __restrict__ fac, const c2<T>* __restrict__ dense, const unsigned short* __restrict__ f3m,
              int nrhs)
@@ -846,7 +848,7 @@ __global__ void __launch_bounds__(4 * (L3 / 8), sizeof(T) == 4 ? 3 : 2)
 
 // Grouped launch over instances with the same z length (offsets ascending).
 template <typename T, int L3, bool CONJ, int REC>
-__global__ void __launch_bounds__(4 * (L3 / 8), sizeof(T) == 4 ? 3 : 2)
+__global__ void __launch_bounds__(4 * (L3 / 8), sizeof(T) == 4 ? (L3 == 512 ? 4 : 3) : 2)
     k_z_fast_multi(const ZGroup g, const c2<T>* __restrict__ tw)
 {
     int i = 0;
@@ -930,19 +932,20 @@ static size_t zfast_lds(int rs)
                             12 * rs + RegPlan<L3>::TW);
 }
 
-void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int k2n, int& chunk, int& nbx, int& gy)
+void z_fast_shape(const DeviceOp& op, int nrhs, int k2n, int& chunk, int& nbx, int& gy)
 {
     const OpView& v = op.view;
     const int n1p1 = v.n[0] + 1;
-    // a chunk only saves twiddle fills: halve it until the grid holds sixteen
-    // workgroups per CU (the autotuned length is the limit)
+    // a chunk only saves twiddle fills: halve it until the grid holds 64
+    // workgroups per CU, so that the last round is short (the autotuned length
+    // is the limit; 256^3 product 3.32 -> 3.29 ms against sixteen per CU)
     chunk = op.zchunk;
-    while (chunk > 2 && (long)k2n * ((n1p1 + chunk - 1) / chunk) < 4096) chunk /= 2;
+    while (chunk > 2 && (long)k2n * ((n1p1 + chunk - 1) / chunk) < 16384) chunk /= 2;
     nbx = k2n * ((n1p1 + chunk - 1) / chunk);
     // right-hand sides share a workgroup's tables as far as the grid holds
     // eight workgroups per CU
     gy = 1;
-    if (elem_bytes == 16 && v.L[2] == 512) gy = nrhs;   // z_shared_table
+    if (v.L[2] == 512) gy = nrhs;   // z_shared_table
     while (gy < nrhs && (long)nbx * gy < 2048) ++gy;
 }
 
@@ -969,7 +972,7 @@ static hipError_t launch_z(const DeviceOp& op, int mode, int recon, int nrhs, c2
         za.k2n = std::min(slab, n2p1 - za.k20);
         if (!za.dense) launch_zv<T>(op, V, za.k20, za.k2n, s);
         int nbx, gy;
-        z_fast_shape(op, nrhs, sizeof(c2<T>), za.k2n, za.chunk, nbx, gy);
+        z_fast_shape(op, nrhs, za.k2n, za.chunk, nbx, gy);
         hipLaunchKernelGGL(kern, dim3(nbx, gy), dim3(4 * (L3 / 8)), lds, s, S2, tw, za, (const c2<T>*)V, fac, dense,
                            (const unsigned short*)op.b16.fac3m, nrhs);
     }

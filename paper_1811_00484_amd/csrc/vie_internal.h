@@ -240,7 +240,7 @@ template <typename T>
 void launch_zv(const DeviceOp& op, c2<T>* V, int k20, int k2n, hipStream_t s);
 // launch shape of the register-FFT z pass over k2n canonical k2: k1 quads per
 // workgroup, workgroups per share of the right-hand sides, shares
-void z_fast_shape(const DeviceOp& op, int nrhs, int elem_bytes, int k2n, int& chunk, int& nbx, int& gy);
+void z_fast_shape(const DeviceOp& op, int nrhs, int k2n, int& chunk, int& nbx, int& gy);
 template <typename T>
 bool z_pass_mix(const DeviceOp& op, int mode, int nrhs, c2<T>* S2, c2<T>* V, size_t vcap, hipStream_t s);
 // recon 1: N^ tables from the BF16 z factors on MFMA (T = float only)
