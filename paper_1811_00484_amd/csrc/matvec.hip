@@ -14,10 +14,14 @@
 //
 // Each pass writes its output transposed so that the next FFT axis is the
 // contiguous one for the Z pass and global accesses of every pass are runs of
-// at least W (= 16 complex64 / 8 complex128) contiguous elements.  Within a
-// block the W pencils of a tile sit in LDS as [element][pencil] (X and Y
-// passes) or [pencil][element] (Z pass) and are transformed by the Stockham
-// stages of fft_device.h.
+// at least W (= 16 complex64 / 8 complex128) contiguous elements.  A single
+// matvec's passes run the register-FFT kernels of matvec_fast.hip or the
+// mixed-radix ones of matvec_mix.hip (any other length).  The kernels of this
+// file carry several instances of different lengths in one launch per pass,
+// and the z pass where there is no scratch for the rows V_c below (a single
+// pass under stream capture, grids of a few voxels): the W pencils of a tile
+// sit in LDS as [element][pencil] (X and Y passes) or [pencil][element] (Z
+// pass) and are transformed by the Stockham stages of fft_device.h.
 //
 // Z pass and the Tucker form (eq. 13-14, Sec. V-A/B): for a pencil (k1, k2)
 //   N^_c(k1, k2, k3) = sum_g V_c[g] U3^_c(k3, g),

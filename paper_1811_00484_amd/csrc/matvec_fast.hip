@@ -1,8 +1,8 @@
 // Register-FFT kernels of the five matvec passes for the FFT lengths of the
 // workloads that matter for throughput: 128, 256, 512 (radix 8/4) on every
-// axis, and 192, 224 (radix 8/4/3, 7/4/2) for the x and y passes.  Same data layouts and results as the generic LDS-staged
-// kernels in matvec.hip (which remain the path for lengths with factors 3,
-// 5, 7), but each thread keeps its pencil elements in registers across the
+// axis, and 192, 224 (radix 8/4/3, 7/4/2) for the x and y passes.  Same
+// buffers as the mixed-radix kernels of matvec_mix.hip, which take every other
+// length, but each thread keeps its pencil elements in registers across the
 // radix-8/4 stages (reg_fft.h) and LDS only carries the transposes between
 // stages.
 //
@@ -23,8 +23,8 @@
 // block (in chunks of sixteen quads, which left most CUs idle on small
 // grids), per launch, MI355X: 64^3, two right-hand sides, BF16 tables
 // 256 -> 62 us (and 10 us for k_zv); 128^3, four right-hand sides 976 -> 561 us;
-// 256^3 1.75 ms either way, where vector issue and the 3.2 GB it streams
-// bound it at three wavefronts a SIMD.
+// 256^3 1.75 -> 1.6 ms, where vector issue and the 3.2 GB it streams bound
+// it at four wavefronts a SIMD.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -55,7 +55,6 @@ struct RegPlan<512> {
     __device__ static void fill_tw(c2<T>* dst, const c2<T>* tw, int tid, int nt)
     {
         TwF::fill(dst, tw, tid, nt);
-        
     }
     template <typename T, int TPP, int NSEQ, int DIR>
     __device__ static void fwd(c2<T>* v, c2<T>* lds, int st, int t, const c2<T>* tws)
@@ -127,7 +126,6 @@ struct RegPlan<64> {
     __device__ static void fill_tw(c2<T>* dst, const c2<T>* tw, int tid, int nt)
     {
         TwF::fill(dst, tw, tid, nt);
-        
     }
     template <typename T, int TPP, int NSEQ, int DIR>
     __device__ static void fwd(c2<T>* v, c2<T>* lds, int st, int t, const c2<T>* tws)
@@ -651,7 +649,8 @@ __device__ __forceinline__ void z_inverse(c2<T> (&d)[3][8], c2<T>* slice, int t,
 // two tables leave three workgroups per CU (complex128: one): then the forward
 // FFTs end before the tables and a workgroup takes one right-hand side, with
 // barriers again, but a fourth (second) workgroup hides more (256^3 product
-// 3.37 -> 3.32 ms; two wavefronts a SIMD instead of three: 3.76).
+// 3.37 -> 3.29 ms in complex64, 9.1 -> 6.5 in complex128; complex64 with two
+// wavefronts a SIMD: 3.76).
 template <typename T, int L3>
 constexpr bool z_shared_table()
 {
