@@ -98,8 +98,8 @@ def copy_bandwidth(torch, dev, reps=5):
 
 
 # sources of the five matvec passes' kernels (and what they include)
-MATVEC_KERNEL_SOURCES = ["matvec.hip", "matvec_fast.hip", "reg_fft.h", "fft_device.h", "dev_common.h",
-                         "vie_internal.h"]
+MATVEC_KERNEL_SOURCES = ["matvec.hip", "matvec_fast.hip", "matvec_mix.hip", "v_rows.h", "mix_fft.h", "reg_fft.h",
+                         "fft_device.h", "dev_common.h", "vie_internal.h"]
 
 
 def kernel_sources_sha256():
