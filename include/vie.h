@@ -729,7 +729,10 @@ vie_status vie_debug_nhat(const vie_op* op, int dtype, int recon, const int* idx
  *   y[b][q][k][j][i] = S3[b][q][k][i][j] for i < n1 (rows n1..L1-1 dropped).
  *   vie_debug_crop(vie_debug_pad(x)) = x bit for bit.
  * vie_debug_pass -- pass `pass` of the matvec of kind (VIE_OP_A or VIE_OP_N)
- *   and adjoint flag, exactly as vie_matvec runs it:
+ *   and adjoint flag, exactly as vie_matvec runs it (pass 2 takes its scratch
+ *   from the device's stream-ordered memory pool; on a capturing stream it
+ *   allocates memory that the operator keeps until vie_op_destroy, so the
+ *   operator must outlive the graph):
  *   0 (X+):  in unused; reads x (and eps_c for the A^H pre-scale x <- conj(chi) x);
  *            out S1[b][q][k][.][j] = F_L1 of x[b][q][k][j][.] padded to L1
  *   1 (Y+):  in S1, out S2[b][q][.][i][k] = F_L2 of S1[b][q][k][i][.] padded to L2

@@ -18,8 +18,8 @@
 // matvec's passes run the register-FFT kernels of matvec_fast.hip or the
 // mixed-radix ones of matvec_mix.hip (any other length).  The kernels of this
 // file carry several instances of different lengths in one launch per pass,
-// and the z pass where there is no scratch for the rows V_c below (a single
-// pass under stream capture, grids of a few voxels): the W pencils of a tile
+// and the z pass where there is no scratch for the rows V_c below (grids of a
+// few voxels): the W pencils of a tile
 // sit in LDS as [element][pencil] (X and Y passes) or [pencil][element] (Z
 // pass) and are transformed by the Stockham stages of fft_device.h.
 //
@@ -579,9 +579,9 @@ static size_t z_lds_bytes(const OpView& v, int G)
 // (out), 4 reads S3 (in) and writes y (out).  ident (passes 0 and 4 only):
 // the transform is replaced by the identity, so only the pass's index maps
 // (padding, transposes, cropping; pass 4 with the bare epilogue) remain.
-// zv: scratch of zv_cap elements for pass 2's V rows; without room for one
-// k2's (no scratch: vie_debug_pass under stream capture; grids of a few
-// voxels) the z pass contracts the cores in every workgroup.
+// zv: scratch of zv_cap elements for pass 2's V rows (a dense spectrum needs
+// none); without room for one k2's (grids of a few voxels) the z pass
+// contracts the cores in every workgroup.
 template <typename TV, typename T>
 hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<TV>* eps, const c2<TV>* x,
                     const void* in, void* out, int nrhs, hipStream_t s, const int* rhs_map, std::string& err,
@@ -631,13 +631,13 @@ hipError_t run_pass(const DeviceOp& op, int pass, int mode, int recon, const c2<
             err = "dense spectrum not materialised";
             return hipErrorInvalidValue;
         }
-        if (allow_fast && zv && z_pass_fast<T>(op, mode, recon, nrhs, S2, zv, zv_cap, tw[2], fac, dense, s))
+        if (allow_fast && z_pass_fast<T>(op, mode, recon, nrhs, S2, zv, zv_cap, tw[2], fac, dense, s))
             return hipGetLastError();
         if (recon == 1) {
             err = "BF16 z pass could not be launched";
             return hipErrorInvalidValue;
         }
-        if (zv && z_pass_mix<T>(op, mode, nrhs, S2, zv, zv_cap, s)) return hipGetLastError();
+        if (z_pass_mix<T>(op, mode, nrhs, S2, zv, zv_cap, s)) return hipGetLastError();
         int G = 4;
         while (G > 1 && z_lds_bytes<T>(v, G) > op.max_lds) G /= 2;
         size_t lds = z_lds_bytes<T>(v, G);

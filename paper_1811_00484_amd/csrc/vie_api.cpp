@@ -626,6 +626,7 @@ vie_status vie_op_destroy(vie_op* op)
 {
     if (!op) return VIE_OK;
     free_op(op->d);
+    for (void* p : op->held) (void)hipFree(p);
     delete op;
     return VIE_OK;
 }
@@ -918,6 +919,31 @@ static bool disjoint(const void* a, size_t na, const void* b, size_t nb)
     return pa + na <= pb || pb + nb <= pa;
 }
 
+// Scratch for one z pass on stream s: from the stream-ordered pool (the caller
+// returns it with hipFreeAsync), or, on a capturing stream, memory that the
+// operator keeps (keep) for the graph's replays.
+static hipError_t debug_scratch(const vie_op* op, size_t bytes, hipStream_t s, void** out, bool* keep)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &cap);
+    if (e != hipSuccess) return e;
+    *keep = cap != hipStreamCaptureStatusNone;
+    if (!*keep) return hipMallocAsync(out, bytes, s);
+    // plain allocations are not stream work, but a capture in global mode
+    // refuses them unless this thread says that it means it
+    hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
+    e = hipThreadExchangeStreamCaptureMode(&m);
+    if (e != hipSuccess) return e;
+    e = hipMalloc(out, bytes);
+    const hipError_t er = hipThreadExchangeStreamCaptureMode(&m);
+    if (e == hipSuccess) {
+        std::lock_guard<std::mutex> lk(op->held_mu);
+        op->held.push_back(*out);
+        e = er;
+    }
+    return e;
+}
+
 static vie_status debug_pass_common(const char* who, const vie_op* op, int pass, int mode, int dtype, int recon,
                                     const void* eps_c, const void* x, const void* in, void* out, int nrhs,
                                     void* stream, bool ident)
@@ -958,25 +984,23 @@ static vie_status debug_pass_common(const char* who, const vie_op* op, int pass,
     if (pass == 2 && in != out) e = hipMemcpyAsync(out, in, nin, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return hip_fail(e, w.c_str());
     std::string err;
-    // pass 2 outside a matvec has no S1 to hold the V tables: take scratch for
-    // the call (not under stream capture, where nothing can be allocated)
+    // pass 2 outside a matvec has no S1 to hold the V rows
     void* zv = nullptr;
-    if (pass == 2) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        e = hipStreamIsCapturing(s, &cap);
-        if (e == hipSuccess && cap == hipStreamCaptureStatusNone) e = hipMalloc(&zv, zv_elems(v) * el);
+    bool keep = false;
+    if (pass == 2 && op->d.nhat_source != 1) {
+        e = debug_scratch(op, zv_elems(v) * el, s, &zv, &keep);
         if (e != hipSuccess) return hip_fail(e, w.c_str());
     }
+    const size_t zcap = zv ? zv_elems(v) : 0;
     if (dtype == VIE_C128)
         e = run_pass<double, double>(op->d, pass, mode, 0, (const c2<double>*)eps_c, (const c2<double>*)x, in, out,
-                                     nrhs, s, nullptr, err, ident, (c2<double>*)zv, zv ? zv_elems(v) : 0);
+                                     nrhs, s, nullptr, err, ident, (c2<double>*)zv, zcap);
     else
         e = run_pass<float, float>(op->d, pass, mode, recon == VIE_RECON_BF16 ? 1 : 0, (const c2<float>*)eps_c,
-                                   (const c2<float>*)x, in, out, nrhs, s, nullptr, err, ident, (c2<float>*)zv, zv ? zv_elems(v) : 0);
-    if (zv) {
-        const hipError_t es = hipStreamSynchronize(s);
-        (void)hipFree(zv);
-        if (e == hipSuccess) e = es;
+                                   (const c2<float>*)x, in, out, nrhs, s, nullptr, err, ident, (c2<float>*)zv, zcap);
+    if (zv && !keep) {
+        const hipError_t ef = hipFreeAsync(zv, s);
+        if (e == hipSuccess) e = ef;
     }
     if (e != hipSuccess) {
         if (!err.empty()) return fail(VIE_E_UNSUPPORTED, w + ": " + err);

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -286,6 +287,10 @@ struct KrylovArgs;
 // opaque handle of the C ABI
 struct vie_op {
     vie::DeviceOp d;
+    // scratch of z passes that vie_debug_pass recorded into graphs: the graphs
+    // use it on every replay, so it lives as long as the operator
+    mutable std::mutex held_mu;
+    mutable std::vector<void*> held;
 };
 
 namespace vie {

@@ -192,3 +192,34 @@ def test_debug_pass_argument_errors():
     assert lib.vie_debug_pass(op.handle, 0, 7, 0, 0, 0, None, x.data_ptr(), None, x.data_ptr(), 1, s) == vie.VIE_E_ARG
     # output overlapping the input
     assert lib.vie_debug_pad(op.handle, 0, x.data_ptr(), x.data_ptr(), 1, s) == vie.VIE_E_ARG
+
+
+@pytest.mark.parametrize("n,dt,recon,source", [
+    ((60, 9, 64), torch.complex64, "bf16", "tucker"), ((60, 9, 64), torch.complex64, "auto", "tucker"),
+    ((60, 9, 64), torch.complex128, "auto", "tucker"), ((20, 15, 18), torch.complex64, "auto", "tucker"),
+    ((60, 9, 64), torch.complex64, "auto", "dense"), ((20, 15, 18), torch.complex128, "auto", "dense")])
+def test_captured_z_pass_equals_the_eager_one_bitwise(n, dt, recon, source):
+    # the kernels of a product under capture too, BF16 tables among them; each
+    # replay on new input, with eager work in between
+    op = _small_operator(n)
+    if source == "dense":
+        vie.densify(op, with_c128=True)
+        vie.set_nhat(op, "dense")
+    rng = np.random.default_rng(6)
+    shape = vie.pass_shape(op, "S2", 2)
+
+    def draw():
+        return to_dev(rng.standard_normal(shape) + 1j * rng.standard_normal(shape), dt)
+
+    inp, out = draw(), torch.zeros(shape, dtype=dt, device="cuda")
+    vie.debug_pass(op, 2, inp=inp, out=out, recon=recon)   # warm: code objects load outside the capture
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        vie.debug_pass(op, 2, inp=inp, out=out, recon=recon)
+    for _ in range(3):
+        inp.copy_(draw())
+        want = vie.debug_pass(op, 2, inp=inp, recon=recon)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
