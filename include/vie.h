@@ -323,7 +323,10 @@ vie_status vie_pwl_op_query(const vie_pwl_op* op, int n[3], int ranks[10][6][3])
  * padded components through the five passes; the rows
  * V_c(k1, k2, :) = U1_c(k1, :) (G_c x2 U2_c(k2, :)) of the sixty (K: thirty)
  * components, shared by the vectors, take the place of the first
- * intermediate, which grows to hold them where the z ranks come near 0.4 n3 */
+ * intermediate, which grows to hold them where the z ranks come near 0.4 n3.
+ * The products and solves accept less, down to the ungrown intermediate (72
+ * n1 n2 n3 complex per vector, where that holds a row of every component): the
+ * z pass then takes the grid in several pieces */
 size_t vie_pwl_workspace_bytes(const vie_pwl_op* op, int dtype, int nrhs);
 
 /*

@@ -22,7 +22,9 @@ namespace vie {
 vie_status fail(vie_status st, const std::string& msg);
 vie_status hip_fail(hipError_t e, const char* where);
 vie_status pwl_apply_mixed(const vie_pwl_op* op, int mode, const void* eps, const void* x, void* y, void* ws,
-                           hipStream_t s);
+                           size_t ws_bytes, hipStream_t s);
+size_t pwl_workspace_least(const vie_pwl_op* op, int dtype, int nrhs);
+size_t jm_pwl_workspace_least(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype);
 
 namespace {
 
@@ -238,49 +240,48 @@ vie_status run_jm(const vie_op* op_n, const vie_op* op_k, int dtype, double h, d
     return gmres_run<TK>(n, L, apply, apply_inner, refine, b, x, o, info, ws, st, "vie_solve_jm");
 }
 
-KLayout pwl_layout(const vie_pwl_op* op, int dtype, int m)
+// opws: the product's workspace (vie_pwl_workspace_bytes or the least)
+KLayout pwl_layout(const vie_pwl_op* op, size_t opws, int dtype, int m)
 {
     const OpView& v = op->blk[0]->d.view;
-    return k_layout(12L * v.n[0] * v.n[1] * v.n[2], vie_pwl_workspace_bytes(op, dtype, 1), dtype, m);
+    return k_layout(12L * v.n[0] * v.n[1] * v.n[2], opws, dtype, m);
 }
 
 template <typename TK>
 vie_status run_pwl(const vie_pwl_op* op, int dtype, const void* eps_c, const c2<TK>* b, c2<TK>* x,
-                   const vie_solve_opts& o, vie_solve_info* info, char* ws, hipStream_t st)
+                   const vie_solve_opts& o, vie_solve_info* info, char* ws, size_t pwb, hipStream_t st)
 {
     const OpView& v = op->blk[0]->d.view;
     const long n = 12L * v.n[0] * v.n[1] * v.n[2];
-    const KLayout L = pwl_layout(op, dtype, o.restart);
+    const KLayout L = pwl_layout(op, pwb, dtype, o.restart);
     void* pw = ws + L.op;
-    const size_t pwb = vie_pwl_workspace_bytes(op, dtype, 1);
     const int mode = o.adjoint ? MODE_AH : MODE_A;
     const bool refine = o.refine && sizeof(TK) == 8;
     auto apply = [&](const c2<TK>* in, c2<TK>* out) {
         return vie_matvec_pwl(op, VIE_OP_A, o.adjoint, dtype, eps_c, in, out, 1, pw, pwb, (void*)st);
     };
     auto apply_inner = [&](const c2<TK>* in, c2<TK>* out) {
-        if (refine) return pwl_apply_mixed(op, mode, eps_c, in, out, pw, st);
+        if (refine) return pwl_apply_mixed(op, mode, eps_c, in, out, pw, pwb, st);
         return vie_matvec_pwl(op, VIE_OP_A, o.adjoint, dtype, eps_c, in, out, 1, pw, pwb, (void*)st);
     };
     return gmres_run<TK>(n, L, apply, apply_inner, refine, b, x, o, info, ws, st, "vie_solve_pwl");
 }
 
-KLayout jm_pwl_layout(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype, int m)
+KLayout jm_pwl_layout(const vie_pwl_op* op_n, size_t opws, int dtype, int m)
 {
     const OpView& v = op_n->blk[0]->d.view;
-    return k_layout(24L * v.n[0] * v.n[1] * v.n[2], vie_jm_pwl_workspace_bytes(op_n, op_k, dtype), dtype, m);
+    return k_layout(24L * v.n[0] * v.n[1] * v.n[2], opws, dtype, m);
 }
 
 template <typename TK>
 vie_status run_jm_pwl(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype, double h, double omega,
                       const void* eps_c, const void* mu_c, const c2<TK>* b, c2<TK>* x, const vie_solve_opts& o,
-                      vie_solve_info* info, char* ws, hipStream_t st)
+                      vie_solve_info* info, char* ws, size_t jwb, hipStream_t st)
 {
     const OpView& v = op_n->blk[0]->d.view;
     const long n = 24L * v.n[0] * v.n[1] * v.n[2];
-    const KLayout L = jm_pwl_layout(op_n, op_k, dtype, o.restart);
+    const KLayout L = jm_pwl_layout(op_n, jwb, dtype, o.restart);
     void* jw = ws + L.op;
-    const size_t jwb = vie_jm_pwl_workspace_bytes(op_n, op_k, dtype);
     const bool refine = o.refine && sizeof(TK) == 8;
     auto apply_prec = [&](const c2<TK>* in, c2<TK>* out, bool mixed) {
         jm_mixed_products = mixed;
@@ -347,7 +348,7 @@ size_t vie_solve_pwl_workspace_bytes(const vie_pwl_op* op, int dtype, const vie_
     if (!op || !op->blk[0] || (dtype != VIE_C64 && dtype != VIE_C128)) return 0;
     const int m = opts ? opts->restart : 50;
     if (m < 1 || m > 200) return 0;
-    return pwl_layout(op, dtype, m).total;
+    return pwl_layout(op, vie_pwl_workspace_bytes(op, dtype, 1), dtype, m).total;
 }
 
 vie_status vie_solve_pwl(const vie_pwl_op* op, int dtype, const void* eps_c, const void* b, void* x,
@@ -372,7 +373,10 @@ vie_status vie_solve_pwl(const vie_pwl_op* op, int dtype, const void* eps_c, con
         return fail(VIE_E_ARG, "vie_solve_pwl: refinement needs VIE_C128 vectors and inner_tol in (0, 1)");
     if (o.refine && o.inner_recon != VIE_RECON_FP32)
         return fail(VIE_E_UNSUPPORTED, "vie_solve_pwl: refinement takes FP32 inner products only");
-    if (ws_bytes < vie_solve_pwl_workspace_bytes(op, dtype, &o))
+    // the product in less workspace than it asks for goes through in slabs
+    size_t pwb = vie_pwl_workspace_bytes(op, dtype, 1);
+    if (ws_bytes < pwl_layout(op, pwb, dtype, o.restart).total) pwb = pwl_workspace_least(op, dtype, 1);
+    if (ws_bytes < pwl_layout(op, pwb, dtype, o.restart).total)
         return fail(VIE_E_ARG, "vie_solve_pwl: workspace too small");
     if (info && info->history && info->hist_cap < 0) return fail(VIE_E_ARG, "vie_solve_pwl: bad history capacity");
     const OpView& v = op->blk[0]->d.view;
@@ -382,8 +386,8 @@ vie_status vie_solve_pwl(const vie_pwl_op* op, int dtype, const void* eps_c, con
     if (!(xb + vbytes <= bb || bb + vbytes <= xb)) return fail(VIE_E_ARG, "vie_solve_pwl: x and b overlap");
     hipStream_t st = (hipStream_t)stream;
     if (dtype == VIE_C128)
-        return run_pwl<double>(op, dtype, eps_c, (const c2<double>*)b, (c2<double>*)x, o, info, (char*)ws, st);
-    return run_pwl<float>(op, dtype, eps_c, (const c2<float>*)b, (c2<float>*)x, o, info, (char*)ws, st);
+        return run_pwl<double>(op, dtype, eps_c, (const c2<double>*)b, (c2<double>*)x, o, info, (char*)ws, pwb, st);
+    return run_pwl<float>(op, dtype, eps_c, (const c2<float>*)b, (c2<float>*)x, o, info, (char*)ws, pwb, st);
 }
 
 size_t vie_solve_jm_pwl_workspace_bytes(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype,
@@ -392,7 +396,7 @@ size_t vie_solve_jm_pwl_workspace_bytes(const vie_pwl_op* op_n, const vie_pwl_op
     if (!op_n || !op_k || !op_n->blk[0] || !op_k->blk[0] || (dtype != VIE_C64 && dtype != VIE_C128)) return 0;
     const int m = opts ? opts->restart : 50;
     if (m < 1 || m > 200) return 0;
-    return jm_pwl_layout(op_n, op_k, dtype, m).total;
+    return jm_pwl_layout(op_n, vie_jm_pwl_workspace_bytes(op_n, op_k, dtype), dtype, m).total;
 }
 
 vie_status vie_solve_jm_pwl(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype, double h, double omega,
@@ -421,7 +425,10 @@ vie_status vie_solve_jm_pwl(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int 
         return fail(VIE_E_ARG, "vie_solve_jm_pwl: refinement needs VIE_C128 vectors and inner_tol in (0, 1)");
     if (o.refine && o.inner_recon != VIE_RECON_FP32)
         return fail(VIE_E_UNSUPPORTED, "vie_solve_jm_pwl: refinement takes FP32 inner products only");
-    if (ws_bytes < vie_solve_jm_pwl_workspace_bytes(op_n, op_k, dtype, &o))
+    size_t jwb = vie_jm_pwl_workspace_bytes(op_n, op_k, dtype);
+    if (ws_bytes < jm_pwl_layout(op_n, jwb, dtype, o.restart).total)
+        jwb = jm_pwl_workspace_least(op_n, op_k, dtype);
+    if (ws_bytes < jm_pwl_layout(op_n, jwb, dtype, o.restart).total)
         return fail(VIE_E_ARG, "vie_solve_jm_pwl: workspace too small");
     if (info && info->history && info->hist_cap < 0) return fail(VIE_E_ARG, "vie_solve_jm_pwl: bad history capacity");
     const OpView& v = op_n->blk[0]->d.view;
@@ -432,9 +439,9 @@ vie_status vie_solve_jm_pwl(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int 
     hipStream_t st = (hipStream_t)stream;
     if (dtype == VIE_C128)
         return run_jm_pwl<double>(op_n, op_k, dtype, h, omega, eps_c, mu_c, (const c2<double>*)b, (c2<double>*)x, o,
-                                  info, (char*)ws, st);
+                                  info, (char*)ws, jwb, st);
     return run_jm_pwl<float>(op_n, op_k, dtype, h, omega, eps_c, mu_c, (const c2<float>*)b, (c2<float>*)x, o, info,
-                             (char*)ws, st);
+                             (char*)ws, jwb, st);
 }
 
 }  // extern "C"

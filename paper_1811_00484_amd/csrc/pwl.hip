@@ -92,26 +92,36 @@ constexpr int pwl_nc()
 }
 
 // ---------------------------------------------------------------------------
-// V[((k2 10 nc + nc b + c) (n1 + 1) + k1) rs + g] for every stored tensor, zero
-// for g beyond its z rank (rs: the largest one, rounded up to whole batches of
-// sixteen, so that the z pass reads and sums without a branch): one workgroup
-// per (k2, tensor).
+// One slab of canonical (k1, k2): k1 in [k10, k10 + k1n), k2 likewise.
+struct PwlSlab {
+    int k10, k1n;
+    int k20, k2n;
+};
+
+// V[(((k2 - k20) 10 nc + nc b + c) k1n + k1 - k10) rs + g] for every stored
+// tensor, zero for g beyond its z rank (rs: pwl_v_stride): one workgroup per
+// (k2, tensor).
 template <typename T, int FAM>
-__global__ void __launch_bounds__(kVNT) k_pwl_v(const PwlBlock<T>* __restrict__ blk, int rmax, int rs,
+__global__ void __launch_bounds__(kVNT) k_pwl_v(const PwlBlock<T>* __restrict__ blk, int rmax, int rs, PwlSlab sl,
                                                 c2<T>* __restrict__ V)
 {
     constexpr int NC = pwl_nc<FAM>();
-    const int k2 = blockIdx.x, bc = blockIdx.y;
+    const int k2 = sl.k20 + blockIdx.x, bc = blockIdx.y;
     const int b = bc / NC, c = 6 - NC + bc % NC;
     const OpView& v = blk[b].v;
-    const int r2 = v.r[c][1], n1p1 = v.n[0] + 1;
-    v_rows<T>(blk[b].core + v.core_off[c], blk[b].fac + v.fac_off[c][0], blk[b].fac + v.fac_off[c][1] + (long)k2 * r2,
-              v.r[c][0], r2, v.r[c][2], r2 * v.r[c][2], v.r[c][2], 1, n1p1, rmax, rs, false, V + ((long)k2 * 10 * NC + bc) * n1p1 * rs);
+    const int r1 = v.r[c][0], r2 = v.r[c][1], r3 = v.r[c][2];
+    v_rows<T>(blk[b].core + v.core_off[c], blk[b].fac + v.fac_off[c][0] + (long)sl.k10 * r1,
+              blk[b].fac + v.fac_off[c][1] + (long)k2 * r2, r1, r2, r3, r2 * r3, r3, 1, sl.k1n, rmax, rs, false,
+              V + ((long)blockIdx.x * 10 * NC + bc) * sl.k1n * rs);
 }
 
 // ---------------------------------------------------------------------------
 // table tasks (64 k3 of one tensor) a wavefront can hold for a second group
 constexpr int kPwlHold = 8;
+
+// elements that the batched reads of V run past its last row (batches of
+// sixteen at most, of which a row has its whole fours)
+constexpr int kPwlPast = 12;
 
 struct PwlZArgs {
     int n[3];
@@ -119,6 +129,7 @@ struct PwlZArgs {
     int L1, L2;
     int nrhs;    // right-hand sides, walked from blockIdx.y in steps of gridDim.y
     int rs;      // V stride per tensor
+    PwlSlab sl;  // of this launch
 };
 
 // threads per workgroup at most: one Fourier position each
@@ -311,7 +322,7 @@ struct PwlZ {
         const int b = b0 + t / NC, c = 6 - NC + t % NC;
         const int r3 = blk[b].v.r[c][2];
         const c2<T>* U3 = blk[b].fac + blk[b].v.fac3t_off[c] + min(k3, a.n[2]);
-        const c2<T>* va = V + (long)(NC * b0 + t) * (a.n[0] + 1) * a.rs;
+        const c2<T>* va = V + (long)(NC * b0 + t) * a.sl.k1n * a.rs;
         c2<T> eA = mk<T>(0, 0), eB = mk<T>(0, 0);   // even g (odd ones in sA, sB): shorter sums round less
         sA = mk<T>(0, 0);
         sB = mk<T>(0, 0);
@@ -325,7 +336,8 @@ struct PwlZ {
                     for (int q = h; q < h + 4; ++q) u[q] = ldg(U3 + (long)min(g0 + q, r3 - 1) * (a.n[2] + 1));
                 }
             }
-            // the whole V rows at once (scalar loads beside the factors')
+            // V a whole batch at once (scalar loads beside the factors'), into
+            // the next row or, from the last one, into kPwlPast elements
 #pragma unroll
             for (int q = 0; q < CH; ++q) {
                 wA[q] = va[g0 + q];
@@ -477,17 +489,22 @@ __global__ void __launch_bounds__(pwl_max_nt<T>())
     const int n1 = a.n[0], n2 = a.n[1];
     // XCD-wise runs of neighbouring groups (workgroups go round robin over
     // the eight XCDs): their pencils share cache lines
-    const int nk1 = G >= 2 ? n1 + 1 : a.L1, nx = (nk1 + a.nq - 1) / a.nq, ny = G == 4 ? n2 + 1 : a.L2;
+    const int nk1 = (G >= 2 ? 1 : 2) * a.sl.k1n, nx = (nk1 + a.nq - 1) / a.nq, ny = (G == 4 ? 1 : 2) * a.sl.k2n;
     const int per = (nx * ny + 7) / 8;
     const int g = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per || g >= nx * ny) return;
     c2<T>* buf = reinterpret_cast<c2<T>*>(smem_raw);                            // [L][12 G + 1]
     c2<T>* tws = buf + (((size_t)p.L * Z::S + 1) & ~(size_t)1);                  // [L]
     c2<T>* tab = tws + p.L;                                                     // [n3 + 1][ROW], 16-byte aligned
-    const int i0 = (g % nx) * a.nq, j0 = g / nx;
-    const int nq = min(a.nq, nk1 - i0);
-    const int k1 = i0 <= n1 ? i0 : a.L1 - i0, k2 = j0 <= n2 ? j0 : a.L2 - j0;
-    Z z{a,    p,  blk, V + ((long)k2 * 10 * Z::NC * (n1 + 1) + k1) * a.rs,
+    // the slab's positions, and after them (groups of one pencil along x, of
+    // one or two along y) their mirrors, where they have one
+    const int ix = (g % nx) * a.nq, jy = g / nx;
+    const bool mx = ix >= a.sl.k1n && G == 1, my = jy >= a.sl.k2n;
+    const int k1 = a.sl.k10 + (mx ? ix - a.sl.k1n : ix), k2 = a.sl.k20 + (my ? jy - a.sl.k2n : jy);
+    if ((mx && (k1 == 0 || k1 == n1)) || (my && (k2 == 0 || k2 == n2))) return;
+    const int i0 = mx ? a.L1 - k1 : k1, j0 = my ? a.L2 - k2 : k2;
+    const int nq = min(a.nq, nk1 - ix);
+    Z z{a,    p,  blk, V + ((long)(k2 - a.sl.k20) * 10 * Z::NC * a.sl.k1n + k1 - a.sl.k10) * a.rs,
         buf,  tab, tws, (int)threadIdx.x, (int)blockDim.x,
         k1,   k2, i0,  j0, G >= 2 && k1 > 0 && k1 < n1, G == 4 && k2 > 0 && k2 < n2};
     c2<T> v[8], hold[kPwlHold];
@@ -575,30 +592,46 @@ int pwl_op_nc(const vie_pwl_op& P)
     return P.fam ? pwl_nc<1>() : pwl_nc<0>();
 }
 
-// largest z rank of the stored tensors, in whole batches of sixteen
+// V's row length: the largest z rank of the stored tensors, in whole fours, so
+// that the z pass reads and sums four at a time without a branch
 int pwl_v_stride(const vie_pwl_op& P)
 {
     int rs = 1;
     for (int b = 0; b < 10; ++b)
         for (int c = P.fam ? 3 : 0; c < 6; ++c) rs = std::max(rs, P.blk[b]->d.view.r[c][2]);
-    return (rs + 15) & ~15;
+    return (rs + 3) & ~3;
 }
 
-// complex elements of the V rows
-size_t pwl_v_elems(const vie_pwl_op& P)
+// complex elements of the V rows of k1n k1 and k2n k2
+size_t pwl_v_elems(const vie_pwl_op& P, int k1n, int k2n)
 {
-    const OpView& v = P.blk[0]->d.view;
-    return (size_t)(v.n[0] + 1) * (v.n[1] + 1) * 10 * pwl_op_nc(P) * pwl_v_stride(P);
+    return (size_t)k1n * k2n * 10 * pwl_op_nc(P) * pwl_v_stride(P) + kPwlPast;
 }
+
+size_t pwl_s2_elems(const OpView& v, int nrhs) { return (size_t)12 * v.L[1] * v.L[0] * v.n[2] * nrhs; }
+size_t pwl_s1_elems(const OpView& v, int nrhs) { return (size_t)12 * v.n[2] * v.L[0] * v.n[1] * nrhs; }
 
 // S2, then S1, in whose place the V rows live while S1 is dead (between Y+ and
-// Y-); they exceed it only where the z ranks come near 0.4 n3
+// Y-).  They exceed it where the z ranks come near 0.4 n3; S1 then grows to
+// hold them, but to three times its size at most (ranks of n3 take 2.5; padded
+// rows on grids of five voxels along z and fewer would take up to ten) where
+// that is more than kPwlGrow elements.
+constexpr size_t kPwlGrow = (size_t)1 << 17;
 size_t pwl_ws_elems(const vie_pwl_op& P, int nrhs)
 {
     const OpView& v = P.blk[0]->d.view;
-    const size_t nb = 4 * (size_t)nrhs;
-    const size_t s2 = (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nb, s1 = (size_t)3 * v.n[2] * v.L[0] * v.n[1] * nb;
-    return s2 + std::max(s1, pwl_v_elems(P));
+    const size_t s1 = pwl_s1_elems(v, nrhs), all = pwl_v_elems(P, v.n[0] + 1, v.n[1] + 1);
+    return pwl_s2_elems(v, nrhs) + std::max(s1, std::min(all, std::max(3 * s1, kPwlGrow)));
+}
+
+// the least that a product runs in: S1 as it is (and room for one row of every
+// tensor), with the z pass in slabs of (k1, k2), which costs launches and a
+// last round of workgroups each: 64 x 64 x 2 complex64 229 us in one piece, 237
+// in two
+size_t pwl_ws_least(const vie_pwl_op& P, int nrhs)
+{
+    const OpView& v = P.blk[0]->d.view;
+    return pwl_s2_elems(v, nrhs) + std::max(pwl_s1_elems(v, nrhs), pwl_v_elems(P, 1, 1));
 }
 
 template <typename T, int FAM, bool CONJ, int G, int PB>
@@ -612,7 +645,7 @@ bool try_pwl_z(const DeviceOp& op, int max_pb, PwlZArgs za, const MixPlan& p, c2
     // the pace of a single one; not where the table tasks exceed what the
     // wavefronts can hold, or where the grid would drop below two workgroups
     // per CU
-    const int nk1 = G >= 2 ? v.n[0] + 1 : v.L[0], ny = G == 4 ? v.n[1] + 1 : v.L[1];
+    const int nk1 = (G >= 2 ? 1 : 2) * za.sl.k1n, ny = (G == 4 ? 1 : 2) * za.sl.k2n;
     const int tasks = 10 * pwl_nc<FAM>() * ((v.n[2] + 64) / 64);
     int waves = (G * v.L[2] + 63) / 64;
     za.nq = 1;
@@ -642,7 +675,7 @@ bool try_pwl_shapes(const DeviceOp& op, int max_pb, const PwlZArgs& za, const Mi
 }
 
 template <typename T>
-hipError_t launch_pwl_z(const vie_pwl_op& P, int conj, c2<T>* S2, c2<T>* V, int nrhs, hipStream_t s,
+hipError_t launch_pwl_z(const vie_pwl_op& P, int conj, c2<T>* S2, c2<T>* V, size_t vcap, int nrhs, hipStream_t s,
                         std::string& err)
 {
     const DeviceOp& op = P.blk[0]->d;
@@ -674,34 +707,52 @@ hipError_t launch_pwl_z(const vie_pwl_op& P, int conj, c2<T>* S2, c2<T>* V, int 
     const size_t vlds = v_rows_lds<T>(P.rmax, za.rs);
     auto kv = P.fam ? k_pwl_v<T, 1> : k_pwl_v<T, 0>;
     (void)hipFuncSetAttribute((const void*)kv, hipFuncAttributeMaxDynamicSharedMemorySize, (int)vlds);
-    hipLaunchKernelGGL(kv, dim3(v.n[1] + 1, 10 * nc), dim3(kVNT), vlds, s, blk, P.rmax, za.rs, V);
-    constexpr auto shapes = std::make_integer_sequence<int, (int)std::size(kPwlShapes<T>)>{};
-    for (int m : {max_pb, 10}) {   // an override that no shape serves is left out
-        const bool ok = P.fam  ? try_pwl_shapes<T, 1, false>(op, m, za, p, S2, tw, blk, V, s, shapes)
-                        : conj ? try_pwl_shapes<T, 0, true>(op, m, za, p, S2, tw, blk, V, s, shapes)
-                               : try_pwl_shapes<T, 0, false>(op, m, za, p, S2, tw, blk, V, s, shapes);
-        if (ok) return hipGetLastError();
+    // slabs: all k1 of as many k2 as V has room for, or part of one k2's k1
+    const int n1p1 = v.n[0] + 1, n2p1 = v.n[1] + 1;
+    const size_t rows = vcap < kPwlPast ? 0 : (vcap - kPwlPast) / ((size_t)10 * nc * za.rs);
+    if (rows < 1) {
+        err = "the workspace has no room for a row of V";
+        return hipErrorInvalidValue;
     }
-    err = "the piecewise-linear z pass does not fit in LDS (z length too large)";
-    return hipErrorInvalidValue;
+    const int k1n = (int)std::min<size_t>(rows, n1p1), k2n = (int)std::min<size_t>(rows / k1n, n2p1);
+    constexpr auto shapes = std::make_integer_sequence<int, (int)std::size(kPwlShapes<T>)>{};
+    auto slab = [&]() {
+        hipLaunchKernelGGL(kv, dim3(za.sl.k2n, 10 * nc), dim3(kVNT), vlds, s, blk, P.rmax, za.rs, za.sl, V);
+        for (int m : {max_pb, 10}) {   // an override that no shape serves is left out
+            const bool ok = P.fam  ? try_pwl_shapes<T, 1, false>(op, m, za, p, S2, tw, blk, V, s, shapes)
+                            : conj ? try_pwl_shapes<T, 0, true>(op, m, za, p, S2, tw, blk, V, s, shapes)
+                                   : try_pwl_shapes<T, 0, false>(op, m, za, p, S2, tw, blk, V, s, shapes);
+            if (ok) return hipGetLastError();
+        }
+        err = "the piecewise-linear z pass does not fit in LDS (z length too large)";
+        return hipErrorInvalidValue;
+    };
+    for (int k20 = 0; k20 < n2p1; k20 += k2n)
+        for (int k10 = 0; k10 < n1p1; k10 += k1n) {
+            za.sl = {k10, std::min(k1n, n1p1 - k10), k20, std::min(k2n, n2p1 - k20)};
+            const hipError_t e = slab();
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
 }
 
 // TV: vector element type, T: compute type (T = float with TV = double: the
 // FP32 products on FP64 vectors of a refined solve)
 template <typename TV, typename T>
 hipError_t pwl_matvec(const vie_pwl_op& P, int mode, const c2<TV>* eps, const c2<TV>* x, c2<TV>* y, c2<T>* ws,
-                      int nrhs, hipStream_t s, std::string& err)
+                      size_t ws_elems, int nrhs, hipStream_t s, std::string& err)
 {
     const DeviceOp& op = P.blk[0]->d;
     const OpView& v = op.view;
     const int nb = 4 * nrhs;   // groups of three components through the pulse passes
+    const size_t s2 = pwl_s2_elems(v, nrhs);
     c2<T>* S2 = ws;
-    c2<T>* S1 = ws + (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nb;
+    c2<T>* S1 = ws + s2;
     const bool conj = (mode == MODE_AH || mode == MODE_NH);
     // X+ : x -> S1, Y+ : S1 -> S2, Z : S2 in place, Y- : S2 -> S1, X- : S1 -> y
     hipError_t e = run_pass<TV, T>(op, 0, mode, 0, eps, x, nullptr, S1, nb, s, nullptr, err, false, nullptr, 0);
     if (e == hipSuccess) e = run_pass<TV, T>(op, 1, mode, 0, eps, x, S1, S2, nb, s, nullptr, err, false, nullptr, 0);
-    if (e == hipSuccess) e = launch_pwl_z<T>(P, conj ? 1 : 0, S2, S1, nrhs, s, err);
+    if (e == hipSuccess) e = launch_pwl_z<T>(P, conj ? 1 : 0, S2, S1, ws_elems - s2, nrhs, s, err);
     if (e == hipSuccess) e = run_pass<TV, T>(op, 3, mode, 0, eps, x, S2, S1, nb, s, nullptr, err, false, nullptr, 0);
     if (e == hipSuccess) e = run_pass<TV, T>(op, 4, mode, 0, eps, x, S1, y, nb, s, nullptr, err, false, nullptr, 0);
     return e;
@@ -710,18 +761,38 @@ hipError_t pwl_matvec(const vie_pwl_op& P, int mode, const c2<TV>* eps, const c2
 }  // namespace
 
 namespace vie {
-// FP32 products on complex128 vectors (refined solves); ws as for VIE_C128
+size_t pwl_workspace_least(const vie_pwl_op* op, int dtype, int nrhs)
+{
+    if (!op || !op->blk[0] || nrhs < 1) return 0;
+    return pwl_ws_least(*op, nrhs) * (dtype == VIE_C128 ? sizeof(c2<double>) : sizeof(c2<float>));
+}
+
+// FP32 products on complex128 vectors (refined solves)
 vie_status pwl_apply_mixed(const vie_pwl_op* op, int mode, const void* eps, const void* x, void* y, void* ws,
-                           hipStream_t s)
+                           size_t ws_bytes, hipStream_t s)
 {
     std::string err;
     hipError_t e = pwl_matvec<double, float>(*op, mode, (const c2<double>*)eps, (const c2<double>*)x, (c2<double>*)y,
-                                             (c2<float>*)ws, 1, s, err);
+                                             (c2<float>*)ws, ws_bytes / sizeof(c2<float>), 1, s, err);
     if (e != hipSuccess) {
         if (!err.empty()) return fail(VIE_E_UNSUPPORTED, "vie_solve_pwl: " + err);
         return hip_fail(e, "vie_solve_pwl launch");
     }
     return VIE_OK;
+}
+
+static size_t jm_pwl_ws_bytes(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype,
+                              size_t (*of)(const vie_pwl_op*, int, int))
+{
+    if (!op_n || !op_k || !op_n->blk[0] || !op_k->blk[0] || (dtype != VIE_C64 && dtype != VIE_C128)) return 0;
+    const OpView& v = op_n->blk[0]->d.view;
+    const size_t vec = (size_t)2 * 12 * v.n[0] * v.n[1] * v.n[2] * (dtype == VIE_C128 ? 16 : 8);
+    return 2 * al256(vec) + std::max(of(op_n, dtype, 2), of(op_k, dtype, 2));
+}
+
+size_t jm_pwl_workspace_least(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype)
+{
+    return jm_pwl_ws_bytes(op_n, op_k, dtype, pwl_workspace_least);
 }
 }  // namespace vie
 
@@ -758,7 +829,7 @@ vie_status vie_matvec_pwl(const vie_pwl_op* op, int kind, int adjoint, int dtype
     if (op->fam != 0 && (kind != VIE_OP_N || adjoint != 0))
         return fail(VIE_E_UNSUPPORTED, "vie_matvec_pwl: a K operator has the bare forward product (VIE_OP_N) only");
     if (kind == VIE_OP_A && !eps_c) return fail(VIE_E_ARG, "vie_matvec_pwl: eps_c is required for VIE_OP_A");
-    if (ws_bytes < vie_pwl_workspace_bytes(op, dtype, nrhs))
+    if (ws_bytes < pwl_workspace_least(op, dtype, nrhs))
         return fail(VIE_E_ARG, "vie_matvec_pwl: workspace too small");
     const OpView& v = op->blk[0]->d.view;
     const size_t vbytes = (size_t)nrhs * 12 * v.n[0] * v.n[1] * v.n[2] * (dtype == VIE_C128 ? 16 : 8);
@@ -770,9 +841,11 @@ vie_status vie_matvec_pwl(const vie_pwl_op* op, int kind, int adjoint, int dtype
     std::string err;
     hipError_t e = dtype == VIE_C128
                        ? pwl_matvec<double, double>(*op, mode, (const c2<double>*)eps_c, (const c2<double>*)x,
-                                                    (c2<double>*)y, (c2<double>*)ws, nrhs, s, err)
+                                                    (c2<double>*)y, (c2<double>*)ws, ws_bytes / sizeof(c2<double>),
+                                                    nrhs, s, err)
                        : pwl_matvec<float, float>(*op, mode, (const c2<float>*)eps_c, (const c2<float>*)x,
-                                                  (c2<float>*)y, (c2<float>*)ws, nrhs, s, err);
+                                                  (c2<float>*)y, (c2<float>*)ws, ws_bytes / sizeof(c2<float>), nrhs,
+                                                  s, err);
     if (e != hipSuccess) {
         if (!err.empty()) return fail(VIE_E_UNSUPPORTED, "vie_matvec_pwl: " + err);
         return hip_fail(e, "vie_matvec_pwl launch");
@@ -782,11 +855,7 @@ vie_status vie_matvec_pwl(const vie_pwl_op* op, int kind, int adjoint, int dtype
 
 size_t vie_jm_pwl_workspace_bytes(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype)
 {
-    if (!op_n || !op_k || !op_n->blk[0] || !op_k->blk[0] || (dtype != VIE_C64 && dtype != VIE_C128)) return 0;
-    const OpView& v = op_n->blk[0]->d.view;
-    const size_t vec = (size_t)2 * 12 * v.n[0] * v.n[1] * v.n[2] * (dtype == VIE_C128 ? 16 : 8);
-    const size_t mv = std::max(vie_pwl_workspace_bytes(op_n, dtype, 2), vie_pwl_workspace_bytes(op_k, dtype, 2));
-    return 2 * al256(vec) + mv;
+    return jm_pwl_ws_bytes(op_n, op_k, dtype, vie_pwl_workspace_bytes);
 }
 
 vie_status vie_matvec_jm_pwl(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype, double h, double omega,
@@ -802,7 +871,7 @@ vie_status vie_matvec_jm_pwl(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int
     for (int a = 0; a < 3; ++a)
         if (op_k->blk[0]->d.view.n[a] != v.n[a]) return fail(VIE_E_ARG, "vie_matvec_jm_pwl: N and K grids differ");
     if (dtype != VIE_C64 && dtype != VIE_C128) return fail(VIE_E_ARG, "vie_matvec_jm_pwl: bad dtype");
-    if (ws_bytes < vie_jm_pwl_workspace_bytes(op_n, op_k, dtype))
+    if (ws_bytes < jm_pwl_workspace_least(op_n, op_k, dtype))
         return fail(VIE_E_ARG, "vie_matvec_jm_pwl: workspace too small");
     const long nv = (long)v.n[0] * v.n[1] * v.n[2];
     const size_t vec = (size_t)2 * 12 * nv * (dtype == VIE_C128 ? 16 : 8);
@@ -820,10 +889,10 @@ vie_status vie_matvec_jm_pwl(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int
         // FP64 vectors, products in FP32 (the inner operator of a refined solve)
         std::string err;
         hipError_t he = pwl_matvec<double, float>(*op_n, MODE_N, nullptr, (const c2<double>*)x, (c2<double>*)NX,
-                                                  (c2<float>*)mw, 2, s, err);
+                                                  (c2<float>*)mw, mb / sizeof(c2<float>), 2, s, err);
         if (he == hipSuccess)
             he = pwl_matvec<double, float>(*op_k, MODE_N, nullptr, (const c2<double>*)x, (c2<double>*)KX,
-                                           (c2<float>*)mw, 2, s, err);
+                                           (c2<float>*)mw, mb / sizeof(c2<float>), 2, s, err);
         if (he != hipSuccess)
             return err.empty() ? hip_fail(he, "vie_matvec_jm_pwl") : fail(VIE_E_UNSUPPORTED, "vie_matvec_jm_pwl: " + err);
     } else {
