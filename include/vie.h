@@ -408,7 +408,9 @@ vie_status vie_op_set_nhat(vie_op* op, int source);
 /* Device workspace (bytes) of vie_matvec / vie_matvec_adjoint for `nrhs`
  * right-hand sides at precision `dtype`: 18 n1 n2 n3 complex per rhs, which
  * is also the least they accept, and more where the z rank comes near n3 (the
- * z pass then takes such a grid in one piece instead of several). */
+ * z pass then takes such a grid in one piece instead of several).  The other
+ * products, the solves and vie_autotune, whose workspaces hold this one,
+ * accept the difference less as well. */
 size_t vie_workspace_bytes(const vie_op* op, int dtype, int nrhs);
 
 /*
@@ -450,7 +452,7 @@ vie_status vie_matvec_adjoint(const vie_op* op, int kind, int dtype, int recon, 
  * process ends.  The caller still passes eps_c, x and y as for vie_matvec
  * (same layouts, kinds, dtypes, recon values and results: the same kernels
  * run).  The current device must be the operator's device.
- * Limit: vie_workspace_bytes(op, dtype, nrhs) <= VIE_NOALLOC_SCRATCH_BYTES
+ * Limit: 18 n1 n2 n3 complex per rhs <= VIE_NOALLOC_SCRATCH_BYTES
  * (e.g. a 96 x 112 x 128 grid with one complex64 right-hand side, 198 MB);
  * larger requests return VIE_E_ARG before any launch.  No part of the
  * scratch needs to start at zero: every pass writes all of what the next

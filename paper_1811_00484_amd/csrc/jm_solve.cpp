@@ -23,6 +23,7 @@ vie_status fail(vie_status st, const std::string& msg);
 vie_status hip_fail(hipError_t e, const char* where);
 vie_status pwl_apply_mixed(const vie_pwl_op* op, int mode, const void* eps, const void* x, void* y, void* ws,
                            size_t ws_bytes, hipStream_t s);
+size_t jm_workspace_least(const vie_op* op_n, const vie_op* op_k, int dtype);
 size_t pwl_workspace_least(const vie_pwl_op* op, int dtype, int nrhs);
 size_t jm_pwl_workspace_least(const vie_pwl_op* op_n, const vie_pwl_op* op_k, int dtype);
 
@@ -65,10 +66,11 @@ KLayout k_layout(long n, size_t opws, int dtype, int m)
     return L;
 }
 
-KLayout jm_layout(const vie_op* op_n, const vie_op* op_k, int dtype, int m)
+// opws: the product's workspace (vie_jm_workspace_bytes or the least)
+KLayout jm_layout(const vie_op* op_n, size_t opws, int dtype, int m)
 {
     const OpView& v = op_n->d.view;
-    return k_layout(6L * v.n[0] * v.n[1] * v.n[2], vie_jm_workspace_bytes(op_n, op_k, dtype), dtype, m);
+    return k_layout(6L * v.n[0] * v.n[1] * v.n[2], opws, dtype, m);
 }
 
 // GMRES(m) on n unknowns: apply(in, out) is the operator (the restart
@@ -219,13 +221,12 @@ vie_status gmres_run(long n, const KLayout& L, FA apply, FI apply_inner, bool re
 template <typename TK>
 vie_status run_jm(const vie_op* op_n, const vie_op* op_k, int dtype, double h, double omega, const void* eps_c,
                   const void* mu_c, const c2<TK>* b, c2<TK>* x, const vie_solve_opts& o, vie_solve_info* info,
-                  char* ws, hipStream_t st)
+                  char* ws, size_t jwb, hipStream_t st)
 {
     const OpView& v = op_n->d.view;
     const long n = 6L * v.n[0] * v.n[1] * v.n[2];
-    const KLayout L = jm_layout(op_n, op_k, dtype, o.restart);
+    const KLayout L = jm_layout(op_n, jwb, dtype, o.restart);
     void* jw = ws + L.op;
-    const size_t jwb = vie_jm_workspace_bytes(op_n, op_k, dtype);
     // refinement (o.refine, complex128 vectors): the Arnoldi steps use the
     // operator with FP32 products, the restart residual the FP64 one
     const bool refine = o.refine && sizeof(TK) == 8;
@@ -240,7 +241,6 @@ vie_status run_jm(const vie_op* op_n, const vie_op* op_k, int dtype, double h, d
     return gmres_run<TK>(n, L, apply, apply_inner, refine, b, x, o, info, ws, st, "vie_solve_jm");
 }
 
-// opws: the product's workspace (vie_pwl_workspace_bytes or the least)
 KLayout pwl_layout(const vie_pwl_op* op, size_t opws, int dtype, int m)
 {
     const OpView& v = op->blk[0]->d.view;
@@ -306,7 +306,7 @@ size_t vie_solve_jm_workspace_bytes(const vie_op* op_n, const vie_op* op_k, int 
     if (!op_n || !op_k || (dtype != VIE_C64 && dtype != VIE_C128)) return 0;
     const int m = opts ? opts->restart : 50;
     if (m < 1 || m > 200) return 0;
-    return jm_layout(op_n, op_k, dtype, m).total;
+    return jm_layout(op_n, vie_jm_workspace_bytes(op_n, op_k, dtype), dtype, m).total;
 }
 
 vie_status vie_solve_jm(const vie_op* op_n, const vie_op* op_k, int dtype, double h, double omega, const void* eps_c,
@@ -332,15 +332,18 @@ vie_status vie_solve_jm(const vie_op* op_n, const vie_op* op_k, int dtype, doubl
     if (dtype != VIE_C64 && dtype != VIE_C128) return fail(VIE_E_ARG, "vie_solve_jm: bad dtype");
     if (o.refine && (dtype != VIE_C128 || !(o.inner_tol > 0 && o.inner_tol < 1)))
         return fail(VIE_E_ARG, "vie_solve_jm: refinement needs VIE_C128 vectors and inner_tol in (0, 1)");
-    if (ws_bytes < vie_solve_jm_workspace_bytes(op_n, op_k, dtype, &o))
+    // a product in less workspace than it asks for goes through in slabs
+    size_t jwb = vie_jm_workspace_bytes(op_n, op_k, dtype);
+    if (ws_bytes < jm_layout(op_n, jwb, dtype, o.restart).total) jwb = jm_workspace_least(op_n, op_k, dtype);
+    if (ws_bytes < jm_layout(op_n, jwb, dtype, o.restart).total)
         return fail(VIE_E_ARG, "vie_solve_jm: workspace too small");
     if (info && info->history && info->hist_cap < 0) return fail(VIE_E_ARG, "vie_solve_jm: bad history capacity");
     hipStream_t st = (hipStream_t)stream;
     if (dtype == VIE_C128)
         return run_jm<double>(op_n, op_k, dtype, h, omega, eps_c, mu_c, (const c2<double>*)b, (c2<double>*)x, o, info,
-                              (char*)ws, st);
+                              (char*)ws, jwb, st);
     return run_jm<float>(op_n, op_k, dtype, h, omega, eps_c, mu_c, (const c2<float>*)b, (c2<float>*)x, o, info,
-                         (char*)ws, st);
+                         (char*)ws, jwb, st);
 }
 
 size_t vie_solve_pwl_workspace_bytes(const vie_pwl_op* op, int dtype, const vie_solve_opts* opts)
@@ -373,7 +376,6 @@ vie_status vie_solve_pwl(const vie_pwl_op* op, int dtype, const void* eps_c, con
         return fail(VIE_E_ARG, "vie_solve_pwl: refinement needs VIE_C128 vectors and inner_tol in (0, 1)");
     if (o.refine && o.inner_recon != VIE_RECON_FP32)
         return fail(VIE_E_UNSUPPORTED, "vie_solve_pwl: refinement takes FP32 inner products only");
-    // the product in less workspace than it asks for goes through in slabs
     size_t pwb = vie_pwl_workspace_bytes(op, dtype, 1);
     if (ws_bytes < pwl_layout(op, pwb, dtype, o.restart).total) pwb = pwl_workspace_least(op, dtype, 1);
     if (ws_bytes < pwl_layout(op, pwb, dtype, o.restart).total)

@@ -912,7 +912,8 @@ hipError_t launch_densify(DeviceOp& op, int with_c128, hipStream_t s)
     return hipGetLastError();
 }
 
-// Whether every instance has register-FFT kernels for all five passes.
+// Whether every instance has register-FFT kernels for all five passes and
+// room for its V rows.
 template <typename T>
 static bool batch_grouped_ok(const std::vector<InstHost>& req, int recon)
 {
@@ -925,6 +926,8 @@ static bool batch_grouped_ok(const std::vector<InstHost>& req, int recon)
         if (op.nhat_source == 1 && (sizeof(T) == 8 ? (const void*)op.dense64 : (const void*)op.dense32) == nullptr)
             return false;
         if (recon == 1 && (sizeof(T) != 4 || !bf16_recon_available(op))) return false;
+        // the grouped z pass takes every instance's V rows in one piece
+        if (op.nhat_source != 1 && h.ws_bytes < (s2_elems(v, h.nact) + zv_elems(v)) * sizeof(c2<T>)) return false;
     }
     return true;
 }
@@ -1029,8 +1032,8 @@ hipError_t launch_batch(const std::vector<InstHost>& req, int mode, int recon, I
     if (req.size() == 1 || g_batch_mode == 0) {
         for (const InstHost& h : req) {
             hipError_t e = launch_matvec<TV, T>(*h.op, mode, recon, (const c2<TV>*)h.eps, (const c2<TV>*)h.x,
-                                                (c2<TV>*)h.y, h.nact, (c2<T>*)h.ws, matvec_ws_elems(*h.op, h.nact), st, h.map,
-                                                err);
+                                                (c2<TV>*)h.y, h.nact, (c2<T>*)h.ws, h.ws_bytes / sizeof(c2<T>), st,
+                                                h.map, err);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;

@@ -37,17 +37,20 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct Layout {
     size_t V, R, mws, partial, h1, h2, coef, nrm, map, total;
+    size_t mws_bytes;
 };
 
-Layout layout(const DeviceOp& op, int dtype, int nrhs, int m, int refine)
+// least: the product's workspace at its least
+Layout layout(const DeviceOp& op, int dtype, int nrhs, int m, int refine, bool least)
 {
     const OpView& v = op.view;
     long n = 3L * v.n[0] * v.n[1] * v.n[2];
     size_t ek = dtype == VIE_C128 ? 16 : 8;
-    size_t mv_el = matvec_ws_elems(op, nrhs);
+    size_t mv_el = least ? matvec_ws_least(op, nrhs) : matvec_ws_elems(op, nrhs);
     size_t mv_bytes = mv_el * (dtype == VIE_C128 && !refine ? 16 : 8);
     if (refine) mv_bytes = mv_el * 16;   // FP64 residual matvec; the FP32 inner matvec uses half of it
     Layout L;
+    L.mws_bytes = mv_bytes;
     size_t off = 0;
     L.V = off;
     off += align256((size_t)(m + 1) * nrhs * n * ek);
@@ -212,7 +215,7 @@ vie_status run_multi(std::vector<Inst<TK>>& I, int mode, const vie_solve_opts& o
                 if (!in.conv[s]) act[i].push_back(s);
             if (act[i].empty()) continue;
             if ((e = upload_map(in, act[i])) != hipSuccess) return hip_fail(e, "vie_solve map");
-            req.push_back({in.op, in.x, in.R, in.eps, in.dmap, (int)act[i].size(), in.mws});
+            req.push_back({in.op, in.x, in.R, in.eps, in.dmap, (int)act[i].size(), in.mws, in.Lt.mws_bytes});
         }
         if (req.empty()) break;
         if (o.refine) {
@@ -275,7 +278,7 @@ vie_status run_multi(std::vector<Inst<TK>>& I, int mode, const vie_solve_opts& o
                 const long vstride = (long)in.nrhs * in.n;
                 if ((e = upload_map(in, in.run)) != hipSuccess) return hip_fail(e, "vie_solve map");
                 req.push_back({in.op, in.V + (long)j * vstride, in.V + (long)(j + 1) * vstride, in.eps, in.dmap,
-                               (int)in.run.size(), in.mws});
+                               (int)in.run.size(), in.mws, in.Lt.mws_bytes});
             }
             if (req.empty()) break;
             if ((e = mv_dispatch<TK, TC>(req, mode, tab, st, err, inner_recon)) != hipSuccess)
@@ -444,16 +447,17 @@ vie_solve_opts defaults(const vie_solve_opts* o)
 
 // total workspace of a multi-instance solve: one instance table, then each
 // instance's own layout, 256-byte aligned
-size_t multi_ws_bytes(const vie_solve_instance* in, int count, int dtype, const vie_solve_opts& o)
+size_t multi_ws_bytes(const vie_solve_instance* in, int count, int dtype, const vie_solve_opts& o, bool least)
 {
     size_t tot = align256(sizeof(InstDev) * (size_t)count);
-    for (int i = 0; i < count; ++i) tot += align256(layout(in[i].op->d, dtype, in[i].nrhs, o.restart, o.refine).total);
+    for (int i = 0; i < count; ++i)
+        tot += align256(layout(in[i].op->d, dtype, in[i].nrhs, o.restart, o.refine, least).total);
     return tot;
 }
 
 template <typename TK, typename TC>
 vie_status solve_typed(const vie_solve_instance* in, int count, int dtype, const vie_solve_opts& o, int mode, char* ws,
-                       hipStream_t st)
+                       bool least, hipStream_t st)
 {
     std::vector<Inst<TK>> I(count);
     InstDev* tab = (InstDev*)ws;
@@ -467,7 +471,7 @@ vie_status solve_typed(const vie_solve_instance* in, int count, int dtype, const
         d.nrhs = in[i].nrhs;
         d.info = in[i].info;
         d.n = 3L * d.op->view.n[0] * d.op->view.n[1] * d.op->view.n[2];
-        d.Lt = layout(*d.op, dtype, d.nrhs, o.restart, o.refine);
+        d.Lt = layout(*d.op, dtype, d.nrhs, o.restart, o.refine, least);
         bind_ws(d, ws + off);
         off += align256(d.Lt.total);
     }
@@ -475,11 +479,14 @@ vie_status solve_typed(const vie_solve_instance* in, int count, int dtype, const
 }
 
 vie_status solve_instances(const vie_solve_instance* in, int count, int dtype, const vie_solve_opts& o, int mode,
-                           char* ws, hipStream_t st)
+                           char* ws, size_t ws_bytes, hipStream_t st)
 {
-    if (dtype == VIE_C64) return solve_typed<float, float>(in, count, dtype, o, mode, ws, st);
-    if (o.refine) return solve_typed<double, float>(in, count, dtype, o, mode, ws, st);
-    return solve_typed<double, double>(in, count, dtype, o, mode, ws, st);
+    // a workspace below what was asked for: the products go through their z
+    // pass in slabs
+    const bool least = ws_bytes < multi_ws_bytes(in, count, dtype, o, false);
+    if (dtype == VIE_C64) return solve_typed<float, float>(in, count, dtype, o, mode, ws, least, st);
+    if (o.refine) return solve_typed<double, float>(in, count, dtype, o, mode, ws, least, st);
+    return solve_typed<double, double>(in, count, dtype, o, mode, ws, least, st);
 }
 
 }  // namespace
@@ -495,7 +502,7 @@ size_t vie_solve_workspace_bytes(const vie_op* op, int dtype, int nrhs, const vi
     vie_solve_opts o = defaults(opts);
     if (o.restart < 1 || o.restart > 200) return 0;
     vie_solve_instance one{op, nullptr, nullptr, nullptr, nrhs, nullptr};
-    return multi_ws_bytes(&one, 1, dtype, o);
+    return multi_ws_bytes(&one, 1, dtype, o, false);
 }
 
 vie_status vie_solve(const vie_op* op, int dtype, const void* eps_c, const void* b, void* x, int nrhs,
@@ -513,7 +520,7 @@ vie_status vie_solve(const vie_op* op, int dtype, const void* eps_c, const void*
         return fail(VIE_E_ARG, "vie_solve: inner_recon must be VIE_RECON_FP32 or VIE_RECON_BF16");
     {
         vie_solve_instance one{op, nullptr, nullptr, nullptr, nrhs, nullptr};
-        if (ws_bytes < multi_ws_bytes(&one, 1, dtype, o)) return fail(VIE_E_ARG, "vie_solve: workspace too small");
+        if (ws_bytes < multi_ws_bytes(&one, 1, dtype, o, true)) return fail(VIE_E_ARG, "vie_solve: workspace too small");
     }
     const OpView& v = op->d.view;
     size_t vbytes = (size_t)nrhs * 3 * v.n[0] * v.n[1] * v.n[2] * (dtype == VIE_C128 ? 16 : 8);
@@ -523,7 +530,7 @@ vie_status vie_solve(const vie_op* op, int dtype, const void* eps_c, const void*
     int mode = o.adjoint ? MODE_AH : MODE_A;
     hipStream_t st = (hipStream_t)stream;
     vie_solve_instance one{op, eps_c, b, x, nrhs, info};
-    return solve_instances(&one, 1, dtype, o, mode, (char*)ws, st);
+    return solve_instances(&one, 1, dtype, o, mode, (char*)ws, ws_bytes, st);
 }
 
 vie_status vie_field_gradient(const vie_op* op, int dtype, const void* z, const void* E, double omega_eps0,
@@ -642,7 +649,7 @@ size_t vie_solve_multi_workspace_bytes(const vie_solve_instance* inst, int count
     if (o.restart < 1 || o.restart > 200) return 0;
     for (int i = 0; i < count; ++i)
         if (!inst[i].op || inst[i].nrhs < 1) return 0;
-    return multi_ws_bytes(inst, count, dtype, o);
+    return multi_ws_bytes(inst, count, dtype, o, false);
 }
 
 vie_status vie_solve_multi(const vie_solve_instance* inst, int count, int dtype, const vie_solve_opts* opts, void* ws,
@@ -663,20 +670,27 @@ vie_status vie_solve_multi(const vie_solve_instance* inst, int count, int dtype,
         const char* bb = (const char*)in.b;
         if (!(xb + vb <= bb || bb + vb <= xb)) return fail(VIE_E_ARG, "vie_solve_multi: x and b overlap");
     }
-    if (ws_bytes < multi_ws_bytes(inst, count, dtype, o)) return fail(VIE_E_ARG, "vie_solve_multi: workspace too small");
-    return solve_instances(inst, count, dtype, o, o.adjoint ? MODE_AH : MODE_A, (char*)ws, (hipStream_t)stream);
+    if (ws_bytes < multi_ws_bytes(inst, count, dtype, o, true))
+        return fail(VIE_E_ARG, "vie_solve_multi: workspace too small");
+    return solve_instances(inst, count, dtype, o, o.adjoint ? MODE_AH : MODE_A, (char*)ws, ws_bytes,
+                           (hipStream_t)stream);
 }
 
-size_t vie_matvec_multi_workspace_bytes(const vie_instance* inst, int count, int dtype)
+static size_t matvec_multi_bytes(const vie_instance* inst, int count, int dtype, size_t (*elems)(const DeviceOp&, int))
 {
     if (!inst || count < 1) return 0;
     size_t el = dtype == VIE_C128 ? 16 : 8;
     size_t tot = align256(sizeof(InstDev) * (size_t)count);
     for (int i = 0; i < count; ++i) {
         if (!inst[i].op || inst[i].nrhs < 1) return 0;
-        tot += align256(matvec_ws_elems(inst[i].op->d, inst[i].nrhs) * el);
+        tot += align256(elems(inst[i].op->d, inst[i].nrhs) * el);
     }
     return tot;
+}
+
+size_t vie_matvec_multi_workspace_bytes(const vie_instance* inst, int count, int dtype)
+{
+    return matvec_multi_bytes(inst, count, dtype, matvec_ws_elems);
 }
 
 vie_status vie_matvec_multi(const vie_instance* inst, int count, int kind, int adjoint, int dtype, void* ws,
@@ -685,7 +699,8 @@ vie_status vie_matvec_multi(const vie_instance* inst, int count, int kind, int a
     if (!inst || count < 1 || !ws) return fail(VIE_E_ARG, "vie_matvec_multi: bad argument");
     if (kind != VIE_OP_A && kind != VIE_OP_N) return fail(VIE_E_ARG, "vie_matvec_multi: bad kind");
     if (dtype != VIE_C64 && dtype != VIE_C128) return fail(VIE_E_ARG, "vie_matvec_multi: bad dtype");
-    size_t need = vie_matvec_multi_workspace_bytes(inst, count, dtype);
+    auto* elems = ws_bytes < vie_matvec_multi_workspace_bytes(inst, count, dtype) ? matvec_ws_least : matvec_ws_elems;
+    size_t need = matvec_multi_bytes(inst, count, dtype, elems);
     if (need == 0 || ws_bytes < need) return fail(VIE_E_ARG, "vie_matvec_multi: workspace too small");
     int mode = kind == VIE_OP_A ? (adjoint ? MODE_AH : MODE_A) : (adjoint ? MODE_NH : MODE_N);
     size_t eb = dtype == VIE_C128 ? 16 : 8;
@@ -701,8 +716,9 @@ vie_status vie_matvec_multi(const vie_instance* inst, int count, int kind, int a
         const char* xb = (const char*)in.x;
         const char* yb = (const char*)in.y;
         if (!(xb + vb <= yb || yb + vb <= xb)) return fail(VIE_E_ARG, "vie_matvec_multi: x and y overlap");
-        req[i] = {&in.op->d, in.x, in.y, in.eps_c, nullptr, in.nrhs, (char*)ws + off};
-        off += align256(matvec_ws_elems(in.op->d, in.nrhs) * eb);
+        const size_t bytes = elems(in.op->d, in.nrhs) * eb;
+        req[i] = {&in.op->d, in.x, in.y, in.eps_c, nullptr, in.nrhs, (char*)ws + off, bytes};
+        off += align256(bytes);
     }
     std::string err;
     hipError_t e;

@@ -813,6 +813,22 @@ vie_status matvec_common(const vie_op* op, int mode, int dtype, int recon, const
     return VIE_OK;
 }
 
+static size_t align_up256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+static size_t jm_ws_bytes(const vie_op* op_n, const vie_op* op_k, int dtype, size_t (*elems)(const DeviceOp&, int))
+{
+    if (!op_n || !op_k || (dtype != VIE_C64 && dtype != VIE_C128)) return 0;
+    const OpView& v = op_n->d.view;
+    const size_t el = dtype == VIE_C128 ? 16 : 8;
+    const size_t vec = (size_t)2 * 3 * v.n[0] * v.n[1] * v.n[2] * el;
+    return 2 * align_up256(vec) + std::max(elems(op_n->d, 2), elems(op_k->d, 2)) * el;
+}
+
+size_t jm_workspace_least(const vie_op* op_n, const vie_op* op_k, int dtype)
+{
+    return jm_ws_bytes(op_n, op_k, dtype, matvec_ws_least);
+}
+
 }  // namespace vie
 
 extern "C" {
@@ -833,15 +849,9 @@ vie_status vie_matvec_adjoint(const vie_op* op, int kind, int dtype, int recon, 
                          stream, nullptr);
 }
 
-static size_t align_up256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 size_t vie_jm_workspace_bytes(const vie_op* op_n, const vie_op* op_k, int dtype)
 {
-    if (!op_n || !op_k || (dtype != VIE_C64 && dtype != VIE_C128)) return 0;
-    const OpView& v = op_n->d.view;
-    const size_t vec = (size_t)2 * 3 * v.n[0] * v.n[1] * v.n[2] * (dtype == VIE_C128 ? 16 : 8);
-    const size_t mv = std::max(vie_workspace_bytes(op_n, dtype, 2), vie_workspace_bytes(op_k, dtype, 2));
-    return 2 * align_up256(vec) + mv;
+    return jm_ws_bytes(op_n, op_k, dtype, matvec_ws_elems);
 }
 
 vie_status vie_matvec_jm(const vie_op* op_n, const vie_op* op_k, int dtype, double h, double omega, const void* eps_c,
@@ -855,8 +865,7 @@ vie_status vie_matvec_jm(const vie_op* op_n, const vie_op* op_k, int dtype, doub
     for (int a = 0; a < 3; ++a)
         if (op_k->d.view.n[a] != v.n[a]) return fail(VIE_E_ARG, "vie_matvec_jm: N and K grids differ");
     if (dtype != VIE_C64 && dtype != VIE_C128) return fail(VIE_E_ARG, "vie_matvec_jm: bad dtype");
-    const size_t need = vie_jm_workspace_bytes(op_n, op_k, dtype);
-    if (ws_bytes < need) return fail(VIE_E_ARG, "vie_matvec_jm: workspace too small");
+    if (ws_bytes < jm_workspace_least(op_n, op_k, dtype)) return fail(VIE_E_ARG, "vie_matvec_jm: workspace too small");
     const long nv = (long)v.n[0] * v.n[1] * v.n[2];
     const size_t vec = (size_t)2 * 3 * nv * (dtype == VIE_C128 ? 16 : 8);
     const char* xb = (const char*)x;
@@ -874,11 +883,12 @@ vie_status vie_matvec_jm(const vie_op* op_n, const vie_op* op_k, int dtype, doub
         // refined solve)
         std::string err;
         hipError_t he = launch_matvec<double, float>(op_n->d, MODE_N, 0, nullptr, (const c2<double>*)x,
-                                                     (c2<double>*)NX, 2, (c2<float>*)mw, matvec_ws_elems(op_n->d, 2), (hipStream_t)stream,
-                                                     nullptr, err);
+                                                     (c2<double>*)NX, 2, (c2<float>*)mw, mb / sizeof(c2<float>),
+                                                     (hipStream_t)stream, nullptr, err);
         if (he == hipSuccess)
             he = launch_matvec<double, float>(op_k->d, MODE_N, 0, nullptr, (const c2<double>*)x, (c2<double>*)KX, 2,
-                                              (c2<float>*)mw, matvec_ws_elems(op_k->d, 2), (hipStream_t)stream, nullptr, err);
+                                              (c2<float>*)mw, mb / sizeof(c2<float>), (hipStream_t)stream, nullptr,
+                                              err);
         if (he != hipSuccess) return err.empty() ? hip_fail(he, "vie_matvec_jm") : fail(VIE_E_UNSUPPORTED, err);
     } else {
         st = matvec_common(op_n, MODE_N, dtype, VIE_RECON_AUTO, nullptr, x, NX, 2, mw, mb, stream, nullptr);
@@ -1152,7 +1162,8 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
     if (!op || !ws || nrhs < 1) return fail(VIE_E_ARG, "vie_autotune: null argument or nrhs < 1");
     if (op->d.view.fam != 0) return fail(VIE_E_UNSUPPORTED, "vie_autotune: N operators only");
     if (dtype != VIE_C64 && dtype != VIE_C128) return fail(VIE_E_ARG, "vie_autotune: bad dtype");
-    if (ws_bytes < vie_workspace_bytes(op, dtype, nrhs)) return fail(VIE_E_ARG, "vie_autotune: workspace too small");
+    const size_t el = dtype == VIE_C128 ? sizeof(c2<double>) : sizeof(c2<float>);
+    if (ws_bytes < matvec_ws_least(op->d, nrhs) * el) return fail(VIE_E_ARG, "vie_autotune: workspace too small");
     if (ms)
         for (int k = 0; k < 4; ++k) ms[k] = 0.0;
     DeviceOp& d = op->d;
@@ -1160,8 +1171,7 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
     if (chosen) *chosen = d.zchunk;
     if (g_kernel_path != 0 || (v.L[2] != 128 && v.L[2] != 256 && v.L[2] != 512)) return VIE_OK;
     hipStream_t s = (hipStream_t)stream;
-    const size_t el = dtype == VIE_C128 ? sizeof(c2<double>) : sizeof(c2<float>);
-    const size_t s2 = (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nrhs;
+    const size_t s2 = (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nrhs, vcap = ws_bytes / el - s2;
     hipError_t e = hipMemsetAsync(ws, 0, s2 * el, s);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (e == hipSuccess) e = hipEventCreate(&e0);
@@ -1172,11 +1182,9 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
     double best = 1e300;
     auto run = [&]() -> bool {
         if (dtype == VIE_C128)
-            return z_pass_fast<double>(d, MODE_A, 0, nrhs, (c2<double>*)ws, (c2<double>*)ws + s2,
-                                       matvec_ws_elems(d, nrhs) - s2, d.tw64[2],
+            return z_pass_fast<double>(d, MODE_A, 0, nrhs, (c2<double>*)ws, (c2<double>*)ws + s2, vcap, d.tw64[2],
                                        d.d64.fac, d.dense64, s);
-        return z_pass_fast<float>(d, MODE_A, 0, nrhs, (c2<float>*)ws, (c2<float>*)ws + s2, matvec_ws_elems(d, nrhs) - s2,
-                                  d.tw32[2], d.d32.fac,
+        return z_pass_fast<float>(d, MODE_A, 0, nrhs, (c2<float>*)ws, (c2<float>*)ws + s2, vcap, d.tw32[2], d.d32.fac,
                                   d.dense32, s);
     };
     for (int k = 0; k < 4 && e == hipSuccess; ++k) {

@@ -160,7 +160,8 @@ struct InstHost {
     const void* eps;
     const int* map;
     int nact;
-    void* ws;         // matvec workspace of this instance (matvec_ws_elems(op, nact) elements)
+    void* ws;         // matvec workspace of this instance, matvec_ws_least(op, nact) elements or more
+    size_t ws_bytes;
 };
 
 // matvec modes
