@@ -819,16 +819,18 @@ vie_status vie_set_batch_mode(int mode);
  * vie_autotune -- pick the launch shape of the fused z pass for this operator
  * by timing the candidates on the device: the number of consecutive k1
  * mirror quads a workgroup takes (4, 8, 16 or 32; fewer means more
- * workgroups, more means the per-k2 core contraction W_c(k2) is shared by
- * more quads).  The choice is stored in the operator and used by every later
- * matvec and solve on it.
+ * workgroups, more means fewer fills of the twiddle table and longer runs of
+ * loads issued ahead).  The fastest is stored in the operator and used by
+ * every later matvec and solve on it, unless the shape of an operator that
+ * was not tuned (up to 16, halved down to 2 until there are 64 workgroups per
+ * CU) is faster still and stays.
  *   dtype   VIE_C64 or VIE_C128 (the arithmetic tuned for).
  *   nrhs    right-hand sides per launch to tune for.
  *   ws      DEVICE workspace of at least vie_workspace_bytes(op, dtype, nrhs);
  *           overwritten (zeroed, then used as the z-pass buffer).
  *   ms      HOST double[4] out (may be NULL): milliseconds per z pass of the
  *           candidates 4, 8, 16, 32 (0 where not applicable).
- *   chosen  HOST int out (may be NULL): the chosen quads per workgroup.
+ *   chosen  HOST int out (may be NULL): the fastest candidate.
  * Synchronous.  Only the register-FFT z pass (2 n3 = 128, 256, 512) has a
  * tunable shape; for other lengths it returns VIE_OK and changes nothing.
  */

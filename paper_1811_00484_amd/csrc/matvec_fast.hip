@@ -935,11 +935,13 @@ void z_fast_shape(const DeviceOp& op, int nrhs, int k2n, int& chunk, int& nbx, i
 {
     const OpView& v = op.view;
     const int n1p1 = v.n[0] + 1;
-    // a chunk only saves twiddle fills: halve it until the grid holds 64
-    // workgroups per CU, so that the last round is short (the autotuned length
-    // is the limit; 256^3 product 3.32 -> 3.29 ms against sixteen per CU)
-    chunk = op.zchunk;
-    while (chunk > 2 && (long)k2n * ((n1p1 + chunk - 1) / chunk) < 16384) chunk /= 2;
+    // a chunk only saves twiddle fills: unless a tuned length says otherwise,
+    // halve it until the grid holds 64 workgroups per CU, so that the last
+    // round is short (z pass, complex64, at 4, 8, 16 and 32 quads: 64 x 48 x 128
+    // 70, 104, 176 and 335 us, 128^3 244, 253, 269 and 389, 256^3 1595, 1557,
+    // 1618 and 1778)
+    chunk = op.zchunk ? op.zchunk : kZChunk;
+    while (!op.zchunk && chunk > 2 && (long)k2n * ((n1p1 + chunk - 1) / chunk) < 16384) chunk /= 2;
     nbx = k2n * ((n1p1 + chunk - 1) / chunk);
     // right-hand sides share a workgroup's tables as far as the grid holds
     // eight workgroups per CU

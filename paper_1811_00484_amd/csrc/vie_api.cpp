@@ -1168,7 +1168,7 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
         for (int k = 0; k < 4; ++k) ms[k] = 0.0;
     DeviceOp& d = op->d;
     const OpView& v = d.view;
-    if (chosen) *chosen = d.zchunk;
+    if (chosen) *chosen = d.zchunk ? d.zchunk : kZChunk;
     if (g_kernel_path != 0 || (v.L[2] != 128 && v.L[2] != 256 && v.L[2] != 512)) return VIE_OK;
     hipStream_t s = (hipStream_t)stream;
     const size_t s2 = (size_t)3 * v.L[1] * v.L[0] * v.n[2] * nrhs, vcap = ws_bytes / el - s2;
@@ -1176,10 +1176,10 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (e == hipSuccess) e = hipEventCreate(&e0);
     if (e == hipSuccess) e = hipEventCreate(&e1);
-    const int cand[4] = {4, 8, 16, 32};
+    const int cand[5] = {0, 4, 8, 16, 32};   // 0: the shape of an operator that was not tuned
     const int keep = d.zchunk;
     int best_c = keep;
-    double best = 1e300;
+    double best = 1e300, untuned = 1e300;
     auto run = [&]() -> bool {
         if (dtype == VIE_C128)
             return z_pass_fast<double>(d, MODE_A, 0, nrhs, (c2<double>*)ws, (c2<double>*)ws + s2, vcap, d.tw64[2],
@@ -1187,7 +1187,7 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
         return z_pass_fast<float>(d, MODE_A, 0, nrhs, (c2<float>*)ws, (c2<float>*)ws + s2, vcap, d.tw32[2], d.d32.fac,
                                   d.dense32, s);
     };
-    for (int k = 0; k < 4 && e == hipSuccess; ++k) {
+    for (int k = 0; k < 5 && e == hipSuccess; ++k) {
         d.zchunk = cand[k];
         if (!run()) continue;   // shape not launchable (LDS): leave 0
         e = hipEventRecord(e0, s);
@@ -1200,7 +1200,11 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
         if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
         if (e != hipSuccess || !ok) break;
         const double per = (double)t / reps;
-        if (ms) ms[k] = per;
+        if (k == 0) {
+            untuned = per;
+            continue;
+        }
+        if (ms) ms[k - 1] = per;
         if (per < best) {
             best = per;
             best_c = cand[k];
@@ -1208,9 +1212,9 @@ vie_status vie_autotune(vie_op* op, int dtype, int nrhs, void* ws, size_t ws_byt
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    d.zchunk = e == hipSuccess ? best_c : keep;
+    d.zchunk = e != hipSuccess ? keep : untuned < best ? 0 : best_c;
     if (e != hipSuccess) return hip_fail(e, "vie_autotune");
-    if (chosen) *chosen = d.zchunk;
+    if (chosen) *chosen = best_c ? best_c : kZChunk;
     return VIE_OK;
 }
 

@@ -91,7 +91,9 @@ struct DeviceOp {
     size_t device_bytes = 0;   // everything the operator holds on the device
     int device = 0;
     size_t max_lds = 65536;
-    int zchunk = 16;   // k1 mirror quads per z-pass workgroup (vie_autotune)
+    // k1 mirror quads per workgroup of the register-FFT z pass, as vie_autotune
+    // left it (0: by the rule of z_fast_shape)
+    int zchunk = 0;
 };
 
 // Arguments of the register-FFT passes.
@@ -240,6 +242,7 @@ size_t zv_elems(const OpView& v);
 int zv_slab(const OpView& v, size_t cap);
 template <typename T>
 void launch_zv(const DeviceOp& op, c2<T>* V, int k20, int k2n, hipStream_t s);
+constexpr int kZChunk = 16;   // longest run of k1 quads of an operator that was not tuned
 // launch shape of the register-FFT z pass over k2n canonical k2: k1 quads per
 // workgroup, workgroups per share of the right-hand sides, shares
 void z_fast_shape(const DeviceOp& op, int nrhs, int k2n, int& chunk, int& nbx, int& gy);

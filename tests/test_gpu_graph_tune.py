@@ -72,3 +72,14 @@ def test_autotune_keeps_results(dt):
     y1 = vie.matvec(op, x, e).cpu().numpy()
     # each quad is computed by the same code whatever the grouping: identical
     assert np.array_equal(y0, y1)
+
+
+@pytest.mark.parametrize("dt", [torch.complex64, torch.complex128])
+def test_autotune_candidates_reach_different_launches(dt):
+    # 81 k1 quads of two k2: 3 workgroups a k2 of 32 quads or 21 of 4, one
+    # after another in a workgroup, on 256 CUs: eight times the work per
+    # workgroup, of which the z pass's other launch leaves more than half
+    op = vie.compress(problem((80, 1, 64), h=0.003)[0], tol=1e-6)
+    times = [vie.autotune(op, dt, nrhs=1)[1] for _ in range(3)]
+    say("   autotune", dt, times)
+    assert min(t[32] for t in times) >= 1.5 * min(t[4] for t in times)
