@@ -8,6 +8,7 @@
 //           V(j,k) = W(k) U2(j, :)^T          (r1 per (j, k); one workgroup per k)
 //   CP:     V_l(j,k) = lambda_l U2(j, l) U3(k, l) (the 4-D loop of Sec. V-B)
 //   then    D(i,j,k) = U1(i, :) . V(j, k), y = D .* x   (last kernel)
+// Rows of few i have a kernel of their own (k_apply_flat).
 // The last kernel gives a workgroup a tile of i and a run of (j, k) rows: a
 // thread keeps U1(i, :) of its i in registers for the whole run, and the rows
 // V(j, k), the same for every lane, come by scalar loads, so that the inner
@@ -38,6 +39,15 @@ using namespace vie;
 constexpr int kRMax = 32;    // largest rank per mode
 constexpr int kNT = 64;      // threads per workgroup of the apply kernel, one i each
 constexpr int kRun = 32;     // (j, k) rows per workgroup of the apply kernel
+// A lane per i wastes 64 - n1 lanes of short rows: below kShort the flat walk
+// of the (i, j) plane wins at every rank (8 M elements, rank 8 and 25:
+// complex64 n1 = 4 200 -> 94 and 291 -> 187 us, 8 117 -> 66 and 170 -> 119, 15
+// 77 -> 55 and 153 -> 125; complex128 12 154 -> 135 and 317 -> 314, but 15 116
+// -> 117 and 264 -> 288).
+template <typename T>
+constexpr int kShort = sizeof(T) == 4 ? 17 : 13;
+constexpr int kFlatNT = 256; // threads per workgroup of the flat kernel, an (i, j) each
+constexpr int kKT = 16;      // k per thread of it
 
 // V(j, k) of a Tucker form: one workgroup per k contracts the core with
 // U3(k, :) and applies it to every row of U2.
@@ -110,11 +120,42 @@ __global__ void __launch_bounds__(kNT) k_apply(const c2<T>* __restrict__ V, cons
     }
 }
 
+// Rows of fewer than kShort<T> elements: consecutive threads take consecutive
+// (i, j), wrapping into the next j, for kKT consecutive k, and read V(j, k)
+// through the cache.
+template <typename T, int R>
+__global__ void __launch_bounds__(kFlatNT) k_apply_flat(const c2<T>* __restrict__ V, const c2<T>* __restrict__ U1T,
+                                                        const c2<T>* __restrict__ x, c2<T>* __restrict__ y, int n1,
+                                                        int n2, int n3)
+{
+    const int plane = n1 * n2;   // at most 16 x 65535
+    const int p = blockIdx.x * kFlatNT + threadIdx.x;
+    if (p >= plane) return;
+    const int j = p / n1, i = p - j * n1;
+    c2<T> u[R];
+#pragma unroll
+    for (int a = 0; a < R; ++a) u[a] = U1T[(long)a * n1 + i];
+    const int k0 = blockIdx.y * kKT, kend = min(n3, k0 + kKT);
+    for (int k = k0; k < kend; ++k) {
+        const c2<T>* v = V + ((long)k * n2 + j) * R;
+        c2<T> d = mk<T>(0, 0);
+#pragma unroll
+        for (int a = 0; a < R; ++a) fma_c(d, u[a], v[a]);
+        const long o = (long)k * plane + p;
+        y[o] = d * x[o];
+    }
+}
+
 template <typename T, int R>
 void launch_apply(int r, const c2<T>* V, const c2<T>* U1T, const c2<T>* x, c2<T>* y, const int n[3], hipStream_t s)
 {
     if constexpr (R > 1) {
         if (r < R) return launch_apply<T, R - 1>(r, V, U1T, x, y, n, s);
+    }
+    if (n[0] < kShort<T>) {
+        hipLaunchKernelGGL((k_apply_flat<T, R>), dim3((n[0] * n[1] + kFlatNT - 1) / kFlatNT, (n[2] + kKT - 1) / kKT),
+                           dim3(kFlatNT), 0, s, V, U1T, x, y, n[0], n[1], n[2]);
+        return;
     }
     const long rows = (long)n[1] * n[2];
     hipLaunchKernelGGL((k_apply<T, R>), dim3((unsigned)((rows + kRun - 1) / kRun), (n[0] + kNT - 1) / kNT), dim3(kNT), 0,
