@@ -8,7 +8,8 @@
 //           V(j,k) = W(k) U2(j, :)^T          (r1 per (j, k); one workgroup per k)
 //   CP:     V_l(j,k) = lambda_l U2(j, l) U3(k, l) (the 4-D loop of Sec. V-B)
 //   then    D(i,j,k) = U1(i, :) . V(j, k), y = D .* x   (last kernel)
-// Rows of few i have a kernel of their own (k_apply_flat).
+// V of fewer than four columns and rows of few i have kernels of their own
+// (k_vk_few, k_apply_flat).
 // The last kernel gives a workgroup a tile of i and a run of (j, k) rows: a
 // thread keeps U1(i, :) of its i in registers for the whole run, and the rows
 // V(j, k), the same for every lane, come by scalar loads, so that the inner
@@ -21,6 +22,7 @@
 // hold their 25 factors, the scalar loads of V set the pace).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <string>
 
 #include "vie.h"
@@ -48,16 +50,61 @@ template <typename T>
 constexpr int kShort = sizeof(T) == 4 ? 17 : 13;
 constexpr int kFlatNT = 256; // threads per workgroup of the flat kernel, an (i, j) each
 constexpr int kKT = 16;      // k per thread of it
+// workgroups of the V kernel below which each k's rows of U2 are split over
+// several: two per CU (complex128, rank 25: 64 x 20000 x 1 2207 -> 53 us, 64 x
+// 8000 x 8 922 -> 77; 290^3 306 -> 308, against 316 at 1024)
+constexpr int kVkFill = 512;
+constexpr int kFew = 4;      // columns of V below which it has a kernel of its own
+constexpr int kFewK = 8;     // k per workgroup of that one
 
-// V(j, k) of a Tucker form: one workgroup per k contracts the core with
-// U3(k, :) and applies it to every row of U2.
+// V(j, k) of a Tucker form: a workgroup contracts the core with U3(k, :) of its
+// k and applies it to nj rows of U2.
 template <typename T>
 __global__ void __launch_bounds__(kVNT) k_vk(const c2<T>* __restrict__ G, const c2<T>* __restrict__ U2,
-                                             const c2<T>* __restrict__ U3, c2<T>* __restrict__ V, int n2, int r1, int r2,
-                                             int r3)
+                                             const c2<T>* __restrict__ U3, c2<T>* __restrict__ V, int n2, int nj, int r1,
+                                             int r2, int r3, int rmax)
 {
     const long k = blockIdx.x;
-    v_rows<T>(G, U2, U3 + k * r3, r2, r3, r1, r3, 1, r2 * r3, n2, kRMax, r1, false, V + k * n2 * r1);
+    const int j0 = blockIdx.y * nj;
+    v_rows<T>(G, U2 + (long)j0 * r2, U3 + k * r3, r2, r3, r1, r3, 1, r2 * r3, min(nj, n2 - j0), rmax, r1, false,
+              V + (k * n2 + j0) * r1);
+}
+
+// V(j, k) of fewer columns than k_vk has wavefronts (n1, and so r1, of a plane
+// or two): a thread holds its row of U2 for kFewK values of k, whose
+// contracted cores come by broadcast.  What bounds k_vk there is U2, read again
+// for every k by one wavefront of four.
+template <typename T>
+__global__ void __launch_bounds__(256) k_vk_few(const c2<T>* __restrict__ G, const c2<T>* __restrict__ U2,
+                                                const c2<T>* __restrict__ U3, c2<T>* __restrict__ V, int n2, int n3,
+                                                int r1, int r2, int r3)
+{
+    __shared__ c2<T> W[kFewK * (kFew - 1) * kRMax];   // [k][r1][kRMax], zero beyond r2
+    const int k0 = blockIdx.y * kFewK, nk = min(kFewK, n3 - k0);
+    for (int e = threadIdx.x; e < nk * r1 * kRMax; e += 256) {
+        const int b = e % kRMax, t = e / kRMax, a = t % r1;
+        const c2<T>* u = U3 + (long)(k0 + t / r1) * r3;
+        c2<T> acc = mk<T>(0, 0);
+        if (b < r2)
+            for (int c = 0; c < r3; ++c) fma_c(acc, G[((long)a * r2 + b) * r3 + c], u[c]);
+        W[e] = acc;
+    }
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    const c2<T>* row = U2 + (long)min(j, n2 - 1) * r2;
+    c2<T> u[kRMax];
+#pragma unroll
+    for (int b = 0; b < kRMax; ++b) u[b] = b < r2 ? row[b] : mk<T>(0, 0);
+    __syncthreads();
+    for (int t = 0; t < nk * r1; ++t) {
+        c2<T> even = mk<T>(0, 0), odd = mk<T>(0, 0);
+#pragma unroll
+        for (int h = 0; h < kRMax; h += 4)
+            if (h < r2) {
+#pragma unroll
+                for (int b = h; b < h + 4; ++b) fma_c(b & 1 ? odd : even, u[b], W[t * kRMax + b]);
+            }
+        if (j < n2) V[((long)(k0 + t / r1) * n2 + j) * r1 + t % r1] = even + odd;
+    }
 }
 
 template <typename T>
@@ -175,11 +222,19 @@ hipError_t run(const int n[3], const int r[3], int cp, const void* core, const v
         const long nv = (long)n[2] * n[1] * r[0];
         hipLaunchKernelGGL((k_vjk_cp<T>), dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, G, (const c2<T>*)u2,
                            (const c2<T>*)u3, V, n[1], n[2], r[0]);
+    } else if (r[0] < kFew) {
+        hipLaunchKernelGGL((k_vk_few<T>), dim3((n[1] + 255) / 256, (n[2] + kFewK - 1) / kFewK), dim3(256), 0, s, G,
+                           (const c2<T>*)u2, (const c2<T>*)u3, V, n[1], n[2], r[0], r[1], r[2]);
     } else {
-        const size_t lds = v_rows_lds<T>(kRMax, r[0]);
+        // rows of U2 in tiles of 64: all of them to one workgroup per k, which
+        // contracts the core once, as long as there are kVkFill workgroups
+        const int rmax = std::max(r[0], std::max(r[1], r[2]));
+        const int tiles = (n[1] + 63) / 64, split = std::min(tiles, (kVkFill + n[2] - 1) / n[2]);
+        const int nj = 64 * ((tiles + split - 1) / split);
+        const size_t lds = v_rows_lds<T>(rmax, r[0]);
         (void)hipFuncSetAttribute((const void*)k_vk<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        hipLaunchKernelGGL((k_vk<T>), dim3(n[2]), dim3(kVNT), lds, s, G, (const c2<T>*)u2, (const c2<T>*)u3, V, n[1],
-                           r[0], r[1], r[2]);
+        hipLaunchKernelGGL((k_vk<T>), dim3(n[2], (n[1] + nj - 1) / nj), dim3(kVNT), lds, s, G, (const c2<T>*)u2,
+                           (const c2<T>*)u3, V, n[1], nj, r[0], r[1], r[2], rmax);
     }
     launch_apply<T, kRMax>(r[0], V, U1T, (const c2<T>*)x, (c2<T>*)y, n, s);
     return hipGetLastError();

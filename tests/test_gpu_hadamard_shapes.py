@@ -64,3 +64,33 @@ def test_planes_of_more_than_2_31_rows():
     for k, row in keep.items():
         want = lam[0] * F[0][0, 0] * F[1] * F[2][k, 0] * row
         assert float(((x[k] - want).abs() / want.abs()).max()) <= 20 * U[torch.complex64]
+
+
+# rows of U2 split over workgroups (few k), with a remainder of a tile; V of
+# one to three columns, whose workgroups take eight k, and of four
+@pytest.mark.parametrize("n,r", [((70, 1000, 1), (9, 25, 1)), ((40, 577, 3), (25, 8, 3)), ((33, 65, 511), (6, 5, 7)),
+                                 ((20, 64, 2), (4, 32, 2)), ((30, 300, 17), (1, 32, 16)), ((30, 256, 8), (2, 31, 5)),
+                                 ((30, 257, 9), (3, 4, 9)), ((9, 1, 1), (3, 1, 1)), ((18, 5, 600), (32, 5, 32))])
+@pytest.mark.parametrize("dt", list(U))
+def test_v_of_few_k_and_few_columns(n, r, dt):
+    _check(n, r, False, dt)
+
+
+@pytest.mark.parametrize("n3,dt", [(1, torch.complex64), (2, torch.complex128)])
+def test_few_k_leave_no_cu_idle(n3, dt):
+    # 20000 rows of U2 to a k: in one workgroup each they take over a
+    # millisecond; spread over the chip, the product is bound by its launches
+    rng = np.random.default_rng(0)
+    n, r = (64, 20000, n3), (25, 25, n3)
+    F = [to_dev(_cx(rng, n[a], r[a]), dt) for a in range(3)]
+    core, x = to_dev(_cx(rng, *r), dt), to_dev(_cx(rng, *reversed(n)), dt)
+    best = 1e9
+    for _ in range(5):
+        s, e = torch.cuda.Event(True), torch.cuda.Event(True)
+        s.record()
+        vie.tucker_hadamard(core, F, x)
+        e.record()
+        e.synchronize()
+        best = min(best, s.elapsed_time(e))
+    say("   hadamard few k", n3, dt, best)
+    assert best <= 0.5
