@@ -109,15 +109,11 @@ __global__ void __launch_bounds__(256) k_vk_few(const c2<T>* __restrict__ G, con
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_vjk_cp(const c2<T>* __restrict__ lam, const c2<T>* __restrict__ U2,
-                                                const c2<T>* __restrict__ U3, c2<T>* __restrict__ V, int n2, int n3,
-                                                int r)
+                                                const c2<T>* __restrict__ U3, c2<T>* __restrict__ V, int n2, int r)
 {
-    const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (long)n3 * n2 * r) return;
-    const int a = (int)(e % r);
-    const long jk = e / r;
-    const int j = (int)(jk % n2), k = (int)(jk / n2);
-    V[e] = lam[a] * (U2[(long)j * r + a] * U3[(long)k * r + a]);
+    const int e = blockIdx.x * 256 + threadIdx.x, k = blockIdx.y;   // a column of one k's rows
+    if (e >= n2 * r) return;
+    V[(long)k * n2 * r + e] = lam[e % r] * (U2[e] * U3[(long)k * r + e % r]);
 }
 
 // U1 (n1 x r1) into U1T (r1 x n1), so that the apply kernel's lanes read
@@ -204,7 +200,7 @@ void launch_apply(int r, const c2<T>* V, const c2<T>* U1T, const c2<T>* x, c2<T>
                            dim3(kFlatNT), 0, s, V, U1T, x, y, n[0], n[1], n[2]);
         return;
     }
-    const long rows = (long)n[1] * n[2];
+    const long rows = (long)n[1] * n[2];   // below 2^31: with rows this long, more exceed the memory
     hipLaunchKernelGGL((k_apply<T, R>), dim3((unsigned)((rows + kRun - 1) / kRun), (n[0] + kNT - 1) / kNT), dim3(kNT), 0,
                        s, V, U1T, x, y, n[0], rows);
 }
@@ -219,9 +215,8 @@ hipError_t run(const int n[3], const int r[3], int cp, const void* core, const v
     hipLaunchKernelGGL((k_transpose<T>), dim3((unsigned)(((long)n[0] * r[0] + 255) / 256)), dim3(256), 0, s,
                        (const c2<T>*)u1, U1T, n[0], r[0]);
     if (cp) {
-        const long nv = (long)n[2] * n[1] * r[0];
-        hipLaunchKernelGGL((k_vjk_cp<T>), dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, G, (const c2<T>*)u2,
-                           (const c2<T>*)u3, V, n[1], n[2], r[0]);
+        hipLaunchKernelGGL((k_vjk_cp<T>), dim3((n[1] * r[0] + 255) / 256, n[2]), dim3(256), 0, s, G,
+                           (const c2<T>*)u2, (const c2<T>*)u3, V, n[1], r[0]);
     } else if (r[0] < kFew) {
         hipLaunchKernelGGL((k_vk_few<T>), dim3((n[1] + 255) / 256, (n[2] + kFewK - 1) / kFewK), dim3(256), 0, s, G,
                            (const c2<T>*)u2, (const c2<T>*)u3, V, n[1], n[2], r[0], r[1], r[2]);

@@ -50,20 +50,22 @@ def test_rows_of_few_elements(n1, dt, cp):
         _check((n1, n2, n3), (r, r, r), cp, dt, inplace=r == 7)
 
 
-def test_planes_of_more_than_2_31_rows():
-    # one i, rank 1: 17 GB of x, worked on in place
+@pytest.mark.parametrize("r", [1, 2])
+def test_planes_of_more_than_2_31_rows(r):
+    # one i: 17 GB of x, worked on in place, and V of as much per rank
     m = 46342
     assert m * m > 2 ** 31
     g = torch.Generator(device="cuda")
     g.manual_seed(1)
-    F = [torch.view_as_complex(torch.randn(k, 1, 2, generator=g, device="cuda")) for k in (1, m, m)]
-    lam = torch.view_as_complex(torch.randn(1, 2, generator=g, device="cuda"))
+    F = [torch.view_as_complex(torch.randn(k, r, 2, generator=g, device="cuda")) for k in (1, m, m)]
+    lam = torch.view_as_complex(torch.randn(r, 2, generator=g, device="cuda"))
     x = torch.view_as_complex(torch.randn(m, m, 1, 2, generator=g, device="cuda"))
     keep = {k: x[k].clone() for k in (0, 1, m // 2, m - 2, m - 1)}
     vie.tucker_hadamard(lam, F, x, cp=True, out=x)
     for k, row in keep.items():
-        want = lam[0] * F[0][0, 0] * F[1] * F[2][k, 0] * row
-        assert float(((x[k] - want).abs() / want.abs()).max()) <= 20 * U[torch.complex64]
+        terms = (lam * F[0][0] * F[2][k]).to(torch.complex128) * F[1]
+        want, size = terms.sum(1, keepdim=True) * row, terms.abs().sum(1, keepdim=True) * row.abs()
+        assert float(((x[k] - want).abs() / size).max()) <= 20 * U[torch.complex64]
 
 
 # rows of U2 split over workgroups (few k), with a remainder of a tile; V of
