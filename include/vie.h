@@ -379,8 +379,7 @@ vie_status vie_tucker_cross_pwl(const int n[3], vie_entry_fn fn, void* ctx, int 
  *   core, u1, u2, u3  DEVICE; U_a is n_a x r_a row-major.
  *   x, y   DEVICE [n3][n2][n1]; y may equal x (in place) but not partly overlap it.
  *   ws     DEVICE workspace of vie_tucker_hadamard_ws_bytes: U1 transposed
- *          (n1 r1 complex), V (n3 n2 r1 complex) and, for Tucker, W (n3 r1 r2
- *          complex).
+ *          (n1 r1 complex) and V (n3 n2 r1 complex), for either form.
  * Asynchronous on `stream`.  Errors: VIE_E_ARG, VIE_E_UNSUPPORTED, VIE_E_HIP.
  */
 size_t vie_tucker_hadamard_ws_bytes(const int n[3], const int r[3], int cp, int dtype);

@@ -239,11 +239,11 @@ hipError_t run(const int n[3], const int r[3], int cp, const void* core, const v
 
 extern "C" {
 
-size_t vie_tucker_hadamard_ws_bytes(const int n[3], const int r[3], int cp, int dtype)
+size_t vie_tucker_hadamard_ws_bytes(const int n[3], const int r[3], int, int dtype)
 {
     if (!n || !r) return 0;
     const size_t el = dtype == VIE_C128 ? 16 : 8;
-    return ((size_t)n[0] * r[0] + (cp ? 0 : (size_t)n[2] * r[0] * r[1]) + (size_t)n[2] * n[1] * r[0]) * el;
+    return ((size_t)n[0] * r[0] + (size_t)n[2] * n[1] * r[0]) * el;
 }
 
 vie_status vie_tucker_hadamard(const int n[3], const int r[3], int cp, int dtype, const void* core, const void* u1,

@@ -213,3 +213,14 @@ def test_debug_pass_entry_points_reject_null_arguments():
     assert lib.vie_debug_pad(None, 0, None, None, 1, None) == vie.VIE_E_ARG
     assert lib.vie_debug_crop(None, 0, None, None, 1, None) == vie.VIE_E_ARG
     assert lib.vie_debug_pass(None, 0, 0, 0, 0, 0, None, None, None, None, 1, None) == vie.VIE_E_ARG
+
+
+def test_hadamard_workspace_is_what_the_product_uses():
+    # U1 transposed and V, for either form: no term in the other two ranks
+    import ctypes
+    lib = _lib().load()
+    n = (ctypes.c_int * 3)(30, 20, 10)
+    for cp, r in ((0, (7, 5, 9)), (0, (7, 32, 32)), (1, (7, 7, 7))):
+        for dtype, el in ((0, 8), (1, 16)):
+            got = lib.vie_tucker_hadamard_ws_bytes(n, (ctypes.c_int * 3)(*r), cp, dtype)
+            assert got == (30 * 7 + 10 * 20 * 7) * el
