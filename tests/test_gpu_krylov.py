@@ -73,3 +73,11 @@ class _quiet:
 
     def __exit__(self, *a):
         return self._c.__exit__(*a)
+
+
+# 3 n1 n2 n3 = 635040: two elements per thread of the Gram-Schmidt kernels (the
+# grids above take one, four and eight), as a 64^3 solve does
+@pytest.mark.parametrize("nrhs", [1, 2])
+@pytest.mark.parametrize("dt,bound", [(torch.complex128, 1e-10), (torch.complex64, 1e-3)])
+def test_cycle_with_two_elements_per_thread(nrhs, dt, bound):
+    test_cycle_equals_torch((63, 60, 56), nrhs, 6, dt, bound)
