@@ -18,8 +18,9 @@
 //
 // 300^3, rank 25, complex128, MI355X: 0.94 ms with V read through the vector
 // memory unit by every lane (16 rows of k per thread) and W through HBM;
-// 0.32 ms now, of which 0.25 apply (3.5 TB/s of x and y; three wavefronts a SIMD
-// hold their 25 factors, the scalar loads of V set the pace).
+// 0.32 ms now, of which 0.27 apply: 3.2 TB/s of x and y, the vector units 30 %
+// busy, three quarters of the wavefronts' time spent waiting (25 complex128
+// factors leave three wavefronts a SIMD to hide the loads of x and V).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -50,9 +51,9 @@ template <typename T>
 constexpr int kShort = sizeof(T) == 4 ? 17 : 13;
 constexpr int kFlatNT = 256; // threads per workgroup of the flat kernel, an (i, j) each
 constexpr int kKT = 16;      // k per thread of it
-// workgroups of the V kernel below which each k's rows of U2 are split over
-// several: two per CU (complex128, rank 25: 64 x 20000 x 1 2207 -> 53 us, 64 x
-// 8000 x 8 922 -> 77; 290^3 306 -> 308, against 316 at 1024)
+// workgroups that the V kernel may reach by splitting each k's rows of U2: two
+// per CU (complex128, rank 25: 64 x 20000 x 1 2207 -> 53 us, 64 x 8000 x 8 922 ->
+// 77; 290^3, which keeps one per k, 306, with two 308, with four 316)
 constexpr int kVkFill = 512;
 constexpr int kFew = 4;      // columns of V below which it has a kernel of its own
 constexpr int kFewK = 8;     // k per workgroup of that one
@@ -222,9 +223,9 @@ hipError_t run(const int n[3], const int r[3], int cp, const void* core, const v
                            (const c2<T>*)u2, (const c2<T>*)u3, V, n[1], n[2], r[0], r[1], r[2]);
     } else {
         // rows of U2 in tiles of 64: all of them to one workgroup per k, which
-        // contracts the core once, as long as there are kVkFill workgroups
+        // contracts the core once, or split over as many as kVkFill allows
         const int rmax = std::max(r[0], std::max(r[1], r[2]));
-        const int tiles = (n[1] + 63) / 64, split = std::min(tiles, (kVkFill + n[2] - 1) / n[2]);
+        const int tiles = (n[1] + 63) / 64, split = std::min(tiles, std::max(1, kVkFill / n[2]));
         const int nj = 64 * ((tiles + split - 1) / split);
         const size_t lds = v_rows_lds<T>(rmax, r[0]);
         (void)hipFuncSetAttribute((const void*)k_vk<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
