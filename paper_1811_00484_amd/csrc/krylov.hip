@@ -23,7 +23,7 @@ static constexpr int KEL = 8;        // elements per thread of the one-vector ke
 // Elements per thread of the Gram-Schmidt kernels: eight amortise the
 // reductions on vectors that fill the chip anyway; shorter vectors take fewer
 // until 1024 workgroups share them (a 32^3 grid's 98 304 elements occupied 48
-// of 256 CUs at eight: 50 us for 25 dots, against 39 MB of reads).
+// of 256 CUs at eight: 50 us for 17 dots, against 27 MB of reads).
 static inline int gs_el(long n)
 {
     int el = KEL;

@@ -51,12 +51,13 @@
 //
 // What bounds it: at 120^3 complex64 a group issues about 38 k cycles of vector
 // instructions per SIMD set (0.9 ms in all) in phases that alternate with LDS
-// traffic behind barriers, one 960-thread workgroup per CU; leaving phases out
+// traffic behind barriers, one 960-thread workgroup per CU (vector units 62 %
+// busy, LDS 26 %, of which a third bank conflicts); leaving phases out
 // of a copy, the tables take 0.5 ms, the product 0.3, the transforms and the
 // rest 0.6.  The previous kernel (V contracted in every group, a table entry
-// read per sign, stages through two barriers) took 3.6 ms for the pass, 1.45
+// read per sign, stages through two barriers) took 3.6 ms for the pass, 1.36
 // now; whole products, MI355X: 120^3 4.63 -> 2.14 ms, 36 x 45 x 50 complex128
-// adjoint 0.90 -> 0.28 ms, the coupled product at 60^3 1.95 -> 0.86 ms.
+// adjoint 0.90 -> 0.28 ms, the coupled product at 60^3 1.95 -> 0.87 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
