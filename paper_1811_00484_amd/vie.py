@@ -1140,7 +1140,8 @@ def set_batch_mode(mode):
 
 def autotune(op, dtype=None, nrhs=1):
     """Time the z-pass launch shapes on the device and keep the fastest in the
-    operator (vie_autotune).  Returns (quads per workgroup, {candidate: ms})."""
+    operator, or the shape of an untuned operator if that is faster
+    (vie_autotune).  Returns (fastest quads per workgroup, {candidate: ms})."""
     lib = load()
     dtype = torch.complex64 if dtype is None else dtype
     dt = VIE_C128 if dtype == torch.complex128 else VIE_C64
