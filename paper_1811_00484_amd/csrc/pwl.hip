@@ -626,22 +626,19 @@ size_t pwl_s2_elems(const OpView& v, int nrhs) { return (size_t)12 * v.L[1] * v.
 size_t pwl_s1_elems(const OpView& v, int nrhs) { return (size_t)12 * v.n[2] * v.L[0] * v.n[1] * nrhs; }
 
 // S2, then S1, in whose place the V rows live while S1 is dead (between Y+ and
-// Y-).  They exceed it where the z ranks come near 0.4 n3; S1 then grows to
-// hold them, but to three times its size at most (ranks of n3 take 2.5; padded
-// rows on grids of five voxels along z and fewer would take up to ten) where
-// that is more than kPwlGrow elements.
-constexpr size_t kPwlGrow = (size_t)1 << 17;
+// Y-).  They exceed it where the z ranks come near 0.4 n3 (ranks of n3 take 2.5
+// (n1 + 1) (n2 + 1) / n1 n2 times S1, rows padded to fours on a grid of one
+// voxel along z ten times that); S1 then grows to hold them in one piece, since
+// a slab of a small grid takes as long as its whole pass: complex64 products,
+// MI355X, 18 x 24 x 6 149 us in two slabs, 84 in one, 128 x 126 x 1 503 and 443.
 size_t pwl_ws_elems(const vie_pwl_op& P, int nrhs)
 {
     const OpView& v = P.blk[0]->d.view;
-    const size_t s1 = pwl_s1_elems(v, nrhs), all = pwl_v_elems(P, v.n[0] + 1, v.n[1] + 1);
-    return pwl_s2_elems(v, nrhs) + std::max(s1, std::min(all, std::max(3 * s1, kPwlGrow)));
+    return pwl_s2_elems(v, nrhs) + std::max(pwl_s1_elems(v, nrhs), pwl_v_elems(P, v.n[0] + 1, v.n[1] + 1));
 }
 
 // the least that a product runs in: S1 as it is (and room for one row of every
-// tensor), with the z pass in slabs of (k1, k2), which costs launches and a
-// last round of workgroups each: 64 x 64 x 2 complex64 229 us in one piece, 237
-// in two
+// tensor), with the z pass in slabs of (k1, k2)
 size_t pwl_ws_least(const vie_pwl_op& P, int nrhs)
 {
     const OpView& v = P.blk[0]->d.view;

@@ -3,9 +3,8 @@ take: slabs of k2, and of k1 within one k2, on thin grids (z ranks near n3),
 at every mirror group that the z pass chooses between.
 
 Workspace: the padded components after Y+ (48 n1 n2 n3 complex per vector) and
-the larger of 24 n1 n2 n3 per vector and the rows, padded to whole fours, but
-no more than three times the former where that is above 2^17; accepted down to
-the former (and one row of every component).  Tolerances
+the larger of 24 n1 n2 n3 per vector and the rows, padded to whole fours;
+accepted down to the former (and one row of every component).  Tolerances
 against the FP64 oracle as in the parity tests of the same products
 (complex64 1e-5, complex128 1e-11); the buffers start as NaN and end in a
 guard."""
@@ -85,7 +84,7 @@ def test_products_in_slabs(n, full_rank, dt, nrhs):
         row = 10 * nc * ((rs + 3) // 4 * 4)
         rows = (n[0] + 1) * (n[1] + 1) * row + 12
         least = (2 * s1 + max(s1, row + 12)) * el
-        assert asked <= (2 * s1 + max(s1, min(rows, max(3 * s1, 1 << 17)))) * el
+        assert asked == (2 * s1 + max(s1, rows)) * el
         for nbytes in (asked, least):
             st, y = _run(op, x, e, mode.endswith("H"), nbytes, mode[0])
             assert st == vie.VIE_OK, vie.load().vie_last_error()
@@ -93,6 +92,32 @@ def test_products_in_slabs(n, full_rank, dt, nrhs):
             say("   pwl slabs", n, dt, mode, nrhs, nbytes == least, rs, "%.2e" % err)
             assert err <= BOUND[dt], (mode, nbytes == least)
         assert _run(op, x, e, mode.endswith("H"), least - 1, mode[0])[0] == vie.VIE_E_ARG
+
+
+# thin grids at full ranks: a slab of the small ones takes as long as the whole
+# pass, so the workspace asked for holds the rows in one piece
+@pytest.mark.parametrize("n", [(18, 24, 6), (25, 16, 9), (5, 56, 16), (10, 35, 5), (5, 5, 5), (60, 64, 1),
+                               (140, 126, 1), (126, 128, 2)])
+@pytest.mark.parametrize("dt", list(BOUND))
+def test_the_workspace_asked_for_holds_all_rows(n, dt):
+    rng = np.random.default_rng(sum(n))
+    f = [rng.standard_normal((60, m, 16)) for m in n]   # sixteen terms: z ranks of min(n3, 16)
+    G = np.einsum("bir,bjr,bkr->bkji", *f).reshape(10, 6, n[2], n[1], n[0])
+    for b, pair in enumerate(pwl.PAIRS):
+        for c, pq in enumerate(((0, 0), (1, 1), (2, 2), (0, 1), (0, 2), (1, 2))):
+            for a, odd in enumerate(pwl.odd_axes(*pair, *pq)):   # zero at offset 0
+                if odd:
+                    G[(b, c) + (slice(None),) * (2 - a) + (0,)] = 0
+    op = vie.compress_pwl(G + 0j, tol=1e-13)
+    x = to_dev(_field(n, 43).reshape(1, 12, n[2], n[1], n[0]), dt)
+    s1, rs = 24 * n[0] * n[1] * n[2], int(op.ranks[:, :, 2].max())
+    assert rs == min(n[2], 16)
+    rows = (n[0] + 1) * (n[1] + 1) * 60 * ((rs + 3) // 4 * 4) + 12
+    asked = vie.load().vie_pwl_workspace_bytes(op.handle, vie._dt(x), 1)
+    say("   pwl asked", n, dt, rs, "%.2f" % (rows / s1))
+    assert rows > s1 and asked >= (2 * s1 + rows) * x.element_size()
+    st, y = _run(op, x, x[0, 0], False, asked, "N")
+    assert st == vie.VIE_OK and bool(torch.isfinite(torch.view_as_real(y)).all())
 
 
 @pytest.mark.parametrize("coupled", [False, True])
